@@ -197,9 +197,11 @@ typedef struct {
 /* Launch shape of the collide-stream kernel: block_x threads along x (a
  * multiple of 64), block_y thread rows, rows_per_thread nodes per thread
  * along y.  The tile is block_x x (block_y * rows_per_thread) nodes.
- * ib_threads: workgroup size of the IB pass (one workgroup per body): 0 for
+ * ib_threads: workgroup size of an IB pass of one workgroup per body: 0 for
  * the library's choice (1024 for DF/MDF bodies whose workspace fits in LDS,
- * 512 otherwise), or 256, 512 or 1024 (the second kind takes at most 512). */
+ * 512 otherwise), or 256, 512 or 1024 (the second kind takes at most 512).  A
+ * pass in arcs has the size its markers need, and fused steps the tile shape
+ * that goes with it. */
 typedef struct {
   int32_t block_x, block_y, rows_per_thread;
   int32_t xcd_remap; /* 1: keep neighbouring tiles on one XCD */
@@ -352,21 +354,25 @@ ib_lbm_status ib_lbm_set_graph(ib_lbm_sim *s, int32_t steps_per_graph);
 ib_lbm_status ib_lbm_set_overlap(ib_lbm_sim *s, int32_t on);
 ib_lbm_status ib_lbm_get_overlap(const ib_lbm_sim *s, int32_t *in_use, int64_t *near_nodes);
 
-/* Fused steps (default on).  A pipelined sim (see ib_lbm_set_overlap) whose
- * single body is fixed, DF or MDF on the 1024-thread IB kernel, with BGK or
- * TRT collision and no Zou-He wall, takes one launch per step on the sim's
- * stream, with no second stream and no events.  Workgroup 0 runs the IB
- * pass: it collides the nodes that push into the body's support itself,
- * from the step's input lattice and the force of the previous pass, while
- * the other workgroups collide and stream every node.  The tiles that read
- * the IB force count themselves on the case state before the pass writes
- * the new force.  Results are bitwise those of unpipelined steps, and the
- * steps can be captured and replayed (ib_lbm_set_graph).  The first call
- * builds the list of nodes the pass collides from the body's support (after
- * one pipelined step if none has run; a synchronising copy, and it may
- * allocate); kernel timing (ib_lbm_timing_enable) runs pipelined steps.
- * set_fused(0/1) forbids or allows it; get_fused reports whether the
- * current configuration uses it (after the first step). */
+/* Fused steps (default on, and only with pipelined steps allowed: see
+ * ib_lbm_set_overlap).  A sim without bodies, or whose bodies all run their
+ * pass in arcs (several workgroups per body: every body but coupled MDF,
+ * IB_LBM_UD_TAYLOR_GREEN, atomic spreading, very small circles or dense
+ * markers, and MDF bodies of many markers), takes one launch per step on the
+ * sim's stream, with no second stream and no events, whatever its faces,
+ * collision and motion: the arcs wait for the tiles whose updates they read
+ * and run beside the others.  Of the rest, a pipelined sim whose single body
+ * is fixed, DF or MDF on the 1024-thread IB kernel, with BGK or TRT and no
+ * Zou-He wall, also takes one launch: workgroup 0 runs the IB pass and
+ * collides the nodes that push into the body's support itself.  Results are
+ * bitwise those of unpipelined steps, and the steps can be captured and
+ * replayed (ib_lbm_set_graph).  The first call runs one step the other way
+ * first where a pass has to leave its tables or rectangles (the second form
+ * makes a synchronising copy and may allocate); kernel timing
+ * (ib_lbm_timing_enable) runs pipelined steps.  set_fused(0/1) forbids or
+ * allows it; get_fused reports (after the first step) whether a pipelined
+ * sim with a fixed DF or MDF body, BGK or TRT and no Zou-He wall uses it, 0
+ * for every other sim. */
 ib_lbm_status ib_lbm_set_fused(ib_lbm_sim *s, int32_t on);
 ib_lbm_status ib_lbm_get_fused(const ib_lbm_sim *s, int32_t *in_use);
 

@@ -30,13 +30,23 @@ struct DevBuf {
 struct HostBody {
   ib_lbm_body_desc d;
   BodyDesc dev;  // host copy of the device description
-  DevBuf cos_t, sin_t, ws, tab, acc, markers, lambda, history, state;
+  DevBuf cos_t, sin_t, ws, tab, acc, markers, lambda, history, state, arc_part;
   // fused steps: the force copy and staged pushes (fixed DF/MDF bodies), and
   // the nodes the IB pass collides itself with their push map, built once
   // the device has built the body's tables
   DevBuf fprev, pstage, src;
   bool src_ready = false;
 };
+
+// The IB launches of a step, in the order of their slots: bodies cut into
+// arcs by workgroup size (256, 512, 1024 threads), then bodies of one
+// workgroup on the 1024-thread kernel and on the general one.
+struct IbSlots {
+  int arcs[3] = {0, 0, 0}, fast = 0, general = 0;
+  int arc_lds[3] = {0, 0, 0}, lds = 0;  // dynamic shared memory, bytes
+  int total() const { return arcs[0] + arcs[1] + arcs[2] + fast + general; }
+};
+constexpr int kArcThreads[3] = {256, 512, 1024};
 
 struct EventPair {
   hipEvent_t a, b;
@@ -64,13 +74,12 @@ struct ib_lbm_sim {
   bool tables_dirty = true;
   std::string err;
   CaseDesc cd;  // host copy
-  DevBuf f0, f1, force, state, ticket;
+  DevBuf f0, f1, force, state, ticket, wall_closed;
   std::vector<HostBody> bodies;
   DevBuf d_bodies, d_case, d_prefix, d_slots, d_tmp;
-  int nslots = 0;
   ib_lbm_launch launch = {128, 2, 1, 1};
   int spread_mode = 0;
-  int nslots_fast = 0;    // the first IB slots, run by the 1024-thread kernel
+  IbSlots ib;             // the IB launches of a step
   int graph_steps = 0;
   // captured steps, one graph per parity of the input lattice at its start
   // (the lattice of each step is a kernel argument)
@@ -85,7 +94,6 @@ struct ib_lbm_sim {
   int host_cur = 0;
   int dev = 0;  // the device current at creation
   ib_lbm_batch *batch = nullptr;
-  int lds_bytes = 0;
   // Pipelined steps (see plan_split): the tiles of the hold rectangle and
   // the IB pass run on `iq`, all other tiles on `lq`, ordered by events.
   bool overlap = true;   // allowed by the caller
@@ -103,6 +111,13 @@ struct ib_lbm_sim {
   // 30.7 us per step at 64 x 16 and at 1024 x 1 x 4, FP64 37.0 us at 64 x 16
   // against 40.6 (256 x 4), 43.3 (512 x 2 x 2) and 46.5 (1024 x 1 x 4)
   int fbx = 64, fby = kFusedThreads / 64, frpt = 1;
+  // One-launch steps (see plan_one).  hold_ready: the last step enqueued left
+  // the hold rectangles of the next one (every pass in arcs does).
+  bool one = false;
+  bool hold_ready = false;
+  bool halted = false;  // the case was halted when its state was last read
+  StepOneArgs one_args;
+  int one_threads = 0, one_lds = 0, one_face = 0;
   uint32_t fused_seq = 0;  // sequence number of the last fused launch (CaseState::gate)
 };
 
@@ -120,11 +135,9 @@ struct ib_lbm_batch {
     int general_zg;  // some case has a zero-gradient face other than the east one
   };
   std::vector<Group> groups;
-  int nslots = 0;
-  int lds_bytes = 0;
+  IbSlots ib;
   ib_lbm_launch launch = {128, 2, 1, 1};
   int spread_mode = 0;
-  int nslots_fast = 0;
   int graph_steps = 0;
   hipGraphExec_t graph_exec = nullptr;
   int graph_len = 0;
@@ -257,10 +270,6 @@ int ws_doubles_for(int scheme, int nb, int ns, int mr, int mn, int pop_bytes) {
   return ws_tab_total(scheme, nb, ns, mr, mn) + ws_dyn_doubles(scheme, nb, ns, mn, pop_bytes);
 }
 
-// LDS bytes for an IB launch: enough for the largest workspace that fits;
-// bodies with larger workspaces use their global buffer.
-int lds_budget(int maxws_fitting) { return maxws_fitting * 8; }
-
 void fill_case_tiles(CaseDesc *c, const ib_lbm_launch &l) {
   const int TX = l.block_x, TY = l.block_y * l.rows_per_thread;
   c->tiles_x = (c->nx + TX - 1) / TX;
@@ -295,6 +304,7 @@ LeanArgs lean_args(const ib_lbm_sim *s, int cur, int force_on) {
   a.dst = c.f[cur ^ 1];
   a.force = c.force;
   a.state = c.state;
+  a.halt = &c.state->flags;
   a.nx = c.nx;
   a.ny = c.ny;
   a.nseg = c.nseg;
@@ -355,6 +365,7 @@ ib_lbm_status plan_split(ib_lbm_sim *s) {
 }
 
 bool body_fast(const HostBody &hb, int spread_mode);
+bool body_arcs(const HostBody &hb, int spread_mode);
 static bool has_zou_he(const CaseDesc &c);
 
 // Fused steps (one launch per step, step_fused_kernel): a pipelined sim
@@ -364,11 +375,19 @@ static bool has_zou_he(const CaseDesc &c);
 // thread): the tiles that read the IB force.
 ib_lbm_status plan_fused(ib_lbm_sim *s) {
   s->fused = false;
+  if (s->one) {
+    // what ib_lbm_get_fused reports; every configuration that steps in one
+    // launch each does so alike
+    const CaseDesc &c = s->cd;
+    s->fused = s->split && s->bodies[0].d.motion == IB_LBM_FIXED && s->bodies[0].d.scheme != IB_LBM_DFC &&
+               c.collision != IB_LBM_CMMRT && !has_zou_he(c);
+    return IB_LBM_OK;
+  }
   if (!s->fused_allowed || !s->split || s->bodies.size() != 1) return IB_LBM_OK;
   const HostBody &hb = s->bodies[0];
   const ib_lbm_body_desc &d = hb.d;
   if (d.motion != IB_LBM_FIXED || d.scheme == IB_LBM_DFC || hb.dev.mdf_coupled) return IB_LBM_OK;
-  if (!body_fast(hb, s->spread_mode) || hb.dev.max_nodes >= 32768 || !hb.fprev.p || !hb.pstage.p)
+  if (body_arcs(hb, s->spread_mode) || !body_fast(hb, s->spread_mode) || hb.dev.max_nodes >= 32768 || !hb.fprev.p || !hb.pstage.p)
     return IB_LBM_OK;
   if (s->cd.collision != IB_LBM_BGK && s->cd.collision != IB_LBM_TRT) return IB_LBM_OK;
   if (has_zou_he(s->cd) || pop_values(s->cd.nx, s->cd.ny) >= (int64_t)INT32_MAX) return IB_LBM_OK;
@@ -385,6 +404,71 @@ ib_lbm_status plan_fused(ib_lbm_sim *s) {
   return IB_LBM_OK;
 }
 
+static bool general_zero_gradient(const CaseDesc &c);
+int arc_lds_bytes(const BodyDesc &B);
+
+// One-launch steps (step_one_kernel): a sim without bodies, or whose bodies
+// are all cut into arcs.  The arcs wait for the tiles they depend on while
+// they are resident, so at most kOneMaxArcs workgroups of a launch wait: half
+// of the part's compute units at one workgroup each, the other half always
+// runs tiles.  All workgroups have the size the arcs need (a body-free sim
+// 256 threads).  Tiles are 128 nodes wide on lattices of at least 1024 columns
+// (186 against 192 us per step on 7175 x 2014, 23.8 against 24.5 us on 1200 x
+// 600) and 64 below, where a row's last tile is mostly past its end and the
+// hold rectangle is a larger share (22.0 against 23.6 us on 400 x 2000 FP64).
+constexpr int kOneMaxArcs = 128;
+void plan_one(ib_lbm_sim *s) {
+  s->one = false;
+  if (!s->overlap || !s->fused_allowed) return;
+  const CaseDesc &c = s->cd;
+  StepOneArgs &a = s->one_args;
+  memset(&a, 0, sizeof a);
+  int threads = 256, lds = 0;
+  for (auto &hb : s->bodies) {
+    if (!body_arcs(hb, s->spread_mode)) return;
+    threads = std::max(threads, hb.dev.arc_threads);
+    lds = std::max(lds, arc_lds_bytes(hb.dev));
+  }
+  if (!s->bodies.empty() && s->bodies[0].dev.scheme == kDFC && threads > 512) return;
+  a.bx = c.nx >= 1024 ? 128 : 64;
+  a.by = threads / a.bx;
+  a.lean = lean_args(s, 0, 0);
+  a.lean.rpt = 1;
+  a.lean.remap = 1;
+  const int TX = a.bx, TY = a.by * a.lean.rpt;
+  while ((1 << a.tx_shift) < TX) a.tx_shift++;
+  while ((1 << a.ty_shift) < TY) a.ty_shift++;
+  a.lean.tiles_x = (c.nx + TX - 1) / TX;
+  a.lean.ntiles = a.lean.tiles_x * ((c.ny + TY - 1) / TY);
+  a.nface = (face_nodes(c.nx, c.ny) + threads - 1) / threads;
+  a.cd = c;
+  a.c = (const CaseDesc *)s->d_case.p;
+  for (size_t b = 0; b < s->bodies.size(); b++) {
+    const HostBody &hb = s->bodies[b];
+    // slots for the tiles of its hold rectangle at the speeds a body moves at
+    // (a faster one's further tiles are updated in their turn)
+    double mv = hb.d.motion == IB_LBM_FIXED ? 0.0 : 1.0;
+    if (hb.d.motion == IB_LBM_PRESCRIBED_SIN)
+      mv = std::min(64.0, 2.0 * M_PI * std::fabs(hb.d.freq) *
+                              std::max(std::fabs(hb.d.amp[0]), std::fabs(hb.d.amp[1])));
+    const int w = (int)std::ceil(2.0 * hb.dev.radius + mv) + hb.dev.ns + 8;
+    a.arc_first[b + 1] = a.arc_first[b] + hb.dev.arc_n;
+    a.hold_first[b + 1] = a.hold_first[b] + ((w >> a.tx_shift) + 2) * ((w >> a.ty_shift) + 2);
+  }
+  const size_t nb = s->bodies.size();
+  for (size_t b = nb; b < kMaxBodiesPerCase; b++) {
+    a.arc_first[b + 1] = a.arc_first[nb];
+    a.hold_first[b + 1] = a.hold_first[nb];
+  }
+  a.narcs = a.arc_first[nb];
+  a.nhold = a.hold_first[nb];
+  if (a.narcs > kOneMaxArcs) return;
+  s->one_threads = threads;
+  s->one_lds = lds;
+  s->one_face = has_zou_he(c) ? 2 : (general_zero_gradient(c) ? 1 : 0);
+  s->one = true;
+}
+
 // A body runs on the 1024-thread IB kernel when it is DF/MDF, its workspace
 // fits in LDS and spreading is by gather; the choice depends on the body
 // alone, so a body's results do not depend on its batch-mates.
@@ -392,27 +476,130 @@ bool body_fast(const HostBody &hb, int spread_mode) {
   return spread_mode == 0 && hb.dev.scheme != kDFC && hb.dev.ws_doubles * 8 <= ibm_max_lds_bytes();
 }
 
-// The IB launches of a step: slots [0, nfast) on the 1024-thread kernel,
-// the rest on the general one (bodies of one case may sit in both; the last
-// of a case's workgroups to finish, in either launch, completes the case).
-hipError_t launch_ibm_slots(int precision, const CaseDesc *cases, const IbmSlot *slots, int nfast, int n,
-                            int lds_bytes, int spread_mode, int threads, hipStream_t stream) {
-  hipError_t e = launch_ibm(precision, cases, slots, nfast, lds_bytes, spread_mode, 1, 1, nullptr,
-                            threads, stream);
-  if (e != hipSuccess) return e;
-  return launch_ibm(precision, cases, slots + nfast, n - nfast, lds_bytes, spread_mode, 0, 1, nullptr,
-                    threads, stream);
+// Whether a body's pass runs in arcs (the choice depends on the body and the
+// spreading variant alone, so its results do not depend on its batch-mates).
+bool body_arcs(const HostBody &hb, int spread_mode) { return spread_mode == 0 && hb.dev.arc_n > 0; }
+
+// Cut a body's pass into arcs (arc_device.h).  Markers that share a support
+// node are less than ns apart in x and in y, so less than ns sqrt 2: on the
+// circle of radius R that bounds |l - k| by (n_b / pi) asin(ns sqrt 2 / (2
+// R)), the band half-width bw.  A marker takes ns lanes, so a workgroup of t
+// threads holds t / ns markers: a body of at most that many is one arc, else
+// the own markers of an arc are what the margins on both sides leave.  The
+// margin is bw for DF, 2 bw for DFC (whose correction scale sums over the
+// markers around each one) and N bw for N marker-space MDF passes.
+// Adaptive MDF needs the residual of all markers in every pass, so it runs
+// as one arc or not at all; coupled MDF, Eq. D1 bodies, very small circles
+// and bodies with very dense markers keep the one-workgroup kernels.
+// Workgroup sizes: 256 threads for DF and DFC (short passes, bound by
+// latency: the smallest arcs with margins that still are the smaller part);
+// MDF takes 512 once 256 do not hold the whole body, and 1024 when the
+// margins would outweigh the own markers at 512.
+void plan_arcs(BodyDesc *B) {
+  B->arc_n = 0;
+  if (B->mdf_coupled || B->udes != kUdRigid) return;
+  const double q = B->ns * std::sqrt(2.0) / (2.0 * B->radius);
+  if (!(q < 1.0)) return;
+  const int nb = B->nb, ns = B->ns, bw = (int)std::floor(nb / M_PI * std::asin(q)) + 1;
+  if (bw > 15 || 2 * bw + 1 >= nb) return;
+  const bool mdf = B->scheme == kMDF, adapt = mdf && B->mdf_tol > 0;
+  const int regs = ns == 4 ? kArcBandRegsP4 : kArcBandRegsHat;
+  if (mdf && 2 * bw + 1 > regs * ns) return;
+  const int64_t halo = mdf ? (int64_t)B->mdf_iters * bw : (B->scheme == kDFC ? 2 * bw : bw);
+  for (int t : kArcThreads) {
+    const int cap = t / ns;
+    int own = 0, n = 0;
+    if (nb <= cap) {
+      own = nb;
+      n = 1;
+    } else if (!adapt && cap - 2 * halo >= cap / 3) {
+      n = (int)((nb + cap - 2 * halo - 1) / (cap - 2 * halo));
+      own = (nb + n - 1) / n;
+      n = (nb + own - 1) / own;
+    }
+    if (B->scheme == kDFC && t > 512) break;
+    if (n == 0 || n > kArcMax) continue;
+    const int nl = n == 1 ? nb : own + 2 * (int)halo;
+    if (n > 1 && nl > nb) continue;
+    if (arc_lds_doubles(B->scheme, ns, bw, nl) * 8 > 64 * 1024) continue;
+    B->arc_n = n;
+    B->arc_own = own;
+    B->arc_halo = (int)halo;
+    B->arc_bw = bw;
+    B->arc_threads = t;
+    return;
+  }
+}
+
+int arc_lds_bytes(const BodyDesc &B) {
+  const int nl = B.arc_n == 1 ? B.nb : B.arc_own + 2 * B.arc_halo;
+  return arc_lds_doubles(B.scheme, B.ns, B.arc_bw, nl) * 8;
+}
+
+// The slots of `n` cases' bodies in launch order (see IbSlots).  all_fast:
+// per case, whether a coupled case runs on the 1024-thread kernel.
+struct SlotLists {
+  std::vector<IbmSlot> arcs[3], fast, general;
+  IbSlots ib;
+  void add(const std::vector<HostBody> &bodies, int cas, int spread_mode) {
+    const int n = std::max<int>(1, (int)bodies.size());
+    if (bodies.empty()) general.push_back({cas, -1, 1, 0});
+    // the bodies of a coupled MDF case meet during their passes, so they run
+    // in one launch: the fast instance only if every one of them fits it
+    bool all_fast = !bodies.empty();
+    for (auto &hb : bodies) all_fast &= body_fast(hb, spread_mode);
+    const bool coupled = !bodies.empty() && bodies[0].dev.mdf_coupled;
+    for (int b = 0; b < (int)bodies.size(); b++) {
+      const BodyDesc &B = bodies[b].dev;
+      if (body_arcs(bodies[b], spread_mode)) {
+        const int t = B.arc_threads == 256 ? 0 : (B.arc_threads == 512 ? 1 : 2);
+        for (int a = 0; a < B.arc_n; a++) arcs[t].push_back({cas, b, n, a});
+        ib.arc_lds[t] = std::max(ib.arc_lds[t], arc_lds_bytes(B));
+        continue;
+      }
+      ((coupled ? all_fast : body_fast(bodies[b], spread_mode)) ? fast : general).push_back({cas, b, n, 0});
+      if (B.ws_doubles * 8 <= ibm_max_lds_bytes()) ib.lds = std::max(ib.lds, B.ws_doubles * 8);
+    }
+  }
+  std::vector<IbmSlot> finish() {
+    std::vector<IbmSlot> all;
+    for (int t = 0; t < 3; t++) {
+      ib.arcs[t] = (int)arcs[t].size();
+      all.insert(all.end(), arcs[t].begin(), arcs[t].end());
+    }
+    ib.fast = (int)fast.size();
+    all.insert(all.end(), fast.begin(), fast.end());
+    ib.general = (int)general.size();
+    all.insert(all.end(), general.begin(), general.end());
+    return all;
+  }
+};
+
+// The IB launches of a step (bodies of one case may sit in several; the last
+// body to finish, in whichever launch, completes the case).
+hipError_t launch_ibm_slots(int precision, const CaseDesc *cases, const IbmSlot *slots, const IbSlots &ib,
+                            int spread_mode, int threads, hipStream_t stream) {
+  hipError_t e = hipSuccess;
+  for (int t = 0; t < 3 && e == hipSuccess; t++) {
+    e = launch_ibm_arcs(precision, cases, slots, ib.arcs[t], ib.arc_lds[t], kArcThreads[t], stream);
+    slots += ib.arcs[t];
+  }
+  if (e == hipSuccess)
+    e = launch_ibm(precision, cases, slots, ib.fast, ib.lds, spread_mode, 1, 1, nullptr, threads, stream);
+  if (e == hipSuccess)
+    e = launch_ibm(precision, cases, slots + ib.fast, ib.general, ib.lds, spread_mode, 0, 1, nullptr,
+                   threads, stream);
+  return e;
 }
 
 ib_lbm_status build_sim_tables(ib_lbm_sim *s) {
   if (!s->tables_dirty) return IB_LBM_OK;
   ib_lbm_status st0;
   std::vector<BodyDesc> bd;
-  int maxws = 0;
-  for (auto &hb : s->bodies) {
-    bd.push_back(hb.dev);
-    if (hb.dev.ws_doubles * 8 <= ibm_max_lds_bytes()) maxws = std::max(maxws, hb.dev.ws_doubles);
-  }
+  for (auto &hb : s->bodies) bd.push_back(hb.dev);
+  SlotLists lists;
+  lists.add(s->bodies, 0, s->spread_mode);
+  const std::vector<IbmSlot> slots = lists.finish();
   if (!bd.empty()) {
     if (!s->d_bodies.p || s->d_bodies.bytes < bd.size() * sizeof(BodyDesc)) {
       dev_free(s, &s->d_bodies);
@@ -429,32 +616,20 @@ ib_lbm_status build_sim_tables(ib_lbm_sim *s) {
     if (st) return st;
     st = dev_alloc(s, &s->d_prefix, sizeof(int32_t) * 4);
     if (st) return st;
-    st = dev_alloc(s, &s->d_slots, sizeof(IbmSlot) * kMaxBodiesPerCase);
+  }
+  if (s->d_slots.bytes < slots.size() * sizeof(IbmSlot)) {
+    dev_free(s, &s->d_slots);
+    ib_lbm_status st = dev_alloc(s, &s->d_slots, slots.size() * sizeof(IbmSlot));
     if (st) return st;
   }
   HIPCHK(s, hipMemcpy(s->d_case.p, &s->cd, sizeof(CaseDesc), hipMemcpyHostToDevice));
   // tile prefix {0, tiles}, then face workgroup prefix {0, face workgroups}
   int32_t pre[4] = {0, s->cd.tiles_x * s->cd.tiles_y, 0, face_blocks(s->cd.nx, s->cd.ny)};
   HIPCHK(s, hipMemcpy(s->d_prefix.p, pre, sizeof pre, hipMemcpyHostToDevice));
-  std::vector<IbmSlot> slots, rest;
-  const int n = std::max(1, (int)bd.size());
-  // the bodies of a coupled MDF case meet during their passes, so they run
-  // in one launch: the fast instance only if every one of them fits it
-  bool all_fast = !bd.empty();
-  for (int b = 0; b < (int)bd.size(); b++) all_fast &= body_fast(s->bodies[b], s->spread_mode);
-  const bool coupled = !bd.empty() && bd[0].mdf_coupled;
-  for (int b = 0; b < n; b++) {
-    const IbmSlot sl{0, bd.empty() ? -1 : b, n, 0};
-    const bool fast = !bd.empty() && (coupled ? all_fast : body_fast(s->bodies[b], s->spread_mode));
-    if (fast) slots.push_back(sl);
-    else rest.push_back(sl);
-  }
-  s->nslots_fast = (int)slots.size();
-  slots.insert(slots.end(), rest.begin(), rest.end());
   HIPCHK(s, hipMemcpy(s->d_slots.p, slots.data(), slots.size() * sizeof(IbmSlot), hipMemcpyHostToDevice));
-  s->nslots = n;
-  s->lds_bytes = lds_budget(maxws);
+  s->ib = lists.ib;
   if ((st0 = plan_split(s))) return st0;
+  plan_one(s);
   if ((st0 = plan_fused(s))) return st0;
   s->tables_dirty = false;
   drop_graphs(s);
@@ -512,8 +687,7 @@ ib_lbm_status enqueue_sim_step(ib_lbm_sim *s, bool timed, hipStream_t stream, in
     HIPCHK(s, hipEventRecord(p1.a, stream));
   }
   HIPCHK(s, launch_ibm_slots(s->cd.precision, (const CaseDesc *)s->d_case.p, (const IbmSlot *)s->d_slots.p,
-                             s->nslots_fast, s->nslots, s->lds_bytes, s->spread_mode,
-                             s->launch.ib_threads, stream));
+                             s->ib, s->spread_mode, s->launch.ib_threads, stream));
   if (timed) {
     HIPCHK(s, hipEventRecord(p1.b, stream));
     s->timing.ev[1].push_back(p1);
@@ -534,8 +708,8 @@ ib_lbm_status ensure_pipe_streams(ib_lbm_sim *s) {
     HIPCHK(s, hipGetDevice(&dev));
     HIPCHK(s, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     std::vector<uint32_t> mask((ncu + 31) / 32, 0u);
-    for (int i = 0; i < ncu - s->nslots; i++) mask[i / 32] |= 1u << (i % 32);
-    if (ncu <= s->nslots ||
+    for (int i = 0; i < ncu - 1; i++) mask[i / 32] |= 1u << (i % 32);
+    if (ncu < 2 ||
         hipExtStreamCreateWithCUMask(&s->lq, (uint32_t)mask.size(), mask.data()) != hipSuccess) {
       (void)hipGetLastError();
       s->lq = nullptr;
@@ -559,6 +733,20 @@ ib_lbm_status ensure_pipe_streams(ib_lbm_sim *s) {
   if (!s->ev_near) HIPCHK(s, hipEventCreateWithFlags(&s->ev_near, evf));
   if (!s->ev_far) HIPCHK(s, hipEventCreateWithFlags(&s->ev_far, evf));
   return IB_LBM_OK;
+}
+
+// The IB pass of a pipelined step's single body: its arcs, or one copy of
+// its workgroup per XCD, the first of which to start runs the pass (the far
+// tiles on the other stream fill the chip).
+hipError_t launch_ibm_pipelined(ib_lbm_sim *s, hipStream_t stream, LaunchTarget *ns) {
+  const CaseDesc *dc = (const CaseDesc *)s->d_case.p;
+  const IbmSlot *slots = (const IbmSlot *)s->d_slots.p;
+  for (int t = 0; t < 3; t++)
+    if (s->ib.arcs[t])
+      return launch_ibm_arcs(s->cd.precision, dc, slots, s->ib.arcs[t], s->ib.arc_lds[t], kArcThreads[t],
+                             stream, ns);
+  return launch_ibm(s->cd.precision, dc, slots, 1, s->ib.lds, s->spread_mode, s->ib.fast, 8,
+                    (uint32_t *)s->ticket.p, s->launch.ib_threads, stream, ns);
 }
 
 // Enqueue nsteps pipelined steps after the work already on `main`, the
@@ -622,13 +810,9 @@ ib_lbm_status enqueue_pipelined(ib_lbm_sim *s, int64_t nsteps, bool timed, hipSt
       p1 = take_pair(s->timing);
       HIPCHK(s, hipEventRecord(p1.a, s->iq));
     }
-    // one copy of the single body's IB workgroup per XCD; the first to start
-    // runs the pass (the far tiles on the other stream fill the chip)
     LaunchTarget ib_done;
     ib_done.done = last ? s->ev_iq : nullptr;
-    HIPCHK(s, launch_ibm(s->cd.precision, dc, (const IbmSlot *)s->d_slots.p, 1, s->lds_bytes,
-                         s->spread_mode, s->nslots_fast, 8, (uint32_t *)s->ticket.p,
-                         s->launch.ib_threads, s->iq, &ib_done));
+    HIPCHK(s, launch_ibm_pipelined(s, s->iq, &ib_done));
     if (timed) {
       HIPCHK(s, hipEventRecord(p1.b, s->iq));
       s->timing.ev[1].push_back(p1);
@@ -690,9 +874,7 @@ ib_lbm_status build_pipelined_graph(ib_lbm_sim *s, int64_t nsteps, int cur0, hip
       if (z) lq_end = z;
     }
     hipGraphNode_t ib = add({hold ? hold : prev_ib}, [&](LaunchTarget *ns) {
-      return launch_ibm(s->cd.precision, dc, (const IbmSlot *)s->d_slots.p, 1, s->lds_bytes,
-                        s->spread_mode, s->nslots_fast, 8, (uint32_t *)s->ticket.p,
-                        s->launch.ib_threads, nullptr, ns);
+      return launch_ibm_pipelined(s, nullptr, ns);
     });
     if (lq_end) prev_lq = lq_end;
     if (hold) prev_hold = hold;
@@ -793,8 +975,28 @@ ib_lbm_status enqueue_fused(ib_lbm_sim *s, int64_t nsteps, hipStream_t stream, i
     fa.gated = s->cd.precision == IB_LBM_FP32_SHIFTED ? 1 : 0;
     fa.cd = s->cd;
     fa.bd = s->bodies[0].dev;
-    HIPCHK(s, launch_step_fused(s->cd.precision, s->cd.collision, fa, s->lds_bytes, stream));
+    HIPCHK(s, launch_step_fused(s->cd.precision, s->cd.collision, fa, s->ib.lds, stream));
   }
+  return IB_LBM_OK;
+}
+
+// Enqueue nsteps one-launch steps on `stream` from input lattice cur0.  A step
+// leaves its Zou-He wall nodes open: the next one closes what it reads, and
+// the last one's are closed here.
+ib_lbm_status enqueue_one(ib_lbm_sim *s, int64_t nsteps, hipStream_t stream, int cur0) {
+  StepOneArgs a = s->one_args;
+  for (int64_t i = 0; i < nsteps; i++) {
+    const int cur = cur0 ^ (int)(i & 1);
+    a.cur = cur;
+    a.lean.src = s->cd.f[cur];
+    a.lean.dst = s->cd.f[cur ^ 1];
+    a.lean.halt = &s->cd.state->halt[cur];
+    a.zh_fold = i > 0;
+    HIPCHK(s, launch_step_one(s->cd.precision, s->one_face, !s->bodies.empty() && s->bodies[0].dev.scheme == kDFC,
+                              a, s->one_threads, s->one_lds, stream));
+  }
+  if (has_zou_he(s->cd) && nsteps > 0)
+    HIPCHK(s, launch_zou_he(s->cd.precision, (const CaseDesc *)s->d_case.p, s->cd.nx, s->cd.ny, -2, stream));
   return IB_LBM_OK;
 }
 
@@ -802,7 +1004,11 @@ ib_lbm_status enqueue_fused(ib_lbm_sim *s, int64_t nsteps, hipStream_t stream, i
 // pipelined when the sim allows it and `pipelined` is set.
 ib_lbm_status enqueue_steps(ib_lbm_sim *s, int64_t nsteps, bool timed, hipStream_t stream, int cur0,
                             bool pipelined) {
-  if (s->fused && s->bodies[0].src_ready && !timed) return enqueue_fused(s, nsteps, stream, cur0);
+  if (s->one && s->hold_ready && !timed) return enqueue_one(s, nsteps, stream, cur0);
+  bool arcs = true;
+  for (auto &hb : s->bodies) arcs &= body_arcs(hb, s->spread_mode);
+  s->hold_ready = nsteps > 0 ? arcs : s->hold_ready;
+  if (s->fused && !s->one && s->bodies[0].src_ready && !timed) return enqueue_fused(s, nsteps, stream, cur0);
   if (s->split && pipelined) return enqueue_pipelined(s, nsteps, timed, stream, cur0);
   for (int64_t i = 0; i < nsteps; i++) {
     ib_lbm_status st = enqueue_sim_step(s, timed, stream, cur0 ^ (int)(i & 1));
@@ -821,6 +1027,7 @@ ib_lbm_status read_state(ib_lbm_sim *s, CaseState *cs) {
   HIPCHK(s, hipStreamSynchronize(s->stream));
   HIPCHK(s, hipMemcpy(cs, s->state.p, sizeof(CaseState), hipMemcpyDeviceToHost));
   s->host_cur = cs->cur;
+  s->halted = (cs->flags & kCaseHalted) != 0;
   return IB_LBM_OK;
 }
 
@@ -834,8 +1041,11 @@ size_t ib_lbm_footprint(const ib_lbm_config *cfg, int32_t n_bodies, const int32_
   if (!cfg) return 0;
   const size_t elem = cfg->precision == IB_LBM_FP64 ? 8 : 4;
   const size_t n = (size_t)cfg->nx * cfg->ny;
+  bool has_zou = false;
+  for (int f = 0; f < 4; f++) has_zou |= cfg->bc[f] == IB_LBM_ZOU_HE;
   const size_t lat = cfg->nx > 0 && cfg->ny > 0 ? (size_t)pop_values(cfg->nx, cfg->ny) : 0;
-  size_t bytes = 2 * lat * elem + 2 * n * elem + sizeof(CaseState) + sizeof(CaseDesc) + 256;
+  size_t bytes = 2 * lat * elem + 2 * n * elem + sizeof(CaseState) + sizeof(CaseDesc) + 256 +
+                 (has_zou ? (size_t)wall_nodes(cfg->nx, cfg->ny) : 0);
   const int hist = cfg->history_capacity > 0 ? cfg->history_capacity : 4096;
   for (int b = 0; b < n_bodies; b++) {
     const int nb = n_markers ? n_markers[b] : 256;
@@ -848,7 +1058,8 @@ size_t ib_lbm_footprint(const ib_lbm_config *cfg, int32_t n_bodies, const int32_
                                    std::max(2 * nb, ws_coupled_doubles(nb, mn))) +
                       ws_tab_total(kMDF, nb, 4, mr, mn) + 2 * mn) * 8 +
              (size_t)nb * (8 + 1 + 2) * 8 +
-             (size_t)hist * kHistCols * 8 + sizeof(BodyState) + sizeof(BodyDesc);
+             (size_t)hist * kHistCols * 8 + sizeof(BodyState) + sizeof(BodyDesc) +
+             (size_t)kArcMax * (64 + sizeof(IbmSlot));
   }
   return bytes;
 }
@@ -928,6 +1139,12 @@ ib_lbm_status ib_lbm_create(const ib_lbm_config *cfg, ib_lbm_sim **out) {
   if ((st = dev_alloc(s, &s->f1, lat))) return fail(st, s->err.c_str());
   if ((st = dev_alloc(s, &s->force, 2 * (size_t)c.plane * elem))) return fail(st, s->err.c_str());
   if ((st = dev_alloc(s, &s->state, sizeof(CaseState)))) return fail(st, s->err.c_str());
+  if (has_zou_he(c)) {
+    const size_t nw = (size_t)wall_nodes(c.nx, c.ny);
+    if ((st = dev_alloc(s, &s->wall_closed, nw))) return fail(st, s->err.c_str());
+    if (hipMemset(s->wall_closed.p, 0, nw) != hipSuccess) return fail(IB_LBM_E_DEVICE, "wall flags");
+    c.wall_closed = (uint8_t *)s->wall_closed.p;
+  }
   c.f[0] = s->f0.p;
   c.f[1] = s->f1.p;
   c.force = s->force.p;
@@ -1092,6 +1309,7 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
       B.ws_doubles += extra;
     }
   }
+  plan_arcs(&B);
   // gather window: a node within s*sqrt(2) of marker k lies within angle
   // 2 asin(s / sqrt(2 R (R - s sqrt 2))) of it
   {
@@ -1116,6 +1334,7 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
   if ((st = dev_alloc(s, &hb.lambda, (size_t)nb * 8))) return st;
   if ((st = dev_alloc(s, &hb.history, (size_t)B.hist_cap * kHistCols * 8))) return st;
   if ((st = dev_alloc(s, &hb.state, sizeof(BodyState)))) return st;
+  if ((st = dev_alloc(s, &hb.arc_part, (size_t)std::max(B.arc_n, 1) * 8 * 8))) return st;
   HIPCHK(s, hipMemcpy(hb.cos_t.p, ct.data(), nb * 8, hipMemcpyHostToDevice));
   HIPCHK(s, hipMemcpy(hb.sin_t.p, stb.data(), nb * 8, hipMemcpyHostToDevice));
   HIPCHK(s, hipMemset(hb.markers.p, 0, (size_t)nb * 64));
@@ -1129,6 +1348,7 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
   B.lambda_cache = (double *)hb.lambda.p;
   B.history = (double *)hb.history.p;
   B.state = (BodyState *)hb.state.p;
+  B.arc_part = (double *)hb.arc_part.p;
   B.src = nullptr;
   B.n_src = 0;
   B.fprev = nullptr;
@@ -1165,7 +1385,19 @@ ib_lbm_status ib_lbm_step(ib_lbm_sim *s, int64_t nsteps) {
   if (s->split && (st = ensure_pipe_streams(s))) return st;
   s->started = true;
   int64_t left = nsteps;
-  if (s->fused && !s->bodies[0].src_ready && left > 0 && !s->timing.on) {
+  if (s->halted) {
+    // a halted case's kernels do nothing
+    s->host_steps += nsteps;
+    return IB_LBM_OK;
+  }
+  if (s->one && !s->hold_ready && left > 0 && !s->timing.on) {
+    // one-launch steps need the hold rectangles that a pass leaves: one plain
+    // step first
+    if ((st = enqueue_steps(s, 1, false, s->stream, s->host_cur, false))) return st;
+    s->host_cur ^= 1;
+    left -= 1;
+  }
+  if (s->fused && !s->one && !s->bodies[0].src_ready && left > 0 && !s->timing.on) {
     // fused steps start from the support the device builds at the body's
     // first IB pass: one pipelined step first if none has run
     if (s->host_steps == 0) {
@@ -1189,7 +1421,7 @@ ib_lbm_status ib_lbm_step(ib_lbm_sim *s, int64_t nsteps) {
     // pipelined steps: an explicitly built graph per starting lattice, both
     // made at the first replay; plain steps: captured on a private stream
     // (the caller's may be the null stream); replayed on the caller's stream
-    if (s->split && !s->fused) {
+    if (s->split && !s->fused && !s->one) {
       for (int p = 0; p < 2; p++)
         if (!s->graph_exec[p] && (st = build_pipelined_graph(s, s->graph_len, p, &s->graph_exec[p])))
           return st;
@@ -1506,9 +1738,10 @@ ib_lbm_status ib_lbm_destroy(ib_lbm_sim *s) {
     dev_free(s, &hb.tab); dev_free(s, &hb.acc);
     dev_free(s, &hb.lambda); dev_free(s, &hb.history); dev_free(s, &hb.state);
     dev_free(s, &hb.fprev); dev_free(s, &hb.pstage); dev_free(s, &hb.src);
+    dev_free(s, &hb.arc_part);
   }
   dev_free(s, &s->f0); dev_free(s, &s->f1); dev_free(s, &s->force); dev_free(s, &s->state);
-  dev_free(s, &s->ticket);
+  dev_free(s, &s->ticket); dev_free(s, &s->wall_closed);
   dev_free(s, &s->d_bodies); dev_free(s, &s->d_case); dev_free(s, &s->d_prefix);
   dev_free(s, &s->d_slots); dev_free(s, &s->d_tmp);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
@@ -1740,6 +1973,8 @@ ib_lbm_status ib_lbm_batch_detach(ib_lbm_batch *b, ib_lbm_sim *s) {
   cs.target = std::numeric_limits<int64_t>::max();
   BHIPCHK(b, hipMemcpy(s->state.p, &cs, sizeof cs, hipMemcpyHostToDevice));
   s->host_cur = cs.cur;
+  s->halted = (cs.flags & kCaseHalted) != 0;
+  s->hold_ready = false;
   return IB_LBM_OK;
 }
 
@@ -1765,7 +2000,6 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
   std::vector<ib_lbm_sim *> case_sims;  // the sim of each case entry
   std::vector<int32_t> fprefix;
   b->groups.clear();
-  int maxws = 0;
   for (int col = 0; col < 3; col++) {
     ib_lbm_batch::Group g{col, (int)cases.size(), 0, 0, (int)prefix.size(), 0, 0};
     int tiles = 0, faces = 0;
@@ -1781,8 +2015,6 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
       case_sims.push_back(s);
       g.count++;
       g.general_zg |= general_zero_gradient(c) ? 1 : 0;
-      for (auto &hb : s->bodies)
-        if (hb.dev.ws_doubles * 8 <= ibm_max_lds_bytes()) maxws = std::max(maxws, hb.dev.ws_doubles);
     }
     prefix.push_back(tiles);
     fprefix.push_back(faces);
@@ -1790,17 +2022,9 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
     g.nface_blocks = faces;
     if (g.count) b->groups.push_back(g);
   }
-  std::vector<IbmSlot> rest;
-  for (int ci = 0; ci < (int)cases.size(); ci++) {
-    const int n = std::max(1, cases[ci].nbodies);
-    for (int k = 0; k < n; k++) {
-      const IbmSlot sl{ci, cases[ci].nbodies ? k : -1, n, 0};
-      if (cases[ci].nbodies && body_fast(case_sims[ci]->bodies[k], b->spread_mode)) slots.push_back(sl);
-      else rest.push_back(sl);
-    }
-  }
-  b->nslots_fast = (int)slots.size();
-  slots.insert(slots.end(), rest.begin(), rest.end());
+  SlotLists lists;
+  for (int ci = 0; ci < (int)cases.size(); ci++) lists.add(case_sims[ci]->bodies, ci, b->spread_mode);
+  slots = lists.finish();
   auto upload = [&](DevBuf *d, const void *src, size_t bytes) -> ib_lbm_status {
     if (d->bytes < bytes) {
       if (d->p) (void)hipFree(d->p);
@@ -1821,9 +2045,7 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
     if ((st = upload(&b->d_fprefix, fprefix.data(), fprefix.size() * sizeof(int32_t)))) return st;
     if ((st = upload(&b->d_slots, slots.data(), slots.size() * sizeof(IbmSlot)))) return st;
   }
-  b->nslots = (int)slots.size();
-  b->lds_bytes = lds_budget(maxws);
-
+  b->ib = lists.ib;
   b->dirty = false;
   return IB_LBM_OK;
 }
@@ -1840,8 +2062,7 @@ static ib_lbm_status batch_enqueue_step(ib_lbm_batch *b, hipStream_t stream) {
                                            g.nface_blocks, -1, 1, g.general_zg, stream));
   }
   BHIPCHK(b, launch_ibm_slots(b->precision, (const CaseDesc *)b->d_cases.p, (const IbmSlot *)b->d_slots.p,
-                              b->nslots_fast, b->nslots, b->lds_bytes, b->spread_mode,
-                              b->launch.ib_threads, stream));
+                              b->ib, b->spread_mode, b->launch.ib_threads, stream));
   return IB_LBM_OK;
 }
 
@@ -1901,6 +2122,7 @@ ib_lbm_status ib_lbm_batch_set_spread(ib_lbm_batch *b, int32_t mode) {
   if (!b) return IB_LBM_E_INVALID;
   if (mode != IB_LBM_SPREAD_GATHER && mode != IB_LBM_SPREAD_ATOMIC) return IB_LBM_E_INVALID;
   b->spread_mode = mode;
+  b->dirty = true;
   if (b->graph_exec) {
     (void)hipGraphExecDestroy(b->graph_exec);
     b->graph_exec = nullptr;

@@ -85,6 +85,14 @@ struct CaseState {
   // takes the support's moments after all of them, then resets it.
   int32_t src_seen;
   double xr[2][kMaxBodiesPerCase];
+  // One-launch steps (step_one_kernel), by the step's input lattice: the
+  // words that a launch's tiles read while its IB pass already prepares the
+  // next step's.  halt[cur]: the case was halted by an earlier launch;
+  // hold[cur][b]: nodes (x0 y0 x1 y1) whose updates body b's pass waits for,
+  // its support widened by two nodes and the nodes that carry its force.
+  int32_t halt[2];
+  int32_t hold[2][kMaxBodiesPerCase][4];
+  int32_t hold_done[kMaxBodiesPerCase];  // workgroups of this launch that updated such nodes
 };
 
 // Mutable per-body state, device resident.
@@ -105,6 +113,8 @@ struct BodyState {
   int32_t lambda_valid; // DFC cache filled (fixed bodies)
   int32_t tables_valid; // geometry tables cached (fixed bodies)
   int32_t tables_full;  // a step needs the whole cached table, not only its hot part
+  int32_t arrived;      // arcs of this step that have left their sums in arc_part
+  int32_t arc_sync;     // DFC: arcs of this step that have read their populations
 };
 
 // A node whose pushes reach the support of a fused step's body: the offset
@@ -157,6 +167,12 @@ struct BodyDesc {
   int32_t pad_src;
   void *fprev;
   void *pstage;
+  // The pass in arcs (arc_device.h): arc_n workgroups of arc_own markers
+  // each (0: the body is not cut; see plan_arcs), with a margin of arc_halo
+  // markers on either side, couplings up to arc_bw markers apart, at least
+  // arc_threads threads; arc_part: 8 doubles per arc.
+  int32_t arc_n, arc_own, arc_halo, arc_bw, arc_threads, pad_arc;
+  double *arc_part;
   BodyState *state;
 };
 
@@ -177,6 +193,9 @@ struct CaseDesc {
   void *force;          // IB force density, 2 planes
   CaseState *state;
   BodyDesc *bodies;     // device array of nbodies
+  // Zou-He walls, one-launch steps: per perimeter node (wall_index), 1 while
+  // it holds closed populations that DFC has corrected since
+  uint8_t *wall_closed;
 };
 
 // Workspace of one body, in doubles.  The table part (marker geometry,
@@ -224,13 +243,28 @@ __host__ __device__ inline int ws_dyn_doubles(int scheme, int nb, int ns, int mn
 // and the node velocities before a trial pass (2 mn)
 __host__ __device__ inline int ws_coupled_doubles(int nb, int mn) { return 4 * nb + 2 * mn; }
 
+// Largest band half-width of marker-space MDF in arcs: a lane keeps its share
+// of the 2 bw + 1 entries, ceil((2 bw + 1) / ns), in registers.
+constexpr int kArcBandRegsP4 = 5;   // bw <= 9
+constexpr int kArcBandRegsHat = 6;  // bw <= 5
+constexpr int kArcMax = 64;         // arcs per body (one wave sums them)
+// LDS entries of an arc of nl local markers (a margin of bw on both sides,
+// ns of slack behind the last lane's share of the band) and its shared memory
+// in doubles: forces, weights, the band (MDF) or the corrections (DFC), and
+// the packed stencil origins.
+__host__ __device__ inline int arc_entries(int ns, int bw, int nl) { return nl + 2 * bw + ns; }
+__host__ __device__ inline int arc_lds_doubles(int scheme, int ns, int bw, int nl) {
+  const int e = arc_entries(ns, bw, nl);
+  return e * (4 + 4 * ns + 2 + (scheme == 2 ? 9 : (scheme == 1 ? bw + 1 : 0))) + (e + 1) / 2;
+}
+
 // One IB workgroup: the body `body` of case `cas` (body = -1: a case without
 // bodies, which only advances the step counter).
 struct IbmSlot {
   int32_t cas;
   int32_t body;
-  int32_t slots_in_case;
-  int32_t pad;
+  int32_t slots_in_case;  // bodies of the case (1 for a case without)
+  int32_t arc;            // the arc of the body (arc launches)
 };
 
 // Number of face nodes of an nx x ny lattice: rows y = 0 and ny-1, columns
@@ -242,6 +276,13 @@ __host__ __device__ inline int face_nodes(int nx, int ny) { return 2 * nx + 3 * 
 constexpr int kFaceBlock = 256;
 __host__ __device__ inline int face_blocks(int nx, int ny) {
   return (face_nodes(nx, ny) + kFaceBlock - 1) / kFaceBlock;
+}
+
+// Perimeter index of a wall node: rows y = 0 and ny-1, then the columns
+// x = 0 and nx-1 between them.
+__host__ __device__ inline int wall_nodes(int nx, int ny) { return 2 * nx + 2 * (ny - 2); }
+__host__ __device__ inline int wall_index(int nx, int ny, int x, int y) {
+  return y == 0 ? x : (y == ny - 1 ? nx + x : 2 * nx + (x == 0 ? 0 : ny - 2) + y - 1);
 }
 
 struct LaunchShape {
@@ -262,6 +303,7 @@ struct LeanArgs {
   void *dst;
   void *force;
   const CaseState *state;
+  const int32_t *halt;  // bit kCaseHalted: leave the lattices as they are
   int32_t nx, ny, nseg, tiles_x, ntiles, rpt, remap, force_on;
   int32_t htx0, hty0, hntx, hnty;
   double omega, s_e, s_o, s_q, s_eps, rho0, fluid_fx, fluid_fy;
@@ -336,6 +378,10 @@ hipError_t launch_collide_stream_faces(int precision, int collision, const CaseD
 hipError_t launch_ibm(int precision, const CaseDesc *cases, const IbmSlot *slots, int nslots,
                       int lds_bytes, int spread_mode, int fast, int replicas, uint32_t *ticket,
                       int threads, hipStream_t stream, LaunchTarget *ns = nullptr);
+// The IB pass of bodies cut into arcs, one workgroup per slot (arc_pass);
+// threads: 256, 512 or 1024 (DFC bodies: at most 512).
+hipError_t launch_ibm_arcs(int precision, const CaseDesc *cases, const IbmSlot *slots, int nslots,
+                           int lds_bytes, int threads, hipStream_t stream, LaunchTarget *ns = nullptr);
 // One launch per step for a case with a single fixed DF/MDF body
 // (step_fused_kernel): workgroup 0 runs the IB pass; the next nsrc
 // workgroups collide the nodes that push into the body's support, from the
@@ -364,6 +410,25 @@ struct FusedArgs {
   CaseDesc cd;
   BodyDesc bd;
 };
+// One launch per step for a case whose bodies are all cut into arcs, or that
+// has none (step_one_kernel), by workgroup: the arcs of every body; per body
+// hold_slots[b] tiles of its hold rectangle (CaseState::hold); the face nodes;
+// every other tile.  An arc waits until the tiles (and, next to a face, the
+// face nodes) of its body's rectangle have counted themselves, so the pass
+// runs beside the other tiles.  threads: 256, 512 or 1024 for all workgroups;
+// a tile is a logical bx x by workgroup with lean.rpt rows per thread.
+struct StepOneArgs {
+  LeanArgs lean;
+  CaseDesc cd;
+  const CaseDesc *c;  // the same in device memory
+  int32_t cur, nface, bx, by, tx_shift, ty_shift;  // shifts: log2 of a tile's nodes along x and y
+  int32_t zh_fold;  // Zou-He walls: the input lattice's wall nodes are still open
+  int32_t narcs, nhold;
+  int32_t arc_first[kMaxBodiesPerCase + 1], hold_first[kMaxBodiesPerCase + 1];  // prefix sums over bodies
+};
+// face: 0 the usual closures, 1 general zero-gradient, 2 Zou-He walls.
+hipError_t launch_step_one(int precision, int face, bool dfc, const StepOneArgs &a, int threads,
+                           int lds_bytes, hipStream_t stream);
 int fused_grid(const FusedArgs &a);
 hipError_t launch_step_fused(int precision, int collision, const FusedArgs &a, int lds_bytes,
                              hipStream_t stream, LaunchTarget *ns = nullptr);

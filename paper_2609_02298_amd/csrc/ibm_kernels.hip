@@ -27,111 +27,13 @@
 #include <mutex>
 
 #include "ib_lbm_internal.h"
+#include "arc_device.h"
+#include "ibm_device.h"
 #include "lbm_device.h"
 
 namespace iblbm {
 
-__constant__ int c_exi[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
-__constant__ int c_eyi[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
-// opposite direction, a compile-time function so that unrolled loops index
-// register arrays with constants
-__device__ __forceinline__ constexpr int opp_of(int i) {
-  return i == 0 ? 0 : (i <= 4 ? ((i + 1) & 3) + 1 : ((i - 3) & 3) + 5);
-}
-__constant__ double c_w[9] = {4.0 / 9.0,  1.0 / 9.0,  1.0 / 9.0,  1.0 / 9.0, 1.0 / 9.0,
-                              1.0 / 36.0, 1.0 / 36.0, 1.0 / 36.0, 1.0 / 36.0};
-
 constexpr int kIbmDynLds = 150 * 1024;
-
-// Regularized delta kernels: hat (Eq. 9) and Peskin 4-point (Eq. 10).
-__device__ __forceinline__ double delta1(int kernel, double r) {
-  const double a = fabs(r);
-  if (kernel == kHat) return a < 1.0 ? 1.0 - a : 0.0;
-  if (a <= 1.0) return 0.125 * (3.0 - 2.0 * a + sqrt(1.0 + 4.0 * a - 4.0 * a * a));
-  if (a <= 2.0) return 0.125 * (5.0 - 2.0 * a - sqrt(-7.0 + 12.0 * a - 4.0 * a * a));
-  return 0.0;
-}
-
-// A device-memory pointer the compiler cannot place by itself (one read
-// from a descriptor) makes generic (flat) accesses, and a flat access also
-// counts as an LDS operation: the next LDS wait or barrier of the wave then
-// waits until a flat store has reached the cache, a long round trip beside
-// a chip-wide stream.  Stores on the IB pass's late path go through this
-// global-address-space view instead.
-template <typename T>
-using gmem = __attribute__((address_space(1))) T;
-template <typename T>
-__device__ __forceinline__ gmem<T> *to_global(T *p) {
-  return (gmem<T> *)p;
-}
-
-// ---- fixed-order block reductions (wave64 shuffles, then LDS) ----
-// A double moved across lanes by a DPP pattern (both 32-bit halves).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-__device__ __forceinline__ double lane_f64(double v, int lane) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-// Wave64 sum and maximum with every lane active: within each row of 16
-// lanes a fixed tree of lane exchanges (pairs, pairs of pairs, half-row
-// mirror, row mirror; each step leaves the same value in both partners, as
-// IEEE addition commutes), then the four row totals in a fixed order.
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_f64<0x141>(v);  // row_half_mirror
-  v += dpp_f64<0x140>(v);  // row_mirror
-  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
-}
-__device__ __forceinline__ double wave_max(double v) {
-  v = fmax(v, dpp_f64<0xB1>(v));
-  v = fmax(v, dpp_f64<0x4E>(v));
-  v = fmax(v, dpp_f64<0x141>(v));
-  v = fmax(v, dpp_f64<0x140>(v));
-  return fmax(fmax(lane_f64(v, 0), lane_f64(v, 16)), fmax(lane_f64(v, 32), lane_f64(v, 48)));
-}
-// Sums a, b, c, d and maxima m1, m2 over the workgroup, each in a fixed
-// order: wave totals, then the wave totals (one lane of wave 0 each) by the
-// same wave tree.  The results are valid in the threads of wave 0.
-// Threads at or past `nlive` must hold a = b = c = d = +0 and maxima that are
-// 0 or held by a live thread as well (all values are non-negative): a wave
-// with no live thread writes those totals without reducing them, which is
-// what its tree would give.  On the IB pass's one compute unit the FP64
-// wave reductions of sixteen waves compete for four SIMDs.
-__device__ __forceinline__ void block_reduce6(double &a, double &b, double &c, double &d, double &m1,
-                                              double &m2, double *red, int nlive) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  if (wv * 64 < nlive) {
-    a = wave_sum(a); b = wave_sum(b); c = wave_sum(c); d = wave_sum(d);
-    m1 = wave_max(m1); m2 = wave_max(m2);
-  } else {
-    a = 0.0; b = 0.0; c = 0.0; d = 0.0; m1 = 0.0; m2 = 0.0;
-  }
-  // (red is used once per pass, so nothing earlier needs a barrier here)
-  if (lane == 0) {
-    red[6 * wv] = a; red[6 * wv + 1] = b; red[6 * wv + 2] = c; red[6 * wv + 3] = d;
-    red[6 * wv + 4] = m1; red[6 * wv + 5] = m2;
-  }
-  __syncthreads();
-  if (wv == 0) {
-    const bool in = lane < nw;
-    const double *r = red + 6 * min(lane, nw - 1);
-    a = wave_sum(in ? r[0] : 0.0);
-    b = wave_sum(in ? r[1] : 0.0);
-    c = wave_sum(in ? r[2] : 0.0);
-    d = wave_sum(in ? r[3] : 0.0);
-    m1 = wave_max(in ? r[4] : -1e300);
-    m2 = wave_max(in ? r[5] : -1e300);
-  }
-}
 
 // Exclusive prefix sum of cnt[0..n) into off[0..n], off[n] = total.  Each
 // thread sums a contiguous chunk, chunk sums are scanned with wave shuffles
@@ -269,21 +171,6 @@ __device__ __forceinline__ void get_u(const float *stg, int mn, int j, double &u
 __device__ __forceinline__ void get_u(const double *stg, int mn, int j, double &ux, double &uy) {
   ux = stg[j];
   uy = stg[mn + j];
-}
-
-// Marker loops run LPM lanes per marker (2, or 4 in the 1024-thread kernel
-// with Peskin 4-point): lanes m*LPM .. m*LPM+LPM-1 of a wave share marker
-// k, lane h sums the stencil rows [h NS/LPM, (h+1) NS/LPM) and group_sum
-// adds the partial sums of the group with DPP quad permutations (lanes
-// 0<->1, 2<->3, then 0,1<->2,3 of every quad).  IEEE addition commutes, so
-// every lane of a group holds the same total.  All lanes of a group are
-// always active together (the loops over LPM nb entries step by a block
-// size that is a multiple of LPM).
-template <int LPM>
-__device__ __forceinline__ double group_sum(double v) {
-  if (LPM >= 2) v += dpp_f64<0xB1>(v);  // quad_perm [1,0,3,2]
-  if (LPM >= 4) v += dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]
-  return v;
 }
 
 // Partial interp2 of the packed node velocities (see group_sum).
@@ -1621,73 +1508,44 @@ __global__ __launch_bounds__(FAST ? kIbmThreadsFast : kIbmThreads) void ibm_kern
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
-  if (sl.slots_in_case == 1) {
-    // the only workgroup of its case: no other body to wait for; the body's
-    // flags and force box come from the workgroup's shared memory
-    if (sl.body >= 0 && ish[50]) {
-      cs->flags |= kCaseHalted;
-    } else {
-      if (sl.body >= 0 && ish[51]) {
-        cs->fbox[0] = ish[52]; cs->fbox[1] = ish[53];
-        cs->fbox[2] = ish[54]; cs->fbox[3] = ish[55];
-        cs->fbox_valid = 1;
-      } else {
-        cs->fbox_valid = 0;
-      }
-      cs->cur = cur ^ 1;
-      cs->step = step + 1;
-    }
-    cs->xcnt = 0;
-    return;
+  const int box[4] = {ish[52], ish[53], ish[54], ish[55]};
+  case_body_done(c, cs, step, cur, sl.slots_in_case, sl.body >= 0 ? ish[50] : 0,
+                 sl.body >= 0 ? ish[51] : 0, box);
+}
+
+// One workgroup per arc of a body (arc_device.h).  MAXT: launch bound, so
+// that the arcs of 256 threads (DF, DFC) are not held to the registers of a
+// 1024-thread workgroup (DFC keeps a row's populations in registers).
+template <typename T, int MAXT>
+__global__ __launch_bounds__(MAXT) void ibm_arc_kernel(const CaseDesc *__restrict__ cases,
+                                                       const IbmSlot *__restrict__ slots) {
+  extern __shared__ double dyn[];
+  __shared__ ArcShared sh;
+  const IbmSlot sl = slots[blockIdx.x];
+  const CaseDesc &c = cases[sl.cas];
+  const CaseState *cs = c.state;
+  const int64_t step = cs->step;
+  const int cur = cs->cur;
+  if (step >= cs->target || (cs->flags & kCaseHalted)) return;
+  arc_body<T, (MAXT > 512 ? 1 : 0), false>(c, c.bodies[sl.body], step, cur, sl.arc, sl.body,
+                                           sl.slots_in_case, -1, dyn, sh);
+}
+
+hipError_t launch_ibm_arcs(int precision, const CaseDesc *cases, const IbmSlot *slots, int nslots,
+                           int lds_bytes, int threads, hipStream_t stream, LaunchTarget *ns) {
+  if (nslots <= 0) return nothing_to_launch(stream, ns);
+  if (threads != 256 && threads != 512 && threads != 1024) return hipErrorInvalidValue;
+#define IBL_ARC(TT, MT) \
+  return issue(ibm_arc_kernel<TT, MT>, dim3(nslots), dim3(threads), lds_bytes, stream, ns, cases, slots)
+  if (precision == kPrecFP64) {
+    if (threads == 256) IBL_ARC(double, 256);
+    if (threads == 512) IBL_ARC(double, 512);
+    IBL_ARC(double, 1024);
   }
-  __threadfence();
-  const int prev = atomicAdd(&cs->done, 1);
-  if (prev != sl.slots_in_case - 1) return;
-  __threadfence();
-  // Last workgroup of its case.  A body that failed this step (support
-  // outside the lattice, work space too small, non-finite force) stops the
-  // case without completing the step; bodies whose supports could meet within
-  // the next step stop it after completing this one.  The union of the
-  // bodies' force boxes tells the next collide-stream launch where to read
-  // the IB force.
-  int bflags = 0, bv = 0, b0 = 1 << 30, b1 = 1 << 30, b2 = -1, b3 = -1;
-  for (int b = 0; b < c.nbodies; b++) {
-    BodyState *st = c.bodies[b].state;
-    bflags |= __hip_atomic_load(&st->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__hip_atomic_load(&st->box_valid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-      bv = 1;
-      b0 = min(b0, __hip_atomic_load(&st->box[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      b1 = min(b1, __hip_atomic_load(&st->box[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      b2 = max(b2, __hip_atomic_load(&st->box[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      b3 = max(b3, __hip_atomic_load(&st->box[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    }
-  }
-  bool meet = false;
-  for (int a = 0; a < c.nbodies && !bflags; a++)
-    for (int b = a + 1; b < c.nbodies; b++) {
-      const BodyDesc &A = c.bodies[a], &Bb = c.bodies[b];
-      const double dx = __hip_atomic_load(&A.state->xc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                        __hip_atomic_load(&Bb.state->xc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const double dy = __hip_atomic_load(&A.state->yc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                        __hip_atomic_load(&Bb.state->yc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const double lim = A.radius + Bb.radius + A.ns + Bb.ns + 4.0;
-      if (dx * dx + dy * dy <= lim * lim) {
-        meet = true;
-        A.state->flags |= kFlagOverlap;
-      }
-    }
-  cs->done = 0;
-  cs->xcnt = 0;
-  if (bflags) {
-    cs->flags |= kCaseHalted;
-  } else {
-    cs->fbox[0] = b0; cs->fbox[1] = b1; cs->fbox[2] = b2; cs->fbox[3] = b3;
-    cs->fbox_valid = bv;
-    cs->cur ^= 1;
-    cs->step = step + 1;
-    if (meet) cs->flags |= kCaseHalted;
-  }
-  __threadfence();
+  if (threads == 256) IBL_ARC(float, 256);
+  if (threads == 512) IBL_ARC(float, 512);
+  IBL_ARC(float, 1024);
+#undef IBL_ARC
 }
 
 // ---- fused step: one launch per step for a case with a single fixed
@@ -1738,6 +1596,7 @@ __device__ __forceinline__ void fused_ib(const FusedArgs &a, int nhold, double *
   if (!active) return;
   if (ish[50] || !met) {
     cs->flags |= kCaseHalted;
+    cs->halt[cur ^ 1] = 1;
   } else {
     if (ish[51]) {
       cs->fbox[0] = ish[52]; cs->fbox[1] = ish[53];

@@ -342,15 +342,23 @@ __device__ __forceinline__ int seg_dx_minus(int x) {
   return (x & (kSeg - 1)) == 0 ? (kSeg - 1) - kSegBlock : -1;
 }
 
+// A store; AGENT: at device scope, written through to the level that all
+// compute dies share, for data that workgroups of the same launch read.
+template <bool AGENT, typename T>
+__device__ __forceinline__ void put(T *p, T v) {
+  if constexpr (AGENT) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
+
 // The nine pushes of an inner node (every link stays inside the lattice).
 // d: the destination lattice at the node's population-0 offset; rs: values
 // per row (nseg kSegBlock).
-template <typename T>
+template <typename T, bool AGENT = false>
 __device__ __forceinline__ void push_inner(T *__restrict__ d, int dxp, int dxm, int rs,
                                            const T (&f)[9]) {
 #pragma unroll
   for (int i = 0; i < 9; i++)
-    d[i * kSeg + (EXI(i) > 0 ? dxp : (EXI(i) < 0 ? dxm : 0)) + EYI(i) * rs] = f[i];
+    put<AGENT>(d + (i * kSeg + (EXI(i) > 0 ? dxp : (EXI(i) < 0 ? dxm : 0)) + EYI(i) * rs), f[i]);
 }
 
 __device__ __forceinline__ int ld_agent(const int32_t *p) {
@@ -389,7 +397,7 @@ __device__ __forceinline__ bool lean_tile_index(const LeanArgs &a, int t, int &t
   return !(MODE == 2 && tx >= a.htx0 && tx < a.htx0 + a.hntx && ty >= a.hty0 && ty < a.hty0 + a.hnty);
 }
 
-template <typename T, int COL, int MODE>
+template <typename T, int COL, int MODE, bool AGENT = false>
 __device__ __forceinline__ void lean_tile(const LeanArgs &a, int tx, int ty, int lx, int ly, int bx,
                                           int by) {
   #pragma clang fp contract(off)
@@ -410,7 +418,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs &a, int tx, int ty, int
   // pass of an earlier launch; a pipelined far tile (MODE 2) runs beside the
   // IB pass of the previous step and may miss a halt that pass sets, and then
   // writes only the lattice that the halted case no longer reads.
-  if (ld_uniform(&cs->flags) & kCaseHalted) return;
+  if (ld_uniform(a.halt) & kCaseHalted) return;
   // the force box (MODE 0): written by the IB pass of an earlier launch,
   // never by one running beside this kernel
   int fv = 0, f0 = 0, f1 = 0, f2 = 0, f3 = 0;
@@ -439,14 +447,81 @@ __device__ __forceinline__ void lean_tile(const LeanArgs &a, int tx, int ty, int
       if (fa != T(0) || fb != T(0)) {
         Fx += fa;
         Fy += fb;
-        frc[p] = T(0);
-        frc[plane + p] = T(0);
+        put<AGENT>(frc + p, T(0));
+        put<AGENT>(frc + plane + p, T(0));
       }
     } else if (MODE == 0) {
       node_force<T>(frc, plane, p, x, y, a.force_on && fv != 0, f0, f1, f2, f3, Fx, Fy);
     }
     collide<T, sizeof(T) == 4, COL>(f, Fx, Fy, a);
-    push_inner<T>(dst + b0, dxp, dxm, rs, f);
+    push_inner<T, AGENT>(dst + b0, dxp, dxm, rs, f);
+  }
+}
+
+// No-slip walls with the on-node closure of Zou and He at zero wall
+// velocity, on the populations v of wall node (x, y) after the step's
+// streaming is complete (the pushes of inner and face nodes have all landed).
+// The populations that would have come from outside are rebuilt so that the
+// node has no momentum: the normal one as its opposite, the two diagonals
+// as their opposites corrected by half the tangential imbalance of the
+// axial pair.  A corner of two such walls bounces the three populations
+// pointing into the fluid and shares between the two buried diagonals what
+// the density of the diagonal inner node leaves (f: the lattice).  The
+// relations pair populations of equal weight, so they hold unchanged for the
+// shifted FP32 store (g = f - w rho0).  Closing a closed node changes
+// nothing: no rebuilt population enters its own rule.
+__device__ __forceinline__ bool is_zou_he_wall(const CaseDesc &c, int x, int y) {
+  return (x == 0 && c.bc[kFaceW] == kZouHe) || (x == c.nx - 1 && c.bc[kFaceE] == kZouHe) ||
+         (y == 0 && c.bc[kFaceS] == kZouHe) || (y == c.ny - 1 && c.bc[kFaceN] == kZouHe);
+}
+
+template <typename T>
+__device__ __forceinline__ void zou_he_close(const CaseDesc &c, const T *f, int x, int y, T (&v)[9]) {
+  #pragma clang fp contract(off)
+  const bool w = x == 0 && c.bc[kFaceW] == kZouHe, e = x == c.nx - 1 && c.bc[kFaceE] == kZouHe;
+  const bool so = y == 0 && c.bc[kFaceS] == kZouHe, no = y == c.ny - 1 && c.bc[kFaceN] == kZouHe;
+  if ((w || e) && (so || no)) {
+    const T *fc = f + pop_node(x + (w ? 1 : -1), y + (so ? 1 : -1), c.nseg);
+    double rc = 0.0, known = 0.0;
+#pragma unroll
+    for (int i = 0; i < 9; i++) rc += (double)fc[i * kSeg];
+    if (w) v[1] = v[3]; else v[3] = v[1];
+    if (so) v[2] = v[4]; else v[4] = v[2];
+    // the diagonal into the fluid as its opposite; the other two are buried
+    if (w && so) v[5] = v[7];
+    if (w && !so) v[8] = v[6];
+    if (!w && so) v[6] = v[8];
+    if (!w && !so) v[7] = v[5];
+    const bool d57 = w == so;  // the diagonal into the fluid is 5 or 7
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+      const bool buried = d57 ? (i == 6 || i == 8) : (i == 5 || i == 7);
+      known += buried ? 0.0 : (double)v[i];
+    }
+    const T b = T(0.5 * (rc - known));
+    if (d57) { v[6] = b; v[8] = b; } else { v[5] = b; v[7] = b; }
+  } else if (so || no) {
+    const T t = T(0.5) * (v[1] - v[3]);
+    if (so) { v[2] = v[4]; v[5] = v[7] - t; v[6] = v[8] + t; }
+    else { v[4] = v[2]; v[8] = v[6] - t; v[7] = v[5] + t; }
+  } else if (w || e) {
+    const T t = T(0.5) * (v[2] - v[4]);
+    if (w) { v[1] = v[3]; v[5] = v[7] - t; v[8] = v[6] + t; }
+    else { v[3] = v[1]; v[6] = v[8] - t; v[7] = v[5] + t; }
+  }
+}
+
+// Node m of the face nodes of an nx x ny lattice: rows 0 and ny-1, then
+// columns 0, nx-2 and nx-1 between them.
+__device__ __forceinline__ void face_node_at(int nx, int ny, int m, int &x, int &y) {
+  if (m < nx) {
+    x = m; y = 0;
+  } else if (m < 2 * nx) {
+    x = m - nx; y = ny - 1;
+  } else {
+    const int q = m - 2 * nx, col = q / (ny - 2);
+    x = col == 0 ? 0 : (col == 1 ? nx - 2 : nx - 1);
+    y = 1 + q % (ny - 2);
   }
 }
 
@@ -478,15 +553,7 @@ __device__ __forceinline__ void face_node(const CaseDesc *__restrict__ cases,
   if (m >= face_nodes(c.nx, c.ny)) return;
   const int nx = c.nx, ny = c.ny;
   int x, y;
-  if (m < nx) {
-    x = m; y = 0;
-  } else if (m < 2 * nx) {
-    x = m - nx; y = ny - 1;
-  } else {
-    const int q = m - 2 * nx, col = q / (ny - 2);
-    x = col == 0 ? 0 : (col == 1 ? nx - 2 : nx - 1);
-    y = 1 + q % (ny - 2);
-  }
+  face_node_at(nx, ny, m, x, y);
   const uint32_t plane = (uint32_t)c.plane;
   const uint32_t p = (uint32_t)y * nx + x;
   const int64_t pn = pop_node(x, y, c.nseg);

@@ -107,26 +107,17 @@ __global__ __launch_bounds__(kFaceBlock) void collide_stream_face_kernel(const C
   face_node<T, COL, GZG>(cases, face_prefix, ncases, nblocks, blockIdx.x, threadIdx.x, cur_arg, force);
 }
 
-// No-slip walls with the on-node closure of Zou and He at zero wall
-// velocity, applied to the wall nodes after the step's streaming is
-// complete (the pushes of inner and face nodes have all landed).  The
-// populations that would have come from outside are rebuilt so that the
-// node has no momentum: the normal one as its opposite, the two diagonals
-// as their opposites corrected by half the tangential imbalance of the
-// axial pair.  A corner of two such walls bounces the three populations
-// pointing into the fluid and shares between the two buried diagonals what
-// the density of the diagonal inner node leaves.  The relations pair
-// populations of equal weight, so they hold unchanged for the shifted FP32
-// store (g = f - w rho0).  Links leaving through these faces were dropped
-// by push_one.  One thread per perimeter node: rows 0 and ny-1, then
-// columns 0 and nx-1 between them.
+// The Zou-He wall nodes of a case (zou_he_close), one thread per perimeter
+// node.  cur_arg >= 0: of the lattice a step with that input lattice writes;
+// -1: the same from the case state; -2 (after one-launch steps): of the
+// current lattice, but not the nodes the pass has closed and corrected.
 template <typename T>
 __global__ __launch_bounds__(256) void zou_he_kernel(const CaseDesc *__restrict__ cp, int cur_arg) {
   const CaseDesc &c = *cp;
   const CaseState *cs = c.state;
   const int nx = c.nx, ny = c.ny;
   const int m = blockIdx.x * blockDim.x + (int)threadIdx.x;
-  if (m >= 2 * nx + 2 * (ny - 2)) return;
+  if (m >= wall_nodes(nx, ny)) return;
   int x, y;
   if (m < 2 * nx) {
     x = m % nx;
@@ -136,56 +127,26 @@ __global__ __launch_bounds__(256) void zou_he_kernel(const CaseDesc *__restrict_
     x = q < ny - 2 ? 0 : nx - 1;
     y = 1 + q % (ny - 2);
   }
-  const bool w = x == 0 && c.bc[kFaceW] == kZouHe, e = x == nx - 1 && c.bc[kFaceE] == kZouHe;
-  const bool so = y == 0 && c.bc[kFaceS] == kZouHe, no = y == ny - 1 && c.bc[kFaceN] == kZouHe;
-  if (!(w || e || so || no)) return;
-  int cur = cur_arg;
-  if (cur < 0) {
+  if (!is_zou_he_wall(c, x, y)) return;
+  if (cur_arg != -2 && c.wall_closed) c.wall_closed[m] = 0;
+  int out;
+  if (cur_arg == -2) {
+    if (c.wall_closed[m]) return;
+    out = cs->cur;
+  } else if (cur_arg < 0) {
     if (cs->step >= cs->target || (cs->flags & kCaseHalted)) return;
-    cur = cs->cur;
-  } else if (__hip_atomic_load(&cs->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kCaseHalted) {
-    return;
+    out = cs->cur ^ 1;
+  } else {
+    if (__hip_atomic_load(&cs->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kCaseHalted) return;
+    out = cur_arg ^ 1;
   }
-  T *__restrict__ f = (T *)c.f[cur ^ 1] + pop_node(x, y, c.nseg);
+  T *__restrict__ f = (T *)c.f[out] + pop_node(x, y, c.nseg);
   T v[9];
 #pragma unroll
   for (int i = 0; i < 9; i++) v[i] = f[i * kSeg];
-  if ((w || e) && (so || no)) {
-    const int sx = w ? 1 : -1, sy = so ? 1 : -1;
-    const int ix = sx > 0 ? 1 : 3, iy = sy > 0 ? 2 : 4;
-    // diagonal into the fluid, and the two buried ones
-    const int id = sx > 0 ? (sy > 0 ? 5 : 8) : (sy > 0 ? 6 : 7);
-    const int ia = sx > 0 ? (sy > 0 ? 6 : 7) : (sy > 0 ? 5 : 8);  // (-sx, sy)
-    const int ib = sx > 0 ? (sy > 0 ? 8 : 5) : (sy > 0 ? 7 : 6);  // (sx, -sy)
-    v[ix] = v[OPPI(ix)];
-    v[iy] = v[OPPI(iy)];
-    v[id] = v[OPPI(id)];
-    const T *fc = (const T *)c.f[cur ^ 1] + pop_node(x + sx, y + sy, c.nseg);
-    double rc = 0.0, known = 0.0;
+  zou_he_close<T>(c, (const T *)c.f[out], x, y, v);
 #pragma unroll
-    for (int i = 0; i < 9; i++) {
-      rc += (double)fc[i * kSeg];
-      if (i != ia && i != ib) known += (double)v[i];
-    }
-    const T b = T(0.5 * (rc - known));
-    f[ix * kSeg] = v[ix];
-    f[iy * kSeg] = v[iy];
-    f[id * kSeg] = v[id];
-    f[ia * kSeg] = b;
-    f[ib * kSeg] = b;
-  } else if (so || no) {
-    const int in = so ? 2 : 4, d1 = so ? 5 : 8, d2 = so ? 6 : 7;
-    const T t = T(0.5) * (v[1] - v[3]);
-    f[in * kSeg] = v[OPPI(in)];
-    f[d1 * kSeg] = v[OPPI(d1)] - t;
-    f[d2 * kSeg] = v[OPPI(d2)] + t;
-  } else {
-    const int in = w ? 1 : 3, d1 = w ? 5 : 6, d2 = w ? 8 : 7;
-    const T t = T(0.5) * (v[2] - v[4]);
-    f[in * kSeg] = v[OPPI(in)];
-    f[d1 * kSeg] = v[OPPI(d1)] - t;
-    f[d2 * kSeg] = v[OPPI(d2)] + t;
-  }
+  for (int i = 1; i < 9; i++) f[i * kSeg] = v[i];
 }
 
 hipError_t launch_zou_he(int precision, const CaseDesc *c, int nx, int ny, int cur, hipStream_t stream,

@@ -1,0 +1,153 @@
+"""The IB pass in arcs and the one-launch step, through the C ABI: against the
+FP64 oracle where the number of arcs changes, and one-launch steps bit for bit
+against plain steps (the same passes in launches of their own) where the pass
+waits for faces, closes walls itself or follows a fast body."""
+import numpy as np
+import pytest
+
+import ib_cases
+import oracle
+import paper_2609_02298_amd as ib
+
+pytestmark = pytest.mark.gpu
+
+# velocity and populations, relative to their maximum (double precision)
+F64_FIELD, F64_DRAG = 1e-12, 1e-10
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    ib.load_library()
+
+
+def rel(a, b):
+    return float(np.abs(np.asarray(a) - np.asarray(b)).max() / max(np.abs(b).max(), 1e-300))
+
+
+def box(nx, ny, bodies, bc, col=ib.TRT, **kw):
+    return dict(nx=nx, ny=ny, collision=col, tau=0.68, trt_magic=0.25, cm_s_q=1.2, cm_s_eps=1.4, bc=bc,
+                bodies=bodies, **kw)
+
+
+FAR = (ib.VEL_UNIFORM, ib.ZERO_GRADIENT, ib.VEL_UNIFORM, ib.VEL_UNIFORM)
+
+
+# markers per workgroup: 64 (P4) or 128 (hat) at 256 threads, MDF of five passes
+# up to 1024 threads; below, at and above each bound, and many arcs
+@pytest.mark.parametrize("scheme,kernel,nb", [
+    (ib.DF, ib.PESKIN4, 64), (ib.DF, ib.PESKIN4, 65), (ib.DF, ib.PESKIN4, 301),
+    (ib.DF, ib.HAT, 128), (ib.DF, ib.HAT, 129), (ib.DF, ib.HAT, 301),
+    (ib.DFC, ib.PESKIN4, 64), (ib.DFC, ib.PESKIN4, 65), (ib.DFC, ib.PESKIN4, 200),
+    (ib.DFC, ib.HAT, 128), (ib.DFC, ib.HAT, 129), (ib.DFC, ib.HAT, 301),
+    (ib.MDF, ib.PESKIN4, 64), (ib.MDF, ib.PESKIN4, 65), (ib.MDF, ib.PESKIN4, 128),
+    (ib.MDF, ib.PESKIN4, 129), (ib.MDF, ib.PESKIN4, 301),
+    (ib.MDF, ib.HAT, 128), (ib.MDF, ib.HAT, 129), (ib.MDF, ib.HAT, 301)])
+def test_arcs_match_the_oracle(scheme, kernel, nb):
+    D = nb / np.pi
+    n = int(D) + 40
+    print(f"arcs scheme={scheme} kernel={kernel} markers={nb}", flush=True)
+    case = box(n + 30, n, [dict(xc=n / 2 + 0.37, yc=n / 2 - 0.21, diameter=D, n_markers=nb, scheme=scheme,
+                                kernel=kernel, mdf_iters=5)], FAR, u_bc=0.06)
+    for over in (False, True):
+        sim, ref = ib.Sim(case), oracle.OracleSim(case)
+        sim.set_overlap(over)
+        ref.add_body(case["bodies"][0])
+        for k in (1, 7):
+            sim.step(k)
+            ref.step(k)
+            a, b = sim.forces(0), ref.body_state(0)
+            assert abs(a["fx"] - b["fx"]) < F64_DRAG * abs(b["fx"])
+            assert abs(a["torque"] - b["torque"]) < F64_DRAG * abs(b["fx"]) * D
+            assert abs(a["slip_mean"] - b["slip_mean"]) < 1e-10 * max(b["slip_mean"], 1e-12)
+        assert rel(sim.populations(), ref.populations()) < F64_FIELD
+        sim.close()
+        ref.close()
+
+
+def free(x, y, D, scheme, kernel, **kw):
+    return dict(xc=x, yc=y, diameter=D, scheme=scheme, kernel=kernel, mdf_iters=3, motion=ib.FREE,
+                density_ratio=1.6, internal_mass=ib.IM_FENG, **kw)
+
+
+ZOU = (ib.ZOU_HE,) * 4
+PER = (ib.PERIODIC,) * 4
+CASES = {
+    # supports on the wall nodes of a corner: the pass waits for the faces and
+    # closes the walls it reads
+    "corner-DF": box(60, 50, [free(7.3, 7.6, 12.0, ib.DF, ib.PESKIN4)], ZOU, gravity=(2e-5, 3e-5)),
+    "corner-DFC": box(60, 50, [free(51.6, 41.6, 12.0, ib.DFC, ib.PESKIN4)], ZOU, ib.CMMRT,
+                      gravity=(-1e-5, -2e-5)),
+    "wall-MDF": box(60, 50, [free(30.2, 7.4, 12.0, ib.MDF, ib.HAT)], (ib.PERIODIC, ib.PERIODIC, ib.ZOU_HE,
+                                                                       ib.ZOU_HE), gravity=(2e-5, 1e-5)),
+    "wall-DFC": box(60, 50, [free(30.2, 43.1, 11.0, ib.DFC, ib.HAT)], (ib.PERIODIC, ib.PERIODIC, ib.ZOU_HE,
+                                                                        ib.ZOU_HE), gravity=(2e-5, 0.0)),
+    # supports on the seam of a periodic lattice, and on open faces
+    "seam-DF": box(70, 66, [free(8.2, 33.3, 13.0, ib.DF, ib.PESKIN4)], PER, ib.BGK, gravity=(0.0, 2e-5)),
+    "open-MDF": box(70, 66, [free(60.9, 57.3, 13.0, ib.MDF, ib.PESKIN4)], (ib.ZERO_GRADIENT,) * 4,
+                    gravity=(-2e-5, -2e-5)),
+    # two bodies, one above the other, until their supports could meet
+    "meet-DF": box(80, 120, [free(40.0, 70.0, 14.0, ib.DF, ib.HAT),
+                             free(41.0, 93.0, 14.0, ib.DF, ib.HAT, amp=(0.0, 0.0))], (ib.BOUNCE_BACK,) * 4,
+                   gravity=(0.0, -4e-4)),
+    # a driven body that crosses several nodes per step (hardly relaxed, so
+    # that the flow stays subsonic), and a slower one
+    "fast-MDF": box(200, 90, [dict(xc=90.0, yc=45.3, diameter=14.0, scheme=ib.MDF, kernel=ib.PESKIN4,
+                                   mdf_iters=4, mdf_omega=1e-3, motion=ib.PRESCRIBED_SIN, amp=(40.0, 6.0),
+                                   freq=0.02, phase=0.4)], FAR, u_bc=0.02),
+    "driven-DFC": box(200, 90, [dict(xc=90.0, yc=45.3, diameter=14.0, scheme=ib.DFC, kernel=ib.HAT,
+                                   motion=ib.PRESCRIBED_SIN, amp=(20.0, 0.0), freq=0.002, phase=0.4)],
+                    FAR, ib.CMMRT, u_bc=0.02),
+    # no body: tiles and faces alone
+    "empty-open": box(131, 47, [], (ib.ZERO_GRADIENT,) * 4, ib.CMMRT),
+    "empty-box": box(64, 33, [], ZOU, ib.BGK, fluid_force=(1e-6, -2e-6)),
+}
+
+
+@pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
+@pytest.mark.parametrize("name", list(CASES))
+def test_one_launch_steps_are_bitwise_the_plain_steps(name, prec):
+    case = CASES[name]
+    print(f"one-launch {name} prec={prec}", flush=True)
+    pops = ib_cases.random_populations(case["nx"], case["ny"], 5, amp=0.004, u=(0.01, 0.005))
+    runs = []
+    for over, graph in ((False, 0), (True, 0), (True, 6)):
+        sim = ib.Sim(case, precision=prec)
+        sim.set_overlap(over)
+        sim.set_populations(pops)
+        if graph:
+            sim.set_graph(graph)
+        seen = []
+        for k in (1, 2, 13, 24):
+            sim.step(k)
+            st = [sim.forces(b, check=False) for b in range(len(case["bodies"]))]
+            seen.append((sim.steps_done, sim.populations(), sim.force(), st))
+        runs.append(seen)
+        sim.close()
+    for seen in runs[1:]:
+        for (n0, p0, f0, s0), (n1, p1, f1, s1) in zip(runs[0], seen):
+            assert n0 == n1 and np.isfinite(p0).all()
+            assert np.array_equal(p0, p1)
+            assert np.array_equal(f0[0], f1[0]) and np.array_equal(f0[1], f1[1])
+            assert s0 == s1
+
+
+def test_one_launch_steps_after_atomic_spreading():
+    """A sim that changes to the atomic scatter and back: the hold rectangles
+    of the steps in between are not kept, so the first step after is plain."""
+    case = CASES["fast-MDF"]
+    print("one-launch after atomic spreading", flush=True)
+    out = []
+    for over in (False, True):
+        sim = ib.Sim(case)
+        sim.set_overlap(over)
+        sim.step(9)
+        sim.set_spread(ib.SPREAD_ATOMIC)
+        sim.step(1)
+        sim.set_spread(ib.SPREAD_GATHER)
+        sim.step(12)
+        out.append(sim.populations())
+        sim.close()
+    assert rel(out[1], out[0]) < F64_FIELD
