@@ -405,9 +405,11 @@ ib_lbm_status ib_lbm_stream_copy(const void *src, void *dst, size_t bytes, int32
 
 /* ---- batching: many independent sims stepped by shared launches ----
  * All sims of a batch share one precision and one stream.  A batch step is
- * one collide-stream launch per collision model present and one IB launch
- * for every body of every attached sim; each sim keeps its own step count
- * and target and stops at its own target (ib_lbm_batch_set_target). */
+ * one launch for everything when every body runs its pass in arcs (see
+ * ib_lbm_set_fused), else a collide-stream and a face launch per collision
+ * model present and the IB launches of all bodies; results are bitwise the
+ * same.  Each sim keeps its own step count and target and stops at its own
+ * target (ib_lbm_batch_set_target). */
 ib_lbm_status ib_lbm_batch_create(void *stream, int32_t precision, ib_lbm_batch **out);
 ib_lbm_status ib_lbm_batch_attach(ib_lbm_batch *b, ib_lbm_sim *s);
 ib_lbm_status ib_lbm_batch_detach(ib_lbm_batch *b, ib_lbm_sim *s);
@@ -415,7 +417,8 @@ ib_lbm_status ib_lbm_batch_detach(ib_lbm_batch *b, ib_lbm_sim *s);
 ib_lbm_status ib_lbm_batch_set_target(ib_lbm_batch *b, ib_lbm_sim *s, int64_t target);
 ib_lbm_status ib_lbm_batch_step(ib_lbm_batch *b, int64_t nsteps);
 ib_lbm_status ib_lbm_batch_set_graph(ib_lbm_batch *b, int32_t steps_per_graph);
-/* Launch shape and spreading variant of the batch's launches (as for a sim). */
+/* Launch shape and spreading variant of the batch's launches (as for a sim;
+ * one-launch steps have a tile shape of their own). */
 ib_lbm_status ib_lbm_batch_set_launch(ib_lbm_batch *b, const ib_lbm_launch *l);
 ib_lbm_status ib_lbm_batch_set_spread(ib_lbm_batch *b, int32_t mode);
 ib_lbm_status ib_lbm_batch_sync(ib_lbm_batch *b);

@@ -148,8 +148,16 @@ __device__ __forceinline__ double ld_agent_f64(const double *p) {
 // The union of the bodies' force boxes tells the next collide-stream where to
 // read the IB force.
 __device__ __forceinline__ void case_body_done(const CaseDesc &c, CaseState *cs, int64_t step, int cur,
-                                               int nslots, int flags, int box_valid, const int (&box)[4]) {
+                                               int nslots, int flags, int box_valid, const int (&box)[4],
+                                               int par = -1) {
+  // what the next one-launch step of a batch does with the case
+  auto control = [&](bool done, bool halted) {
+    if (par < 0) return;
+    const bool on = !halted && (!done || step + 1 < cs->target);
+    cs->ctl[par ^ 1] = (done ? cur ^ 1 : cur) | (on ? kCtlActive : 0) | (done ? kCtlHold : 0);
+  };
   if (nslots == 1) {
+    control(!flags, flags != 0);
     if (flags) {
       cs->flags |= kCaseHalted;
       cs->halt[cur ^ 1] = 1;
@@ -195,6 +203,7 @@ __device__ __forceinline__ void case_body_done(const CaseDesc &c, CaseState *cs,
   cs->done = 0;
   cs->xcnt = 0;
   if (bflags || meet) cs->halt[cur ^ 1] = 1;
+  control(!bflags, bflags || meet);
   if (bflags) {
     cs->flags |= kCaseHalted;
   } else {
@@ -257,17 +266,19 @@ __device__ __forceinline__ bool count_wait(const int32_t *cnt, int n) {
   return spins < kArcSpins;
 }
 
-// One arc of one body.  T: stored population; NS: stencil width; DFC: the
-// distribution-function correction, else DF / MDF.  body: its index in the
-// case, of nslots bodies.  The workgroup has at least NS nl threads (a
-// multiple of 64).  wait_for >= 0 (one-launch steps): the pass runs beside
-// the tiles of its step and first waits until that many workgroups have
+// One arc of one body.  T: stored population; NS: stencil width; KIND: the
+// scheme; RPL: stencil rows per lane (a marker has NS / RPL lanes).  body: its
+// index in the case, of nslots bodies.  The workgroup has at least nl NS / RPL
+// threads (a multiple of 64).  wait_for >= 0 (one-launch steps): the pass runs
+// beside the tiles of its step and first waits until that many workgroups have
 // counted themselves in hold_done; OPEN: the lattice's Zou-He wall nodes are
-// still open then.
-template <typename T, int NS, bool DFC, bool OPEN>
+// still open then; par: the launch's parity in a batch, or -1.
+enum { kArcDF = 0, kArcMDF = 1, kArcDFC = 2 };
+template <typename T, int NS, int KIND, int RPL, bool OPEN>
 __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, int64_t step, int cur,
-                                         int arc, int body, int nslots, int wait_for, double *dyn,
+                                         int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
+  constexpr int LPM = NS / RPL;
   constexpr int QMAX = NS == 4 ? kArcBandRegsP4 : kArcBandRegsHat;
   const int tid = threadIdx.x;
   const double rho0 = c.rho0;
@@ -284,8 +295,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
     sh.flags = bs->flags;
   }
   if (tid == 64 && B.motion == kPrescribedSin) sh.next = body_kinematics(c, B, bs, step + 1);
-  // the lane's marker and row
-  const int mm = tid / NS, h = tid & (NS - 1);
+  // the lane's marker and its first row
+  const int mm = tid / LPM, h = tid % LPM;
   const bool live = mm < nl;
   const int m = live ? mm : 0;
   int k = whole ? m : k0 - halo + m;
@@ -304,8 +315,9 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
   double *const lwx = (double *)(lF + 2 * E);      // [E][SW]
   double *const lwy = lwx + E * SW;                // [E][SY]
   double *const lB = lwy + E * SY;                 // [E][bw + 1] (MDF), [E][9] (DFC)
-  const int nB = DFC ? 9 : (B.scheme == kMDF ? bw + 1 : 0);
+  const int nB = KIND == kArcDFC ? 9 : (KIND == kArcMDF ? bw + 1 : 0);
   int *const lpos = (int *)(lB + E * nB);          // [E] first node of the stencil
+  double *const lX = (double *)(lpos + ((E + 1) & ~1));  // [nl][3] X, Y, (sum w_x)(sum w_y)
   for (int i = tid; i < E * (4 + SW + SY + nB); i += blockDim.x) dyn[i] = 0.0;
   for (int i = tid; i < E; i += blockDim.x) lpos[i] = kArcNowhere;
   if (tid < 3) sh.rmax[tid] = 0ull;
@@ -332,9 +344,9 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
   const double udx = sh.kin.udx - sh.kin.udo * (Y - yc), udy = sh.kin.udy + sh.kin.udo * (X - xc);
   const double ds = B.ds;
   const int ix0 = (int)floor(X) - s1, iy0 = (int)floor(Y) - s1;
-  const int yrow = iy0 + h;
+  const int y0 = iy0 + h * RPL;  // the lane's rows: y0 .. y0 + RPL - 1
   double a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0, a6 = 0;  // fx fy torque slip | residual slip_max
-  int iters = DFC ? 0 : 1;
+  int iters = KIND == kArcDFC ? 0 : 1;
   const int motion = B.motion;
   if (tid == 64) {
     // what the end of the pass writes and the position alone decides
@@ -350,17 +362,11 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
     sh.hist = (step % B.hist_cap) * kHistCols;
   }
   // The geometry of the step, all of it before the wait of a one-launch step:
-  // weights, the markers covering the lane's row, its nodes' first markers,
+  // weights, the markers covering the lane's rows, its nodes' first markers,
   // and DFC's correction scale.
-  double wx[NS], wyv[NS];
+  double wx[NS], wyv[NS], wy[RPL];
   row_weights<NS>(X, wx);
   row_weights<NS>(Y, wyv);
-  double wy = wyv[0], wxh = wx[0];
-#pragma unroll
-  for (int j = 1; j < NS; j++) {
-    wy = h == j ? wyv[j] : wy;
-    wxh = h == j ? wx[j] : wxh;
-  }
   double wsum;  // (sum w_x) (sum w_y)
   {
     double wsx = 0, wsy = 0;
@@ -368,27 +374,48 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
     for (int j = 0; j < NS; j++) { wsx += wx[j]; wsy += wyv[j]; }
     wsum = wsx * wsy;
   }
-  if (live) {
-    lwx[e0 * SW + NS + h] = wxh;
-    lwy[e0 * SY + 1 + h] = wy;
-    if (h == 0) lpos[e0] = ix0 | (iy0 << 16);
-    if (e1 != e0) {
-      lwx[e1 * SW + NS + h] = wxh;
-      lwy[e1 * SY + 1 + h] = wy;
-      if (h == 0) lpos[e1] = ix0 | (iy0 << 16);
+#pragma unroll
+  for (int r = 0; r < RPL; r++) {
+    double wxh = wx[r];
+    wy[r] = wyv[r];
+#pragma unroll
+    for (int q = 1; q < LPM; q++) {
+      wy[r] = h == q ? wyv[q * RPL + r] : wy[r];
+      wxh = h == q ? wx[q * RPL + r] : wxh;
+    }
+    if (live) {
+      lwx[e0 * SW + NS + h * RPL + r] = wxh;
+      lwy[e0 * SY + 1 + h * RPL + r] = wy[r];
+      if (e1 != e0) {
+        lwx[e1 * SW + NS + h * RPL + r] = wxh;
+        lwy[e1 * SY + 1 + h * RPL + r] = wy[r];
+      }
     }
   }
+  if (live && h == 0) {
+    // (kept here rather than in registers: only the end of the pass reads them)
+    lX[3 * m] = X;
+    lX[3 * m + 1] = Y;
+    lX[3 * m + 2] = wsum;
+    lpos[e0] = ix0 | (iy0 << 16);
+    lpos[e1] = ix0 | (iy0 << 16);
+  }
   __syncthreads();
-  // The marker at stencil origin p against this lane's row: dx, its first
-  // column relative to this marker's, and ly, the row in its stencil.
-  auto offsets = [&](int p, int &dx, int &ly) {
+  // The marker at stencil origin p against row y: dx, its first column
+  // relative to this marker's, and ly, the row in its stencil.
+  auto offsets = [&](int p, int y, int &dx, int &ly) {
     dx = (p & 0xffff) - ix0;
-    ly = yrow - (p >> 16);
+    ly = y - (p >> 16);
   };
-  // cov: the markers covering this lane's row, one bit per entry m .. m + 2 bw
+  // cov: the markers covering each row, one bit per entry m .. m + 2 bw
   // (origins loaded four at a time: one LDS round trip each); mine: the nodes
   // of the row, one bit each, that no earlier marker covers.
-  uint32_t cov = 0, mine = (1u << NS) - 1;
+  uint32_t cov[RPL], mine[RPL];
+#pragma unroll
+  for (int r = 0; r < RPL; r++) {
+    cov[r] = 0;
+    mine[r] = (1u << NS) - 1;
+  }
   for (int i0 = 0; i0 <= 2 * bw; i0 += 4) {
     int p[4];
 #pragma unroll
@@ -396,39 +423,45 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
 #pragma unroll
     for (int u = 0; u < 4; u++) {
       int dx, ly;
-      offsets(p[u], dx, ly);
-      if ((unsigned)ly < (unsigned)NS && dx > -NS && dx < NS && i0 + u <= 2 * bw) {
-        cov |= 1u << (i0 + u);
-        if (i0 + u < bw) mine &= ~((((1u << NS) - 1) << NS) >> (NS - dx));
-      }
+      offsets(p[u], y0, dx, ly);
+      const bool in = dx > -NS && dx < NS && i0 + u <= 2 * bw;
+      const uint32_t cols = i0 + u < bw ? ((((1u << NS) - 1) << NS) >> (NS - dx)) : 0u;
+#pragma unroll
+      for (int r = 0; r < RPL; r++)
+        if (in && (unsigned)(ly + r) < (unsigned)NS) {
+          cov[r] |= 1u << (i0 + u);
+          mine[r] &= ~cols;
+        }
     }
   }
-  // Calls f(i, w, wy) for the markers of a set in order along the circle:
-  // entry m + i, its weights at this lane's nodes (w, zero where it does not
-  // reach) and at this row.
-  auto for_cover = [&](uint32_t set, auto &&f) {
+  // Calls f(i, w, wy) for the markers of a set covering row y in order along
+  // the circle: entry m + i, its weights at this lane's columns (w, zero where
+  // it does not reach) and at the row.
+  auto for_cover = [&](uint32_t set, int y, auto &&f) {
     while (set) {
       const int i = __ffs(set) - 1;
       set &= set - 1;
       int dx, ly;
-      offsets(lpos[m + i], dx, ly);
+      offsets(lpos[m + i], y, dx, ly);
       f(i, lwx + (m + i) * SW + NS - dx, lwy[(m + i) * SY + 1 + ly]);
     }
   };
   double lam = 0.0;
-  if constexpr (DFC) {
+  if constexpr (KIND == kArcDFC) {
     if (bs->lambda_valid) {
       lam = B.lambda_cache[k];
     } else {
       // W_total interpolated to the marker (Eq. 17): sum_l sum_x D_k D_l
       double ws = 0.0;
-      for_cover(cov, [&](int, const double *w, double wyl) {
-        double r = 0.0;
 #pragma unroll
-        for (int j = 0; j < NS; j++) r += wx[j] * w[j];
-        ws += r * (wy * wyl);
-      });
-      lam = 1.0 / (2.0 * rho0 * ds * group_sum<NS>(ws));
+      for (int r = 0; r < RPL; r++)
+        for_cover(cov[r], y0 + r, [&](int, const double *w, double wyl) {
+          double q = 0.0;
+#pragma unroll
+          for (int j = 0; j < NS; j++) q += wx[j] * w[j];
+          ws += q * (wy[r] * wyl);
+        });
+      lam = 1.0 / (2.0 * rho0 * ds * group_sum<LPM>(ws));
       if (motion == kFixed && owned && h == 0 && !fail) B.lambda_cache[k] = lam;
     }
   }
@@ -440,22 +473,24 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
     __syncthreads();
   }
   if (!fail) {
-    T v[9][NS];
-    load_pop_row<T, NS>((const T *)c.f[cur ^ 1], ix0, yrow, nseg, v);
-    if constexpr (OPEN) {
-      if (yrow == 0 || yrow == ny - 1 || ix0 == 0 || ix0 + NS == nx) {
+    const T *const fpop = (const T *)c.f[cur ^ 1];
+    auto load_row = [&](int y, T (&v)[9][NS]) {
+      load_pop_row<T, NS>(fpop, ix0, y, nseg, v);
+      if constexpr (OPEN) {
+        if (y == 0 || y == ny - 1 || ix0 == 0 || ix0 + NS == nx) {
 #pragma unroll
-        for (int j = 0; j < NS; j++) {
-          if (!is_zou_he_wall(c, ix0 + j, yrow)) continue;
-          T w[9];
+          for (int j = 0; j < NS; j++) {
+            if (!is_zou_he_wall(c, ix0 + j, y)) continue;
+            T w[9];
 #pragma unroll
-          for (int i = 0; i < 9; i++) w[i] = v[i][j];
-          zou_he_close<T>(c, (const T *)c.f[cur ^ 1], ix0 + j, yrow, w);
+            for (int i = 0; i < 9; i++) w[i] = v[i][j];
+            zou_he_close<T>(c, fpop, ix0 + j, y, w);
 #pragma unroll
-          for (int i = 0; i < 9; i++) v[i][j] = w[i];
+            for (int i = 0; i < 9; i++) v[i][j] = w[i];
+          }
         }
       }
-    }
+    };
     auto put_force = [&](double2 *f, double Fx, double Fy) {
       if (live && h == 0) {
         f[e0] = make_double2(Fx, Fy);
@@ -463,34 +498,48 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
       }
     };
     double Ux, Uy, Ftx = 0.0, Fty = 0.0;
-    if constexpr (!DFC) {
-      double rho[NS], rin[NS], ux[NS], uy[NS];
-#pragma unroll
-      for (int j = 0; j < NS; j++) {
-        double sm, jx, jy;
-        T q[9];
-#pragma unroll
-        for (int i = 0; i < 9; i++) q[i] = v[i][j];
-        node_sums<T>(q, rho0, sm, jx, jy);
-        const double inv = 1.0 / sm;
-        rho[j] = sm;
-        rin[j] = inv;
-        ux[j] = jx * inv;
-        uy[j] = jy * inv;
-      }
+    if constexpr (KIND != kArcDFC) {
+      // moments of the rows' nodes, interpolated to the marker (rin, ux, uy:
+      // 1/rho and the velocity, kept for DF)
+      constexpr int KR = KIND == kArcDF ? RPL : 1;
+      double rin[KR][NS], ux[KR][NS], uy[KR][NS], t[RPL][NS];
       double ra = 0, rb = 0, rc = 0;
 #pragma unroll
-      for (int j = 0; j < NS; j++) {
-        ra += rho[j] * wx[j];
-        rb += ux[j] * wx[j];
-        rc += uy[j] * wx[j];
+      for (int r = 0; r < RPL; r++) {
+        T v[9][NS];
+        load_row(y0 + r, v);
+        double qa = 0, qb = 0, qc = 0;
+#pragma unroll
+        for (int j = 0; j < NS; j++) {
+          double sm, jx, jy;
+          T q[9];
+#pragma unroll
+          for (int i = 0; i < 9; i++) q[i] = v[i][j];
+          node_sums<T>(q, rho0, sm, jx, jy);
+          const double inv = 1.0 / sm;
+          jx *= inv;
+          jy *= inv;
+          qa += sm * wx[j];
+          qb += jx * wx[j];
+          qc += jy * wx[j];
+          if constexpr (KIND == kArcDF) {
+            rin[r][j] = inv;
+            ux[r][j] = jx;
+            uy[r][j] = jy;
+          } else {
+            t[r][j] = wx[j] * wy[r] * (0.5 * ds * inv);
+          }
+        }
+        ra += qa * wy[r];
+        rb += qb * wy[r];
+        rc += qc * wy[r];
+        if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);  // one row of populations at a time
       }
-      const double rX = group_sum<NS>(ra * wy);
-      Ux = group_sum<NS>(rb * wy);
-      Uy = group_sum<NS>(rc * wy);
-      const bool mdf = B.scheme == kMDF;
-      if (!mdf) {
-        // DF, Eq. (11)
+      const double rX = group_sum<LPM>(ra);
+      Ux = group_sum<LPM>(rb);
+      Uy = group_sum<LPM>(rc);
+      if constexpr (KIND == kArcDF) {
+        // Eq. (11)
         Ftx = 2.0 * rX * (udx - Ux);
         Fty = 2.0 * rX * (udy - Uy);
         put_force(lF, Ftx, Fty);
@@ -499,46 +548,48 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
         // MDF, Eq. (12)-(14), in marker space: interpolating the updated
         // node velocities of Eq. (14) gives U^(n+1) = U^(n) + omega B F^(n),
         // B_kl = sum_x D_h(x - X_k) D_h(x - X_l) ds / (2 rho(x)).  The lane
-        // keeps its row's terms of B's row k and, for the passes, its share of
-        // the band in registers: a pass is one LDS round trip and one barrier
-        // (0.6 us; 1.44 us with the band, velocities and forces in LDS and
-        // two barriers).
-        double t[NS];
-#pragma unroll
-        for (int j = 0; j < NS; j++) t[j] = wx[j] * wy * (0.5 * ds * rin[j]);
+        // keeps its rows' terms of B's row k and, for the passes, its share of
+        // the band in registers: a pass is one LDS round trip and one barrier.
         for (int d0 = 0; d0 <= bw; d0 += 2) {
           double b[2];
 #pragma unroll
           for (int u = 0; u < 2; u++) {
             const int e = e0 + min(d0 + u, bw);
             int dx, ly;
-            offsets(lpos[e], dx, ly);
+            offsets(lpos[e], y0, dx, ly);
             const double *w = lwx + e * SW + NS - max(-NS, min(NS, dx));
-            double r = 0.0;
+            double wj[NS];
 #pragma unroll
-            for (int j = 0; j < NS; j++) r += t[j] * w[j];
-            b[u] = r * lwy[e * SY + 1 + max(-1, min(NS, ly))];
+            for (int j = 0; j < NS; j++) wj[j] = w[j];
+            b[u] = 0.0;
+#pragma unroll
+            for (int r = 0; r < RPL; r++) {
+              double q = 0.0;
+#pragma unroll
+              for (int j = 0; j < NS; j++) q += t[r][j] * wj[j];
+              b[u] += q * lwy[e * SY + 1 + max(-1, min(NS, ly + r))];
+            }
           }
 #pragma unroll
           for (int u = 0; u < 2; u++) {
-            b[u] = group_sum<NS>(b[u]);
+            b[u] = group_sum<LPM>(b[u]);
             const int d = d0 + u;
-            if (live && d <= bw && h == (d & (NS - 1))) {
+            if (live && d <= bw && h == (d & (LPM - 1))) {
               lB[e0 * nB + d] = b[u];
               if (e1 != e0) lB[e1 * nB + d] = b[u];
             }
           }
         }
         __syncthreads();
-        // the lane's entries of row k: i = h, h + NS, ... of 0 .. 2 bw; the
+        // the lane's entries of row k: i = h, h + LPM, ... of 0 .. 2 bw; the
         // ones behind the diagonal are read from the earlier marker's row
         double bq[QMAX];
 #pragma unroll
         for (int q = 0; q < QMAX; q++) {
-          const int i = q * NS + h;
+          const int i = q * LPM + h;
           bq[q] = i > 2 * bw ? 0.0 : (i >= bw ? lB[e0 * nB + i - bw] : lB[(m + i) * nB + bw - i]);
         }
-        const int nq = (2 * bw + NS) / NS;  // entries of a lane, ceil((2 bw + 1) / NS)
+        const int nq = (2 * bw + LPM) / LPM;  // entries of a lane, ceil((2 bw + 1) / LPM)
         const int N = B.mdf_iters;
         const double om = B.omega_mdf, tol = B.mdf_tol;
         const bool adapt = tol > 0.0;
@@ -551,13 +602,13 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
           put_force(fb, Fx, Fy);
           if (adapt) {
             // the largest squared residual over the workgroup (a square root
-            // keeps the order): the lanes of a marker hold the same value, so
-            // each row of 16 lanes folds to one in two steps
+            // keeps the order)
             double r = live ? ex * ex + ey * ey : 0.0;
             r = r == r ? r : 0.0;
-            r = fmax(r, dpp_f64<0x141>(r));  // row_half_mirror
-            r = fmax(r, dpp_f64<0x140>(r));  // row_mirror
-            if (NS == 2) r = fmax(r, dpp_f64<0x4E>(r));
+            if (LPM == 1) r = fmax(r, dpp_f64<0xB1>(r));
+            r = fmax(r, dpp_f64<0x4E>(r));
+            r = fmax(r, dpp_f64<0x141>(r));
+            r = fmax(r, dpp_f64<0x140>(r));
             r = fmax(fmax(lane_f64(r, 0), lane_f64(r, 16)), fmax(lane_f64(r, 32), lane_f64(r, 48)));
             if ((tid & 63) == 0) atomicMax(&sh.rmax[n % 3], (unsigned long long)__double_as_longlong(r));
           } else if (n == N) {
@@ -578,12 +629,12 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
 #pragma unroll
           for (int q = 0; q < QMAX; q++)
             if (q < nq) {
-              const double2 F = fb[m + h + q * NS];
+              const double2 F = fb[m + h + q * LPM];
               sx += bq[q] * F.x;
               sy += bq[q] * F.y;
             }
-          Ux += group_sum<NS>(sx);
-          Uy += group_sum<NS>(sy);
+          Ux += group_sum<LPM>(sx);
+          Uy += group_sum<LPM>(sy);
         }
         a5 = res;
         // every lane has read the last pass's forces
@@ -593,71 +644,85 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
       }
       // Eulerian force f(x) = sum_k F_total D_h ds (Eq. 8) on the nodes whose
       // first marker is this lane's; DF also adds f/(2 rho) to the velocity
-      // for the slip, so there every lane sums every node of its row
+      // for the slip, so there every lane sums every node of its rows
       if (owned) {
-        double fx[NS], fy[NS];
+        double sa = 0, sb = 0;
 #pragma unroll
-        for (int j = 0; j < NS; j++) fx[j] = fy[j] = 0.0;
-        const uint32_t set = !mdf ? cov : (mine ? cov & (~0u << bw) : 0u);
-        for_cover(set, [&](int i, const double *w, double wyl) {
-          const double2 F = lF[m + i];
-          const double Fx = F.x * wyl, Fy = F.y * wyl;
+        for (int r = 0; r < RPL; r++) {
+          double fx[NS], fy[NS];
 #pragma unroll
-          for (int j = 0; j < NS; j++) {
-            fx[j] += Fx * w[j];
-            fy[j] += Fy * w[j];
+          for (int j = 0; j < NS; j++) fx[j] = fy[j] = 0.0;
+          const uint32_t set = KIND == kArcDF ? cov[r] : (mine[r] ? cov[r] & (~0u << bw) : 0u);
+          for_cover(set, y0 + r, [&](int i, const double *w, double wyl) {
+            const double2 F = lF[m + i];
+            const double Fx = F.x * wyl, Fy = F.y * wyl;
+#pragma unroll
+            for (int j = 0; j < NS; j++) {
+              fx[j] += Fx * w[j];
+              fy[j] += Fy * w[j];
+            }
+          });
+          gmem<T> *const frc = to_global((T *)c.force) + ((uint32_t)(y0 + r) * nx + ix0);
+#pragma unroll
+          for (int j = 0; j < NS; j++)
+            if (mine[r] & (1u << j)) {
+              frc[j] = (T)(fx[j] * ds);
+              frc[plane + j] = (T)(fy[j] * ds);
+            }
+          if constexpr (KIND == kArcDF) {
+            double qa = 0, qb = 0;
+#pragma unroll
+            for (int j = 0; j < NS; j++) {
+              const double g = 0.5 * ds * rin[r][j];
+              qa += (ux[r][j] + fx[j] * g) * wx[j];
+              qb += (uy[r][j] + fy[j] * g) * wx[j];
+            }
+            sa += qa * wy[r];
+            sb += qb * wy[r];
           }
-        });
-        gmem<T> *const frc = to_global((T *)c.force) + ((uint32_t)yrow * nx + ix0);
-#pragma unroll
-        for (int j = 0; j < NS; j++)
-          if (mine & (1u << j)) {
-            frc[j] = (T)(fx[j] * ds);
-            frc[plane + j] = (T)(fy[j] * ds);
-          }
-        if (!mdf) {
-          double qa = 0, qb = 0;
-#pragma unroll
-          for (int j = 0; j < NS; j++) {
-            const double g = 0.5 * ds * rin[j];
-            qa += (ux[j] + fx[j] * g) * wx[j];
-            qb += (uy[j] + fy[j] * g) * wx[j];
-          }
-          Ux = group_sum<NS>(qa * wy);
-          Uy = group_sum<NS>(qb * wy);
+        }
+        if constexpr (KIND == kArcDF) {
+          Ux = group_sum<LPM>(sa);
+          Uy = group_sum<LPM>(sb);
         }
         if (h == 0) {
           // force on the body (Newton's third law) and torque (Sec. 2.7)
-          a1 = -Ftx * ds * wsum;
-          a2 = -Fty * ds * wsum;
-          a3 = -((X - xc) * Fty - (Y - yc) * Ftx) * ds;
+          const double ws = lX[3 * m + 2];
+          a1 = -Ftx * ds * ws;
+          a2 = -Fty * ds * ws;
+          a3 = -((lX[3 * m] - sh.kin.xc) * Fty - (lX[3 * m + 1] - sh.kin.yc) * Ftx) * ds;
         }
       }
     } else {
       // DFC, Eq. (15)-(20)
+      T v[RPL][9][NS];
+#pragma unroll
+      for (int r = 0; r < RPL; r++) load_row(y0 + r, v[r]);
       double gi[9];
 #pragma unroll
       for (int i = 0; i < 9; i++) {
-        double r = 0.0;
+        double s = 0.0;
 #pragma unroll
-        for (int j = 0; j < NS; j++) r += (double)v[i][j] * wx[j];
-        gi[i] = group_sum<NS>(r * wy);
+        for (int r = 0; r < RPL; r++) {
+          double q = 0.0;
+#pragma unroll
+          for (int j = 0; j < NS; j++) q += (double)v[r][i][j] * wx[j];
+          s += q * wy[r];
+        }
+        gi[i] = group_sum<LPM>(s);
       }
       double fsx = 0, fsy = 0;
-      double dl[9];
 #pragma unroll
       for (int i = 0; i < 9; i++) {
         const double eud = c_exi[i] * udx + c_eyi[i] * udy;
-        dl[i] = lam * (gi[opp_of(i)] - gi[i] + 6.0 * c_w[i] * rho0 * eud);
-        fsx += c_exi[i] * dl[i];
-        fsy += c_eyi[i] * dl[i];
-      }
-#pragma unroll
-      for (int i = 0; i < 9; i++)
-        if (live && h == (i & (NS - 1))) {
-          lB[e0 * 9 + i] = dl[i];
-          if (e1 != e0) lB[e1 * 9 + i] = dl[i];
+        const double dl = lam * (gi[opp_of(i)] - gi[i] + 6.0 * c_w[i] * rho0 * eud);
+        fsx += c_exi[i] * dl;
+        fsy += c_eyi[i] * dl;
+        if (live && h == (i & (LPM - 1))) {
+          lB[e0 * 9 + i] = dl;
+          if (e1 != e0) lB[e1 * 9 + i] = dl;
         }
+      }
       Ftx = -ds * fsx;
       Fty = -ds * fsy;
       // every arc has read its populations before any of them is corrected
@@ -673,50 +738,60 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
         met = !(sh.flags & kFlagExchange);
       }
       if (owned && met) {
-        // Eq. (19) on every node of the lane's row; the first marker's lane
+        // Eq. (19) on every node of the lane's rows; the first marker's lane
         // writes it, and every lane takes the corrected velocity for the slip
-        double corr[NS][9];
+        // (two columns at a time: the sums of four would take 72 registers)
+        double sa = 0, sb = 0;
 #pragma unroll
-        for (int j = 0; j < NS; j++)
+        for (int r = 0; r < RPL; r++) {
+          double qa = 0, qb = 0;
 #pragma unroll
-          for (int i = 0; i < 9; i++) corr[j][i] = 0.0;
-        for_cover(cov, [&](int i, const double *w, double wyl) {
-          const double *q = lB + (m + i) * 9;
-          double dq[9];
+          for (int j0 = 0; j0 < NS; j0 += 2) {
+            double corr[2][9];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int n = 0; n < 9; n++) dq[n] = q[n];
+            for (int u = 0; u < 2; u++)
 #pragma unroll
-          for (int j = 0; j < NS; j++) {
-            const double ww = w[j] * wyl;
+              for (int i = 0; i < 9; i++) corr[u][i] = 0.0;
+            for_cover(cov[r], y0 + r, [&](int i, const double *w, double wyl) {
+              const double *q = lB + (m + i) * 9;
+              const double w0 = w[j0] * wyl, w1 = w[j0 + 1] * wyl;
 #pragma unroll
-            for (int n = 0; n < 9; n++) corr[j][n] += dq[n] * ww;
+              for (int n = 0; n < 9; n++) {
+                const double dq = q[n];
+                corr[0][n] += dq * w0;
+                corr[1][n] += dq * w1;
+              }
+            });
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+              const int j = j0 + u;
+              gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(ix0 + j, y0 + r, nseg);
+              const bool first = (mine[r] & (1u << j)) != 0;
+              if (first && c.wall_closed && is_zou_he_wall(c, ix0 + j, y0 + r))
+                c.wall_closed[wall_index(nx, ny, ix0 + j, y0 + r)] = 1;
+              T q[9];
+#pragma unroll
+              for (int i = 0; i < 9; i++) {
+                q[i] = (T)((double)v[r][i][j] + corr[u][i] * ds);
+                if (first) fw[i * kSeg] = q[i];
+              }
+              double sm, jx, jy;
+              node_sums<T>(q, rho0, sm, jx, jy);
+              const double inv = 1.0 / sm;
+              qa += jx * inv * wx[j];
+              qb += jy * inv * wx[j];
+            }
           }
-        });
-        double qa = 0, qb = 0;
-#pragma unroll
-        for (int j = 0; j < NS; j++) {
-          gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(ix0 + j, yrow, nseg);
-          const bool first = (mine & (1u << j)) != 0;
-          if (first && c.wall_closed && is_zou_he_wall(c, ix0 + j, yrow))
-            c.wall_closed[wall_index(nx, ny, ix0 + j, yrow)] = 1;
-          T q[9];
-#pragma unroll
-          for (int i = 0; i < 9; i++) {
-            q[i] = (T)((double)v[i][j] + corr[j][i] * ds);
-            if (first) fw[i * kSeg] = q[i];
-          }
-          double sm, jx, jy;
-          node_sums<T>(q, rho0, sm, jx, jy);
-          const double inv = 1.0 / sm;
-          qa += jx * inv * wx[j];
-          qb += jy * inv * wx[j];
+          sa += qa * wy[r];
+          sb += qb * wy[r];
         }
-        Ux = group_sum<NS>(qa * wy);
-        Uy = group_sum<NS>(qb * wy);
+        Ux = group_sum<LPM>(sa);
+        Uy = group_sum<LPM>(sb);
         if (h == 0) {
           a1 = Ftx;
           a2 = Fty;
-          a3 = (X - xc) * Fty - (Y - yc) * Ftx;
+          a3 = (lX[3 * m] - sh.kin.xc) * Fty - (lX[3 * m + 1] - sh.kin.yc) * Ftx;
         }
       }
     }
@@ -725,8 +800,9 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
       if (h == 0) {
         a4 = sqrt((Ux - udx) * (Ux - udx) + (Uy - udy) * (Uy - udy));
         a6 = a4;
-        mo[0] = X; mo[1] = Y; mo[2] = udx; mo[3] = udy;
-      } else if (h == 1) {
+        mo[0] = lX[3 * m]; mo[1] = lX[3 * m + 1]; mo[2] = udx; mo[3] = udy;
+      }
+      if (h == LPM - 1) {
         mo[4] = Ftx; mo[5] = Fty; mo[6] = lam; mo[7] = ds;
       }
     }
@@ -811,12 +887,12 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
     const int f = sh.flags | kFlagRange;
     g->flags = f;
     g->box_valid = 0;
-    case_body_done(c, c.state, step, cur, nslots, f, 0, box);
+    case_body_done(c, c.state, step, cur, nslots, f, 0, box, par);
     return;
   }
   int flags = sh.flags;
   if (!isfinite(a1) || !isfinite(a2) || !isfinite(a3) || !isfinite(a4)) flags |= kFlagNonfinite;
-  const int box_valid = DFC ? 0 : 1;
+  const int box_valid = KIND == kArcDFC ? 0 : 1;
   double vx = kn.vhx, vy = kn.vhy, om = kn.omh;
   if (motion == kFree) {
     if (!euler) {
@@ -828,13 +904,13 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
     if (!isfinite(vx) || !isfinite(vy) || fabs(vx) > 0.5 || fabs(vy) > 0.5) flags |= kFlagNonfinite;
   } else if (motion == kFixed) {
     vx = 0.0; vy = 0.0; om = 0.0;
-    if (DFC) g->lambda_valid = 1;
+    if (KIND == kArcDFC) g->lambda_valid = 1;
   }
-  const double slip_mean = a4 / nb, res = B.scheme == kMDF ? fmax(a5, 0.0) : 0.0;
+  const double slip_mean = a4 / nb, res = KIND == kArcMDF ? fmax(a5, 0.0) : 0.0;
   g->fhx = a1; g->fhy = a2; g->torque = a3;
   g->slip_mean = slip_mean; g->slip_max = a6; g->mdf_res = res;
   g->mdf_iters_done = iters;
-  if (!DFC)
+  if (KIND != kArcDFC)
     for (int i = 0; i < 4; i++) g->box[i] = box[i];
   g->box_valid = box_valid;
   if (motion != kPrescribedSin) { g->vx = vx; g->vy = vy; g->om = om; }
@@ -845,6 +921,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
   hr[9] = slip_mean; hr[10] = a6; hr[11] = res;
   hr[12] = iters; hr[13] = flags; hr[14] = 0; hr[15] = 0;
   {
+    c.state->hold_step = step + 1;
     int32_t *const hb = c.state->hold[cur ^ 1][body];
     if (motion == kFree) {
       BodyState t;
@@ -858,25 +935,32 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
       for (int i = 0; i < 4; i++) hb[i] = sh.hold[i];
     }
   }
-  case_body_done(c, c.state, step, cur, nslots, flags, box_valid, box);
+  case_body_done(c, c.state, step, cur, nslots, flags, box_valid, box, par);
 }
 
-// The pass of one arc (see arc_pass).  KIND: 0 any scheme, 1 DF or MDF, 2 DFC.
-template <typename T, int KIND, bool OPEN>
+// The pass of one arc (see arc_pass).  SET: the schemes the instance holds, 0
+// all, 1 DF and MDF, 2 DFC.
+template <typename T, int SET, bool OPEN>
 __device__ __forceinline__ void arc_body(const CaseDesc &c, const BodyDesc &B, int64_t step, int cur,
-                                         int arc, int body, int nslots, int wait_for, double *dyn,
+                                         int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
-  if (KIND == 2 || (KIND == 0 && B.scheme == kDFC)) {
-    if constexpr (KIND != 1) {
-      if (B.ns == 2) arc_pass<T, 2, true, OPEN>(c, B, step, cur, arc, body, nslots, wait_for, dyn, sh);
-      else arc_pass<T, 4, true, OPEN>(c, B, step, cur, arc, body, nslots, wait_for, dyn, sh);
+#define IBL_PASS(NSV, KINDV, RPLV) \
+  arc_pass<T, NSV, KINDV, RPLV, OPEN>(c, B, step, cur, arc, body, nslots, wait_for, par, dyn, sh)
+  if (SET == 2 || (SET == 0 && B.scheme == kDFC)) {
+    if constexpr (SET != 1) {
+      if (B.ns == 2) IBL_PASS(2, kArcDFC, 1);
+      else IBL_PASS(4, kArcDFC, 1);
     }
-  } else {
-    if constexpr (KIND != 2) {
-      if (B.ns == 2) arc_pass<T, 2, false, OPEN>(c, B, step, cur, arc, body, nslots, wait_for, dyn, sh);
-      else arc_pass<T, 4, false, OPEN>(c, B, step, cur, arc, body, nslots, wait_for, dyn, sh);
+  } else if constexpr (SET != 2) {
+    if (B.scheme == kMDF) {
+      if (B.ns == 2) IBL_PASS(2, kArcMDF, 1);
+      else IBL_PASS(4, kArcMDF, 1);
+    } else {
+      if (B.ns == 2) IBL_PASS(2, kArcDF, 1);
+      else IBL_PASS(4, kArcDF, 1);
     }
   }
+#undef IBL_PASS
 }
 
 }  // namespace iblbm

@@ -138,6 +138,11 @@ struct ib_lbm_batch {
   IbSlots ib;
   ib_lbm_launch launch = {128, 2, 1, 1};
   int spread_mode = 0;
+  // One-launch steps (see OneShape): the cases' arguments and prefix sums
+  bool one = false;
+  DevBuf d_one, d_one_prefix, d_work;
+  StepBatchArgs one_args{};
+  int one_threads = 0, one_lds = 0, one_face = 0;
   int graph_steps = 0;
   hipGraphExec_t graph_exec = nullptr;
   int graph_len = 0;
@@ -407,33 +412,39 @@ ib_lbm_status plan_fused(ib_lbm_sim *s) {
 static bool general_zero_gradient(const CaseDesc &c);
 int arc_lds_bytes(const BodyDesc &B);
 
-// One-launch steps (step_one_kernel): a sim without bodies, or whose bodies
-// are all cut into arcs.  The arcs wait for the tiles they depend on while
-// they are resident, so at most kOneMaxArcs workgroups of a launch wait: half
-// of the part's compute units at one workgroup each, the other half always
-// runs tiles.  All workgroups have the size the arcs need (a body-free sim
-// 256 threads).  Tiles are 128 nodes wide on lattices of at least 1024 columns
-// (186 against 192 us per step on 7175 x 2014, 23.8 against 24.5 us on 1200 x
-// 600) and 64 below, where a row's last tile is mostly past its end and the
-// hold rectangle is a larger share (22.0 against 23.6 us on 400 x 2000 FP64).
-constexpr int kOneMaxArcs = 128;
-void plan_one(ib_lbm_sim *s) {
-  s->one = false;
-  if (!s->overlap || !s->fused_allowed) return;
-  const CaseDesc &c = s->cd;
-  StepOneArgs &a = s->one_args;
-  memset(&a, 0, sizeof a);
+// One-launch steps (step_one_kernel, step_batch_kernel): sims without bodies,
+// or whose bodies are all cut into arcs.  The arcs wait for the tiles they
+// depend on while they are resident, so a launch has at most half as many arcs
+// as workgroups fit the device (step_max_waiting): the rest always runs tiles.
+// All workgroups have the size the arcs need (256 threads without bodies).
+// Tiles are 128 nodes wide on lattices of at least 1024 columns (186 against
+// 192 us per step on 7175 x 2014, 23.8 against 24.5 us on 1200 x 600) and 64
+// below, where a row's last tile is mostly past its end and the hold rectangle
+// is a larger share (22.0 against 23.6 us on 400 x 2000 FP64).  One row per
+// thread for a sim on its own, whose pass waits for the first tiles; two in a
+// batch, whose tiles outlast the passes (12 cases, 3.6 M nodes: 68 us per step
+// against 76 with one row and 67 with four).
+struct OneShape {
   int threads = 256, lds = 0;
-  for (auto &hb : s->bodies) {
-    if (!body_arcs(hb, s->spread_mode)) return;
-    threads = std::max(threads, hb.dev.arc_threads);
-    lds = std::max(lds, arc_lds_bytes(hb.dev));
+  // false: the bodies do not all run in arcs
+  bool add(const std::vector<HostBody> &bodies, int spread_mode) {
+    for (auto &hb : bodies) {
+      if (!body_arcs(hb, spread_mode)) return false;
+      threads = std::max(threads, hb.dev.arc_threads);
+      lds = std::max(lds, arc_lds_bytes(hb.dev));
+    }
+    return true;
   }
-  if (!s->bodies.empty() && s->bodies[0].dev.scheme == kDFC && threads > 512) return;
+};
+
+void fill_step_args(const ib_lbm_sim *s, int threads, int rows, StepOneArgs *out) {
+  const CaseDesc &c = s->cd;
+  StepOneArgs &a = *out;
+  memset(&a, 0, sizeof a);
   a.bx = c.nx >= 1024 ? 128 : 64;
   a.by = threads / a.bx;
   a.lean = lean_args(s, 0, 0);
-  a.lean.rpt = 1;
+  a.lean.rpt = rows;
   a.lean.remap = 1;
   const int TX = a.bx, TY = a.by * a.lean.rpt;
   while ((1 << a.tx_shift) < TX) a.tx_shift++;
@@ -443,7 +454,11 @@ void plan_one(ib_lbm_sim *s) {
   a.nface = (face_nodes(c.nx, c.ny) + threads - 1) / threads;
   a.cd = c;
   a.c = (const CaseDesc *)s->d_case.p;
-  for (size_t b = 0; b < s->bodies.size(); b++) {
+  const size_t nb = s->bodies.size();
+  for (size_t b = 0; b < kMaxBodiesPerCase; b++) {
+    a.arc_first[b + 1] = a.arc_first[b];
+    a.hold_first[b + 1] = a.hold_first[b];
+    if (b >= nb) continue;
     const HostBody &hb = s->bodies[b];
     // slots for the tiles of its hold rectangle at the speeds a body moves at
     // (a faster one's further tiles are updated in their turn)
@@ -452,21 +467,25 @@ void plan_one(ib_lbm_sim *s) {
       mv = std::min(64.0, 2.0 * M_PI * std::fabs(hb.d.freq) *
                               std::max(std::fabs(hb.d.amp[0]), std::fabs(hb.d.amp[1])));
     const int w = (int)std::ceil(2.0 * hb.dev.radius + mv) + hb.dev.ns + 8;
-    a.arc_first[b + 1] = a.arc_first[b] + hb.dev.arc_n;
-    a.hold_first[b + 1] = a.hold_first[b] + ((w >> a.tx_shift) + 2) * ((w >> a.ty_shift) + 2);
+    a.arc_first[b + 1] += hb.dev.arc_n;
+    a.hold_first[b + 1] += ((w >> a.tx_shift) + 2) * ((w >> a.ty_shift) + 2);
   }
-  const size_t nb = s->bodies.size();
-  for (size_t b = nb; b < kMaxBodiesPerCase; b++) {
-    a.arc_first[b + 1] = a.arc_first[nb];
-    a.hold_first[b + 1] = a.hold_first[nb];
-  }
-  a.narcs = a.arc_first[nb];
-  a.nhold = a.hold_first[nb];
-  if (a.narcs > kOneMaxArcs) return;
-  s->one_threads = threads;
-  s->one_lds = lds;
-  s->one_face = has_zou_he(c) ? 2 : (general_zero_gradient(c) ? 1 : 0);
-  s->one = true;
+  a.narcs = a.arc_first[kMaxBodiesPerCase];
+  a.nhold = a.hold_first[kMaxBodiesPerCase];
+}
+
+void plan_one(ib_lbm_sim *s) {
+  s->one = false;
+  if (!s->overlap || !s->fused_allowed) return;
+  OneShape sh;
+  if (!sh.add(s->bodies, s->spread_mode)) return;
+  const bool dfc = !s->bodies.empty() && s->bodies[0].dev.scheme == kDFC;
+  if (dfc && sh.threads > 512) return;
+  fill_step_args(s, sh.threads, 1, &s->one_args);
+  s->one_threads = sh.threads;
+  s->one_lds = sh.lds;
+  s->one_face = has_zou_he(s->cd) ? 2 : (general_zero_gradient(s->cd) ? 1 : 0);
+  s->one = s->one_args.narcs <= step_max_waiting(s->cd.precision, s->one_face, dfc, false, sh.threads, sh.lds);
 }
 
 // A body runs on the 1024-thread IB kernel when it is DF/MDF, its workspace
@@ -483,18 +502,17 @@ bool body_arcs(const HostBody &hb, int spread_mode) { return spread_mode == 0 &&
 // Cut a body's pass into arcs (arc_device.h).  Markers that share a support
 // node are less than ns apart in x and in y, so less than ns sqrt 2: on the
 // circle of radius R that bounds |l - k| by (n_b / pi) asin(ns sqrt 2 / (2
-// R)), the band half-width bw.  A marker takes ns lanes, so a workgroup of t
-// threads holds t / ns markers: a body of at most that many is one arc, else
-// the own markers of an arc are what the margins on both sides leave.  The
-// margin is bw for DF, 2 bw for DFC (whose correction scale sums over the
-// markers around each one) and N bw for N marker-space MDF passes.
-// Adaptive MDF needs the residual of all markers in every pass, so it runs
-// as one arc or not at all; coupled MDF, Eq. D1 bodies, very small circles
-// and bodies with very dense markers keep the one-workgroup kernels.
-// Workgroup sizes: 256 threads for DF and DFC (short passes, bound by
-// latency: the smallest arcs with margins that still are the smaller part);
-// MDF takes 512 once 256 do not hold the whole body, and 1024 when the
-// margins would outweigh the own markers at 512.
+// R)), the band half-width bw.  A marker takes ns lanes, so a workgroup of
+// t threads holds t / ns markers: a body of at most that many is one
+// arc, else the own markers of an arc are what the margins on both sides leave.
+// The margin is bw for DF, 2 bw for DFC (whose correction scale sums over the
+// markers around each one) and N bw for N marker-space MDF passes.  Adaptive
+// MDF needs the residual of all markers in every pass, so it runs as one arc
+// or not at all; coupled MDF, Eq. D1 bodies, very small circles and bodies with
+// very dense markers keep the one-workgroup kernels.
+// The smallest workgroup whose margins leave a quarter of its markers is
+// taken: a pass is bound by instruction issue, and a wave more on each SIMD
+// costs as much as the pass of the wave that is there.
 void plan_arcs(BodyDesc *B) {
   B->arc_n = 0;
   if (B->mdf_coupled || B->udes != kUdRigid) return;
@@ -512,7 +530,7 @@ void plan_arcs(BodyDesc *B) {
     if (nb <= cap) {
       own = nb;
       n = 1;
-    } else if (!adapt && cap - 2 * halo >= cap / 3) {
+    } else if (!adapt && cap - 2 * halo >= cap / 4) {
       n = (int)((nb + cap - 2 * halo - 1) / (cap - 2 * halo));
       own = (nb + n - 1) / n;
       n = (nb + own - 1) / own;
@@ -2025,16 +2043,21 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
   SlotLists lists;
   for (int ci = 0; ci < (int)cases.size(); ci++) lists.add(case_sims[ci]->bodies, ci, b->spread_mode);
   slots = lists.finish();
-  auto upload = [&](DevBuf *d, const void *src, size_t bytes) -> ib_lbm_status {
-    if (d->bytes < bytes) {
-      if (d->p) (void)hipFree(d->p);
-      d->p = nullptr;
-      if (hipMalloc(&d->p, bytes) != hipSuccess) {
-        set_err(&b->err, "batch table allocation failed");
-        return IB_LBM_E_NOMEM;
-      }
-      d->bytes = bytes;
+  auto reserve = [&](DevBuf *d, size_t bytes) -> ib_lbm_status {
+    if (d->bytes >= bytes) return IB_LBM_OK;
+    if (d->p) (void)hipFree(d->p);
+    d->p = nullptr;
+    d->bytes = 0;
+    if (hipMalloc(&d->p, bytes) != hipSuccess) {
+      set_err(&b->err, "batch table allocation failed");
+      return IB_LBM_E_NOMEM;
     }
+    d->bytes = bytes;
+    return IB_LBM_OK;
+  };
+  auto upload = [&](DevBuf *d, const void *src, size_t bytes) -> ib_lbm_status {
+    ib_lbm_status rs = reserve(d, bytes);
+    if (rs) return rs;
     BHIPCHK(b, hipMemcpy(d->p, src, bytes, hipMemcpyHostToDevice));
     return IB_LBM_OK;
   };
@@ -2046,7 +2069,74 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
     if ((st = upload(&b->d_slots, slots.data(), slots.size() * sizeof(IbmSlot)))) return st;
   }
   b->ib = lists.ib;
+  OneShape sh;
+  b->one = !cases.empty();
+  b->one_face = 0;
+  for (auto *s : case_sims) {
+    b->one = b->one && sh.add(s->bodies, b->spread_mode);
+    if (general_zero_gradient(s->cd)) b->one_face = 1;
+  }
+  if (b->one) {
+    std::vector<StepOneArgs> one(cases.size());
+    std::vector<int32_t> pre[3];
+    StepBatchArgs &g = b->one_args;
+    memset(&g, 0, sizeof g);
+    for (size_t i = 0; i < cases.size(); i++) {
+      fill_step_args(case_sims[i], sh.threads, 2, &one[i]);
+      pre[0].push_back(g.nhold);
+      pre[1].push_back(g.nface);
+      pre[2].push_back(g.ntile);
+      g.narcs += one[i].narcs;
+      g.nhold += one[i].nhold;
+      g.nface += one[i].nface;
+      g.ntile += one[i].lean.ntiles;
+    }
+    b->one = g.narcs <= step_max_waiting(b->precision, b->one_face, false, true, sh.threads, sh.lds);
+    if (b->one) {
+      if ((st = upload(&b->d_one, one.data(), one.size() * sizeof(StepOneArgs)))) return st;
+      std::vector<int32_t> all;
+      for (auto &p : pre) all.insert(all.end(), p.begin(), p.end());
+      if ((st = upload(&b->d_one_prefix, all.data(), all.size() * sizeof(int32_t)))) return st;
+      const size_t n = cases.size();
+      g.cases = (const StepOneArgs *)b->d_one.p;
+      g.arcs = (const IbmSlot *)b->d_slots.p;
+      g.hold_prefix = (const int32_t *)b->d_one_prefix.p;
+      g.face_prefix = g.hold_prefix + n;
+      g.tile_prefix = g.hold_prefix + 2 * n;
+      g.ncases = (int)n;
+      g.nwork = g.nhold + g.nface + (g.ntile + 7) / 8 * 8;
+      if ((st = reserve(&b->d_work, (size_t)g.nwork * sizeof(StepWork)))) return st;
+      g.work = (StepWork *)b->d_work.p;
+      BHIPCHK(b, launch_batch_work(g, b->stream));
+      b->one_threads = sh.threads;
+      b->one_lds = sh.lds;
+    }
+  }
+
   b->dirty = false;
+  return IB_LBM_OK;
+}
+
+static ib_lbm_status batch_enqueue_step(ib_lbm_batch *b, hipStream_t stream);
+
+// Enqueue nsteps steps of the batch: one launch each where it can, after the
+// control words are set from the cases' states, so that the parity of the
+// launches always starts at 0.
+static ib_lbm_status batch_enqueue(ib_lbm_batch *b, int64_t nsteps, hipStream_t stream) {
+  if (nsteps <= 0) return IB_LBM_OK;
+  if (!b->one) {
+    for (int64_t i = 0; i < nsteps; i++) {
+      ib_lbm_status st = batch_enqueue_step(b, stream);
+      if (st) return st;
+    }
+    return IB_LBM_OK;
+  }
+  StepBatchArgs g = b->one_args;
+  BHIPCHK(b, launch_batch_control(g.cases, g.ncases, stream));
+  for (int64_t i = 0; i < nsteps; i++) {
+    g.par = (int)(i & 1);
+    BHIPCHK(b, launch_step_batch(b->precision, b->one_face, g, b->one_threads, b->one_lds, stream));
+  }
   return IB_LBM_OK;
 }
 
@@ -2080,12 +2170,10 @@ ib_lbm_status ib_lbm_batch_step(ib_lbm_batch *b, int64_t nsteps) {
       if (!b->cap_stream) BHIPCHK(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
       hipGraph_t g;
       BHIPCHK(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
-      for (int i = 0; i < b->graph_steps; i++) {
-        if ((st = batch_enqueue_step(b, b->cap_stream))) {
-          hipGraph_t dummy;
-          (void)hipStreamEndCapture(b->cap_stream, &dummy);
-          return st;
-        }
+      if ((st = batch_enqueue(b, b->graph_steps, b->cap_stream))) {
+        hipGraph_t dummy;
+        (void)hipStreamEndCapture(b->cap_stream, &dummy);
+        return st;
       }
       BHIPCHK(b, hipStreamEndCapture(b->cap_stream, &g));
       BHIPCHK(b, hipGraphInstantiate(&b->graph_exec, g, nullptr, nullptr, 0));
@@ -2097,9 +2185,7 @@ ib_lbm_status ib_lbm_batch_step(ib_lbm_batch *b, int64_t nsteps) {
       left -= b->graph_len;
     }
   }
-  for (int64_t i = 0; i < left; i++)
-    if ((st = batch_enqueue_step(b, b->stream))) return st;
-  return IB_LBM_OK;
+  return batch_enqueue(b, left, b->stream);
 }
 
 ib_lbm_status ib_lbm_batch_set_graph(ib_lbm_batch *b, int32_t steps_per_graph) {
@@ -2147,6 +2233,9 @@ ib_lbm_status ib_lbm_batch_destroy(ib_lbm_batch *b) {
   if (b->d_prefix.p) (void)hipFree(b->d_prefix.p);
   if (b->d_fprefix.p) (void)hipFree(b->d_fprefix.p);
   if (b->d_slots.p) (void)hipFree(b->d_slots.p);
+  if (b->d_one.p) (void)hipFree(b->d_one.p);
+  if (b->d_one_prefix.p) (void)hipFree(b->d_one_prefix.p);
+  if (b->d_work.p) (void)hipFree(b->d_work.p);
   delete b;
   return IB_LBM_OK;
 }

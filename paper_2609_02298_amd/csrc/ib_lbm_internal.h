@@ -93,7 +93,12 @@ struct CaseState {
   int32_t halt[2];
   int32_t hold[2][kMaxBodiesPerCase][4];
   int32_t hold_done[kMaxBodiesPerCase];  // workgroups of this launch that updated such nodes
+  // One-launch batch steps, by the parity of the launch: bit 0 the input
+  // lattice, bit 1 the case is stepped, bit 2 hold[] is set (kCtl*).
+  int32_t ctl[2];
+  int64_t hold_step;  // hold[] is that of the step from this time level
 };
+enum { kCtlCur = 1, kCtlActive = 2, kCtlHold = 4 };
 
 // Mutable per-body state, device resident.
 struct BodyState {
@@ -250,12 +255,12 @@ constexpr int kArcBandRegsHat = 6;  // bw <= 5
 constexpr int kArcMax = 64;         // arcs per body (one wave sums them)
 // LDS entries of an arc of nl local markers (a margin of bw on both sides,
 // ns of slack behind the last lane's share of the band) and its shared memory
-// in doubles: forces, weights, the band (MDF) or the corrections (DFC), and
+// in doubles: position and weight sum, forces, weights, the band (MDF) or the corrections (DFC), and
 // the packed stencil origins.
 __host__ __device__ inline int arc_entries(int ns, int bw, int nl) { return nl + 2 * bw + ns; }
 __host__ __device__ inline int arc_lds_doubles(int scheme, int ns, int bw, int nl) {
   const int e = arc_entries(ns, bw, nl);
-  return e * (4 + 4 * ns + 2 + (scheme == 2 ? 9 : (scheme == 1 ? bw + 1 : 0))) + (e + 1) / 2;
+  return 3 * nl + e * (4 + 4 * ns + 2 + (scheme == 2 ? 9 : (scheme == 1 ? bw + 1 : 0))) + (e + 1) / 2;
 }
 
 // One IB workgroup: the body `body` of case `cas` (body = -1: a case without
@@ -429,6 +434,29 @@ struct StepOneArgs {
 // face: 0 the usual closures, 1 general zero-gradient, 2 Zou-He walls.
 hipError_t launch_step_one(int precision, int face, bool dfc, const StepOneArgs &a, int threads,
                            int lds_bytes, hipStream_t stream);
+// The same for every case of a batch (step_batch_kernel): the arcs of all
+// cases, then nwork workgroups (all hold slots, face workgroups and tiles) with
+// an entry each in `work`, which launch_batch_work fills from prefix sums over
+// the cases.  par: parity of the launch, from 0 after launch_batch_control,
+// which sets the cases' control words.
+struct StepWork {
+  int32_t cas;  // -1: none
+  int32_t idx;  // hold slot, face workgroup or tile of the case
+};
+struct StepBatchArgs {
+  const StepOneArgs *cases;
+  const IbmSlot *arcs;
+  StepWork *work;
+  const int32_t *hold_prefix, *face_prefix, *tile_prefix;  // ncases each
+  int32_t ncases, narcs, nhold, nface, ntile, nwork, par;
+};
+hipError_t launch_step_batch(int precision, int face, const StepBatchArgs &a, int threads, int lds_bytes,
+                             hipStream_t stream);
+hipError_t launch_batch_control(const StepOneArgs *cases, int ncases, hipStream_t stream);
+hipError_t launch_batch_work(const StepBatchArgs &a, hipStream_t stream);
+// Workgroups of a one-launch step that can wait at once without keeping the
+// rest from running: half of what the device holds.
+int step_max_waiting(int precision, int face, bool dfc, bool batch, int threads, int lds_bytes);
 int fused_grid(const FusedArgs &a);
 hipError_t launch_step_fused(int precision, int collision, const FusedArgs &a, int lds_bytes,
                              hipStream_t stream, LaunchTarget *ns = nullptr);

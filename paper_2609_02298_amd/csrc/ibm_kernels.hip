@@ -1528,7 +1528,7 @@ __global__ __launch_bounds__(MAXT) void ibm_arc_kernel(const CaseDesc *__restric
   const int cur = cs->cur;
   if (step >= cs->target || (cs->flags & kCaseHalted)) return;
   arc_body<T, (MAXT > 512 ? 1 : 0), false>(c, c.bodies[sl.body], step, cur, sl.arc, sl.body,
-                                           sl.slots_in_case, -1, dyn, sh);
+                                           sl.slots_in_case, -1, -1, dyn, sh);
 }
 
 hipError_t launch_ibm_arcs(int precision, const CaseDesc *cases, const IbmSlot *slots, int nslots,

@@ -151,3 +151,32 @@ def test_one_launch_steps_after_atomic_spreading():
         out.append(sim.populations())
         sim.close()
     assert rel(out[1], out[0]) < F64_FIELD
+
+
+@pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
+@pytest.mark.parametrize("graph", [0, 3])
+def test_batch_steps_are_bitwise_the_steps_alone(graph, prec):
+    """Cases that move, halt, have no body or wait at a target that is raised
+    later, stepped by shared launches in calls of odd and even lengths."""
+    import torch
+    names = ["seam-DF", "open-MDF", "meet-DF", "driven-DFC", "empty-open", "fast-MDF"]
+    targets = [9, 40, 40, 23, 17, 31]
+    print(f"batch of one-launch steps graph={graph} prec={prec}", flush=True)
+    stream = torch.cuda.current_stream().cuda_stream
+    batch = ib.Batch(prec, stream=stream)
+    sims = [ib.Sim(CASES[n], precision=prec, stream=stream) for n in names]
+    for s, t in zip(sims, targets):
+        batch.attach(s, target=t)
+    batch.set_graph(graph)
+    for k in (1, 7, 4, 30):
+        batch.step(k)
+    batch.set_target(sims[0], 14)
+    batch.step(5)
+    batch.sync()
+    targets[0] = 14
+    for n, s, t in zip(names, sims, targets):
+        ref = ib.Sim(CASES[n], precision=prec)
+        ref.step(t)
+        assert s.steps_done == ref.steps_done, n
+        assert np.array_equal(s.populations(), ref.populations()), n
+        ref.close()
