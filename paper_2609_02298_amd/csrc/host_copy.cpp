@@ -1,0 +1,128 @@
+#include "host_copy.h"
+
+#include <algorithm>
+#include <atomic>
+#include <cstring>
+#include <exception>
+#include <mutex>
+#include <thread>
+#include <vector>
+
+namespace iblbm {
+namespace {
+
+constexpr int kLanes = 6;                  // threads, each with a buffer and an event
+constexpr size_t kBlock = size_t(2) << 20; // bytes per buffer
+constexpr size_t kSmall = size_t(4) << 20; // copies below this are plain
+
+struct Lane {
+  void *buf = nullptr;
+  hipEvent_t done = nullptr;
+};
+
+std::mutex mu;           // all below
+Lane lanes[kLanes];
+void *pinned = nullptr;  // the lanes' buffers
+hipStream_t stream = nullptr;
+int lanes_dev = -1;      // the device the stream is on
+int users = 0;
+
+void drop_lanes() {
+  if (stream) (void)hipStreamDestroy(stream);
+  stream = nullptr;
+  for (Lane &l : lanes) {
+    if (l.done) (void)hipEventDestroy(l.done);
+    l = Lane{};
+  }
+  if (pinned) (void)hipHostFree(pinned);
+  pinned = nullptr;
+  lanes_dev = -1;
+}
+
+bool make_lanes(int dev) {
+  if (lanes_dev == dev) return true;
+  drop_lanes();
+  bool ok = hipHostMalloc(&pinned, kLanes * kBlock, hipHostMallocDefault) == hipSuccess &&
+            hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) == hipSuccess;
+  for (int i = 0; ok && i < kLanes; i++) {
+    lanes[i].buf = (char *)pinned + i * kBlock;
+    ok = hipEventCreateWithFlags(&lanes[i].done, hipEventDisableTiming) == hipSuccess;
+  }
+  if (!ok) {
+    (void)hipGetLastError();
+    drop_lanes();
+    return false;
+  }
+  lanes_dev = dev;
+  return true;
+}
+
+hipError_t plain(const HostCopy *p, int n) {
+  for (int i = 0; i < n; i++) {
+    const hipError_t e = hipMemcpy(p[i].host, p[i].dev, p[i].bytes, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// One lane: takes blocks until there are none left (or one has failed).
+void run_lane(Lane &l, int dev, const std::vector<HostCopy> &blocks, std::atomic<size_t> &next,
+              std::atomic<int> &err) {
+  hipError_t e = hipSetDevice(dev);
+  while (e == hipSuccess && err.load(std::memory_order_relaxed) == hipSuccess) {
+    const size_t i = next.fetch_add(1, std::memory_order_relaxed);
+    if (i >= blocks.size()) return;
+    const HostCopy &b = blocks[i];
+    e = hipMemcpyAsync(l.buf, b.dev, b.bytes, hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipEventRecord(l.done, stream);
+    if (e == hipSuccess) e = hipEventSynchronize(l.done);
+    if (e == hipSuccess) memcpy(b.host, l.buf, b.bytes);
+  }
+  if (e != hipSuccess) err.store((int)e, std::memory_order_relaxed);
+}
+
+}  // namespace
+
+hipError_t host_copy(const HostCopy *pieces, int n) {
+  size_t total = 0;
+  for (int i = 0; i < n; i++) total += pieces[i].bytes;
+  if (total < kSmall) return plain(pieces, n);
+  std::unique_lock<std::mutex> lk(mu, std::try_to_lock);
+  int dev = 0;
+  if (!lk.owns_lock() || hipGetDevice(&dev) != hipSuccess || !make_lanes(dev))
+    return plain(pieces, n);
+  std::atomic<size_t> next{0};
+  std::atomic<int> err{(int)hipSuccess};
+  std::vector<HostCopy> blocks;
+  std::vector<std::thread> threads;
+  try {
+    for (int i = 0; i < n; i++)
+      for (size_t o = 0; o < pieces[i].bytes; o += kBlock)
+        blocks.push_back({(char *)pieces[i].dev + o, (char *)pieces[i].host + o,
+                          std::min(kBlock, pieces[i].bytes - o)});
+    threads.reserve(kLanes);
+  } catch (const std::exception &) {
+    return plain(pieces, n);
+  }
+  try {
+    for (int t = 1; t < (int)std::min<size_t>(kLanes, blocks.size()); t++)
+      threads.emplace_back([&, t] { run_lane(lanes[t], dev, blocks, next, err); });
+  } catch (const std::exception &) {
+    // fewer threads than wanted: the others and the caller do the rest
+  }
+  run_lane(lanes[0], dev, blocks, next, err);
+  for (auto &t : threads) t.join();
+  return (hipError_t)err.load();
+}
+
+void host_copy_retain() {
+  std::lock_guard<std::mutex> lk(mu);
+  users++;
+}
+
+void host_copy_release() {
+  std::lock_guard<std::mutex> lk(mu);
+  if (--users == 0) drop_lanes();
+}
+
+}  // namespace iblbm

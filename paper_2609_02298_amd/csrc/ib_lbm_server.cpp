@@ -21,6 +21,7 @@
 
 #include "../../include/ib_lbm.h"
 #include "../../include/ib_lbm_server.h"
+#include "host_copy.h"
 
 namespace {
 
@@ -240,6 +241,7 @@ ib_lbm_status ib_lbm_server_create(const ib_lbm_server_config *cfg, ib_lbm_serve
   (void)ib_lbm_batch_set_spread(S->batch, S->cfg.spread);
   if (S->cfg.graph_steps > 0) (void)ib_lbm_batch_set_graph(S->batch, S->cfg.graph_steps);
   S->t0 = Clock::now();
+  iblbm::host_copy_retain();
   ib_lbm_server *raw = S.release();
   raw->worker = std::thread(worker_main, raw);
   *out = raw;
@@ -315,6 +317,7 @@ ib_lbm_status ib_lbm_server_destroy(ib_lbm_server *srv) {
   if (srv->worker.joinable()) srv->worker.join();
   (void)ib_lbm_batch_destroy(srv->batch);
   if (srv->own_stream) (void)hipStreamDestroy(srv->stream);
+  iblbm::host_copy_release();
   delete srv;
   return IB_LBM_OK;
 }
