@@ -550,12 +550,10 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
         // B_kl = sum_x D_h(x - X_k) D_h(x - X_l) ds / (2 rho(x)).  The lane
         // keeps its rows' terms of B's row k and, for the passes, its share of
         // the band in registers: a pass is one LDS round trip and one barrier.
-        // (four entries at a time: their LDS round trips overlap; 25.0 us per step
-        // on 2000 x 800 fp32, 25.7 with two)
-        for (int d0 = 0; d0 <= bw; d0 += 4) {
-          double b[4];
+        for (int d0 = 0; d0 <= bw; d0 += 2) {
+          double b[2];
 #pragma unroll
-          for (int u = 0; u < 4; u++) {
+          for (int u = 0; u < 2; u++) {
             const int e = e0 + min(d0 + u, bw);
             int dx, ly;
             offsets(lpos[e], y0, dx, ly);
@@ -573,7 +571,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
             }
           }
 #pragma unroll
-          for (int u = 0; u < 4; u++) {
+          for (int u = 0; u < 2; u++) {
             b[u] = group_sum<LPM>(b[u]);
             const int d = d0 + u;
             if (live && d <= bw && h == (d & (LPM - 1))) {

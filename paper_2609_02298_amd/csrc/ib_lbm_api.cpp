@@ -31,7 +31,7 @@ struct DevBuf {
 struct HostBody {
   ib_lbm_body_desc d;
   BodyDesc dev;  // host copy of the device description
-  DevBuf cos_t, sin_t, ws, tab, acc, markers, lambda, history, state;
+  DevBuf cos_t, sin_t, ws, tab, acc, markers, lambda, history, state, arc_part;
   // fused steps: the force copy and staged pushes (fixed DF/MDF bodies), and
   // the nodes the IB pass collides itself with their push map, built once
   // the device has built the body's tables
@@ -502,29 +502,25 @@ bool body_arcs(const HostBody &hb, int spread_mode) { return spread_mode == 0 &&
 
 // Cut a body's pass into arcs (arc_device.h).  Markers that share a support
 // node are less than ns apart in x and in y, so less than ns sqrt 2: on the
-// circle of radius R that makes |l - k| less than (n_b / pi) asin(ns sqrt 2 /
-// (2 R)); the band half-width bw is the largest whole number below it (up to
-// rounding of the markers).  A marker takes ns lanes, so a workgroup of t
-// threads holds t / ns markers: a body of at most that many is one arc, else
-// the own markers of an arc are what the margins on both sides leave.  The
-// margin is bw for DF, 2 bw for DFC (whose correction scale sums over the
+// circle of radius R that bounds |l - k| by (n_b / pi) asin(ns sqrt 2 / (2
+// R)), the band half-width bw.  A marker takes ns lanes, so a workgroup of
+// t threads holds t / ns markers: a body of at most that many is one
+// arc, else the own markers of an arc are what the margins on both sides leave.
+// The margin is bw for DF, 2 bw for DFC (whose correction scale sums over the
 // markers around each one) and N bw for N marker-space MDF passes.  Adaptive
 // MDF needs the residual of all markers in every pass, so it runs as one arc
 // or not at all; coupled MDF, Eq. D1 bodies, very small circles and bodies with
 // very dense markers keep the one-workgroup kernels.
-// The smallest workgroup whose margins leave an eighth of its markers is
-// taken: a pass is bound by instruction issue, so at 256 threads, one wave per
-// SIMD, it takes little more than half of what 512 take, and the work done
-// twice in the margins runs on compute units that would hold tiles for longer
-// (2000 x 800 MDF P4, 251 markers: XX us per step in 18 arcs of 256 threads,
-// 25.0 in 4 of 512).
+// The smallest workgroup whose margins leave a quarter of its markers is
+// taken: a pass is bound by instruction issue, and a wave more on each SIMD
+// costs as much as the pass of the wave that is there.
 void plan_arcs(BodyDesc *B) {
   B->arc_n = 0;
   if (B->mdf_coupled || B->udes != kUdRigid) return;
   const double q = B->ns * std::sqrt(2.0) / (2.0 * B->radius);
   if (!(q < 1.0)) return;
-  const int nb = B->nb, ns = B->ns, bw = (int)std::ceil(nb / M_PI * std::asin(q) + 1e-6) - 1;
-  if (bw < 1 || bw > 15 || 2 * bw + 1 >= nb) return;
+  const int nb = B->nb, ns = B->ns, bw = (int)std::floor(nb / M_PI * std::asin(q)) + 1;
+  if (bw > 15 || 2 * bw + 1 >= nb) return;
   const bool mdf = B->scheme == kMDF, adapt = mdf && B->mdf_tol > 0;
   const int regs = ns == 4 ? kArcBandRegsP4 : kArcBandRegsHat;
   if (mdf && 2 * bw + 1 > regs * ns) return;
@@ -535,7 +531,7 @@ void plan_arcs(BodyDesc *B) {
     if (nb <= cap) {
       own = nb;
       n = 1;
-    } else if (!adapt && cap - 2 * halo >= cap / 8) {
+    } else if (!adapt && cap - 2 * halo >= cap / 4) {
       n = (int)((nb + cap - 2 * halo - 1) / (cap - 2 * halo));
       own = (nb + n - 1) / n;
       n = (nb + own - 1) / own;
@@ -1357,9 +1353,8 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
   if ((st = dev_alloc(s, &hb.markers, (size_t)nb * 8 * 8))) return st;
   if ((st = dev_alloc(s, &hb.lambda, (size_t)nb * 8))) return st;
   if ((st = dev_alloc(s, &hb.history, (size_t)B.hist_cap * kHistCols * 8))) return st;
-  // the state, and behind it the arcs' partial sums
-  const size_t state_bytes = (sizeof(BodyState) + 63) / 64 * 64;
-  if ((st = dev_alloc(s, &hb.state, state_bytes + (size_t)B.arc_n * 8 * 8))) return st;
+  if ((st = dev_alloc(s, &hb.state, sizeof(BodyState)))) return st;
+  if ((st = dev_alloc(s, &hb.arc_part, (size_t)std::max(B.arc_n, 1) * 8 * 8))) return st;
   HIPCHK(s, hipMemcpy(hb.cos_t.p, ct.data(), nb * 8, hipMemcpyHostToDevice));
   HIPCHK(s, hipMemcpy(hb.sin_t.p, stb.data(), nb * 8, hipMemcpyHostToDevice));
   HIPCHK(s, hipMemset(hb.markers.p, 0, (size_t)nb * 64));
@@ -1373,13 +1368,13 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
   B.lambda_cache = (double *)hb.lambda.p;
   B.history = (double *)hb.history.p;
   B.state = (BodyState *)hb.state.p;
-  B.arc_part = (double *)((char *)hb.state.p + state_bytes);
+  B.arc_part = (double *)hb.arc_part.p;
   B.src = nullptr;
   B.n_src = 0;
   B.fprev = nullptr;
   B.pstage = nullptr;
-  if (b->motion == IB_LBM_FIXED && b->scheme != IB_LBM_DFC && B.arc_n == 0) {
-    // fused steps of a body that is not cut into arcs: the copy of the last force (zero, as the force field
+  if (b->motion == IB_LBM_FIXED && b->scheme != IB_LBM_DFC) {
+    // fused steps: the copy of the last force (zero, as the force field
     // starts) and the staged pushes of the support nodes
     if ((st = dev_alloc(s, &hb.fprev, (size_t)B.max_nodes * 2 * B.pop_bytes))) return st;
     if ((st = dev_alloc(s, &hb.pstage, (size_t)B.max_nodes * 9 * B.pop_bytes))) return st;
@@ -1761,6 +1756,7 @@ ib_lbm_status ib_lbm_destroy(ib_lbm_sim *s) {
   for (auto &hb : s->bodies) {
     dev_free(s, &hb.cos_t); dev_free(s, &hb.sin_t); dev_free(s, &hb.ws); dev_free(s, &hb.markers);
     dev_free(s, &hb.tab); dev_free(s, &hb.acc);
+    dev_free(s, &hb.arc_part);
     dev_free(s, &hb.lambda); dev_free(s, &hb.history); dev_free(s, &hb.state);
     dev_free(s, &hb.fprev); dev_free(s, &hb.pstage); dev_free(s, &hb.src);
   }
