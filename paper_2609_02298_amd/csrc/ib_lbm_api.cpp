@@ -502,24 +502,31 @@ bool body_arcs(const HostBody &hb, int spread_mode) { return spread_mode == 0 &&
 
 // Cut a body's pass into arcs (arc_device.h).  Markers that share a support
 // node are less than ns apart in x and in y, so less than ns sqrt 2: on the
-// circle of radius R that bounds |l - k| by (n_b / pi) asin(ns sqrt 2 / (2
-// R)), the band half-width bw.  A marker takes ns lanes, so a workgroup of
-// t threads holds t / ns markers: a body of at most that many is one
-// arc, else the own markers of an arc are what the margins on both sides leave.
-// The margin is bw for DF, 2 bw for DFC (whose correction scale sums over the
-// markers around each one) and N bw for N marker-space MDF passes.  Adaptive
-// MDF needs the residual of all markers in every pass, so it runs as one arc
-// or not at all; coupled MDF, Eq. D1 bodies, very small circles and bodies with
-// very dense markers keep the one-workgroup kernels.
+// circle of radius R that makes |l - k| less than (n_b / pi) asin(ns sqrt 2 /
+// (2 R)); the band half-width bw is the largest whole number below it (1e-6 for
+// the rounding of the markers; at least 1).  One marker more on each side costs
+// as much margin in every pass: 2000 x 800 MDF P4 takes 24.4 us per step, 25.2
+// with it.
+// A marker takes ns lanes, so a workgroup of t threads holds t / ns markers: a
+// body of at most that many is one arc, else the own markers of an arc are what
+// the margins on both sides leave.  The margin is bw for DF, 2 bw for DFC (whose
+// correction scale sums over the markers around each one) and N bw for N
+// marker-space MDF passes.  Adaptive MDF needs the residual of all markers in
+// every pass, so it runs as one arc or not at all; coupled MDF, Eq. D1 bodies,
+// very small circles and bodies with very dense markers keep the one-workgroup
+// kernels.
 // The smallest workgroup whose margins leave a quarter of its markers is
 // taken: a pass is bound by instruction issue, and a wave more on each SIMD
-// costs as much as the pass of the wave that is there.
+// costs as much as the pass of the wave that is there.  At an eighth more
+// bodies take many arcs of 256 threads, whose repeated margins hold up the
+// tiles: 2000 x 800 MDF P4 fp32 23.9 us per step instead of 24.4, but fp64 36.5
+// instead of 35.5 and a batch of twelve 68.9 instead of 66.9.
 void plan_arcs(BodyDesc *B) {
   B->arc_n = 0;
   if (B->mdf_coupled || B->udes != kUdRigid) return;
   const double q = B->ns * std::sqrt(2.0) / (2.0 * B->radius);
   if (!(q < 1.0)) return;
-  const int nb = B->nb, ns = B->ns, bw = (int)std::floor(nb / M_PI * std::asin(q)) + 1;
+  const int nb = B->nb, ns = B->ns, bw = std::max((int)std::ceil(nb / M_PI * std::asin(q) + 1e-6) - 1, 1);
   if (bw > 15 || 2 * bw + 1 >= nb) return;
   const bool mdf = B->scheme == kMDF, adapt = mdf && B->mdf_tol > 0;
   const int regs = ns == 4 ? kArcBandRegsP4 : kArcBandRegsHat;

@@ -67,6 +67,29 @@ def test_arcs_match_the_oracle(scheme, kernel, nb):
         ref.close()
 
 
+# marker spacings just below and above those at which one neighbour more shares
+# a support node (ns sqrt 2 / j), where the band half-width steps
+@pytest.mark.parametrize("side", [0.97, 1.03])
+@pytest.mark.parametrize("scheme", [ib.DF, ib.MDF, ib.DFC])
+@pytest.mark.parametrize("kernel,j", [(ib.HAT, 2), (ib.HAT, 3), (ib.PESKIN4, 5), (ib.PESKIN4, 6)])
+def test_band_width_at_its_steps(kernel, j, scheme, side):
+    nb = 180
+    D = nb * side * (2 if kernel == ib.HAT else 4) * 2 ** 0.5 / j / np.pi
+    n = int(D) + 40
+    print(f"band scheme={scheme} kernel={kernel} neighbours={j} side={side}", flush=True)
+    case = box(n + 30, n, [dict(xc=n / 2 + 0.37, yc=n / 2 - 0.21, diameter=D, n_markers=nb, scheme=scheme,
+                                kernel=kernel, mdf_iters=3)], FAR, u_bc=0.06)
+    sim, ref = ib.Sim(case), oracle.OracleSim(case)
+    ref.add_body(case["bodies"][0])
+    sim.step(6)
+    ref.step(6)
+    a, b = sim.forces(0), ref.body_state(0)
+    assert abs(a["fx"] - b["fx"]) < F64_DRAG * abs(b["fx"])
+    assert rel(sim.populations(), ref.populations()) < F64_FIELD
+    sim.close()
+    ref.close()
+
+
 def free(x, y, D, scheme, kernel, **kw):
     return dict(xc=x, yc=y, diameter=D, scheme=scheme, kernel=kernel, mdf_iters=3, motion=ib.FREE,
                 density_ratio=1.6, internal_mass=ib.IM_FENG, **kw)
