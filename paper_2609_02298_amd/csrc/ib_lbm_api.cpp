@@ -31,7 +31,7 @@ struct DevBuf {
 struct HostBody {
   ib_lbm_body_desc d;
   BodyDesc dev;  // host copy of the device description
-  DevBuf cos_t, sin_t, ws, tab, acc, markers, lambda, history, state, arc_part;
+  DevBuf cos_t, sin_t, ws, tab, acc, markers, lambda, history, state;
   // fused steps: the force copy and staged pushes (fixed DF/MDF bodies), and
   // the nodes the IB pass collides itself with their push map, built once
   // the device has built the body's tables
@@ -1360,8 +1360,9 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
   if ((st = dev_alloc(s, &hb.markers, (size_t)nb * 8 * 8))) return st;
   if ((st = dev_alloc(s, &hb.lambda, (size_t)nb * 8))) return st;
   if ((st = dev_alloc(s, &hb.history, (size_t)B.hist_cap * kHistCols * 8))) return st;
-  if ((st = dev_alloc(s, &hb.state, sizeof(BodyState)))) return st;
-  if ((st = dev_alloc(s, &hb.arc_part, (size_t)std::max(B.arc_n, 1) * 8 * 8))) return st;
+  // the state, and behind it the arcs' partial sums
+  const size_t state_bytes = (sizeof(BodyState) + 63) / 64 * 64;
+  if ((st = dev_alloc(s, &hb.state, state_bytes + (size_t)B.arc_n * 8 * 8))) return st;
   HIPCHK(s, hipMemcpy(hb.cos_t.p, ct.data(), nb * 8, hipMemcpyHostToDevice));
   HIPCHK(s, hipMemcpy(hb.sin_t.p, stb.data(), nb * 8, hipMemcpyHostToDevice));
   HIPCHK(s, hipMemset(hb.markers.p, 0, (size_t)nb * 64));
@@ -1375,14 +1376,14 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
   B.lambda_cache = (double *)hb.lambda.p;
   B.history = (double *)hb.history.p;
   B.state = (BodyState *)hb.state.p;
-  B.arc_part = (double *)hb.arc_part.p;
+  B.arc_part = (double *)((char *)hb.state.p + state_bytes);
   B.src = nullptr;
   B.n_src = 0;
   B.fprev = nullptr;
   B.pstage = nullptr;
-  if (b->motion == IB_LBM_FIXED && b->scheme != IB_LBM_DFC) {
-    // fused steps: the copy of the last force (zero, as the force field
-    // starts) and the staged pushes of the support nodes
+  if (b->motion == IB_LBM_FIXED && b->scheme != IB_LBM_DFC && B.arc_n == 0) {
+    // fused steps of a body that is not cut into arcs: the copy of the last force
+    // (zero, as the force field starts) and the staged pushes of the support nodes
     if ((st = dev_alloc(s, &hb.fprev, (size_t)B.max_nodes * 2 * B.pop_bytes))) return st;
     if ((st = dev_alloc(s, &hb.pstage, (size_t)B.max_nodes * 9 * B.pop_bytes))) return st;
     HIPCHK(s, hipMemset(hb.fprev.p, 0, (size_t)B.max_nodes * 2 * B.pop_bytes));
@@ -1763,7 +1764,6 @@ ib_lbm_status ib_lbm_destroy(ib_lbm_sim *s) {
   for (auto &hb : s->bodies) {
     dev_free(s, &hb.cos_t); dev_free(s, &hb.sin_t); dev_free(s, &hb.ws); dev_free(s, &hb.markers);
     dev_free(s, &hb.tab); dev_free(s, &hb.acc);
-    dev_free(s, &hb.arc_part);
     dev_free(s, &hb.lambda); dev_free(s, &hb.history); dev_free(s, &hb.state);
     dev_free(s, &hb.fprev); dev_free(s, &hb.pstage); dev_free(s, &hb.src);
   }
