@@ -5,11 +5,11 @@
 // m is thread m NS + h), each lane holding one row of NS nodes in registers:
 // it loads their populations, forms their moments and its row's part of the
 // interpolation, and DPP adds join the rows.  Markers whose stencils share a
-// node are at most `bw` apart along the circle (arc_band), so an arc works on
-// its own markers plus a margin on either side ("local" markers): bw for DF
-// and DFC, N bw for N marker-space MDF passes, whose results are exact on all
-// but bw more markers per pass.  Arcs therefore need nothing from each other
-// while they run; only the force sums meet (part / arrived), and DFC, which
+// node are at most `bw` apart along the circle (plan_arcs), so an arc works on
+// its own markers plus a margin on either side ("local" markers): bw for DF,
+// 2 bw for DFC, N bw for N marker-space MDF passes, whose results are exact on
+// all but bw more markers per pass.  Arcs therefore need nothing from each other
+// while they run; only the force sums meet (arc_part / arrived), and DFC, which
 // corrects the populations in place, once between its reads and its writes
 // (arc_sync).  A body of few markers is one arc that wraps around.
 //
@@ -18,9 +18,13 @@
 // the last, and the lane of the first marker writes the node.  Each support
 // node has exactly one such lane over all arcs.
 //
-// The pass is bound by latency, not bytes (a few hundred nodes per arc): the
-// tables this form does without took most of a moving body's pass (their
-// build: row intervals, scans, node lists), one workgroup per body the rest.
+// The pass is bound by latency and instruction issue, not bytes (a few hundred
+// nodes per arc): the tables this form does without took most of a moving
+// body's pass (their build: row intervals, scans, node lists), one workgroup per
+// body the rest.  Whole steps, one workgroup with tables and now: fixed 2000 x
+// 800 MDF P4 fp32 27.7 and 24.4 us, oscillating 1200 x 600 MDF P4 41 and 21.4,
+// settling 400 x 2000 DFC P4 fp64 55.5 and 23.6, settling 1281 x 3841 DF P4 (a
+// workspace in device memory before) 254 and 68.
 #pragma once
 #include "ib_lbm_internal.h"
 #include "ibm_device.h"
