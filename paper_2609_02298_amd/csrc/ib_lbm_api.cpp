@@ -2080,7 +2080,15 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
   }
   b->ib = lists.ib;
   OneShape sh;
-  b->one = !cases.empty();
+  // One launch per step saves a batch the launches per collision model and
+  // their gaps; its tiles, compiled with the passes, have fewer waves per SIMD
+  // than collide_stream_kernel's, which costs more the larger the batch.  us per
+  // step in one launch and in several: FP32 5.5 M nodes 109 and 167, 17.5 M 341
+  // and 366, 22 M 418 and 379, 131 M 2277 and 1923; FP64 5.5 M 181 and 248, 30 M
+  // 888 and 912, 47 M 1374 and 1362, 131 M 3782 and 3579.
+  int64_t nodes = 0;
+  for (auto *s : case_sims) nodes += (int64_t)s->cd.nx * s->cd.ny;
+  b->one = !cases.empty() && nodes <= (b->precision == IB_LBM_FP64 ? 40000000 : 20000000);
   b->one_face = 0;
   for (auto *s : case_sims) {
     b->one = b->one && sh.add(s->bodies, b->spread_mode);

@@ -203,3 +203,29 @@ def test_batch_steps_are_bitwise_the_steps_alone(graph, prec):
         assert s.steps_done == ref.steps_done, n
         assert np.array_equal(s.populations(), ref.populations()), n
         ref.close()
+
+
+# a batch's steps take one launch up to 20 M nodes (FP32) or 40 M (FP64), several
+# beyond: on both sides of the line the members are bitwise the sims alone
+@pytest.mark.parametrize("prec,ny", [(ib.FP32_SHIFTED, 2220), (ib.FP32_SHIFTED, 2225),
+                                     (ib.FP64, 4440), (ib.FP64, 4450)])
+def test_batch_steps_on_both_sides_of_the_size_line(prec, ny):
+    print(f"batch of 2 x 4500 x {ny}, precision {prec}", flush=True)
+    bodies = [dict(xc=900.3, yc=ny / 2 + 0.4, diameter=60.0, scheme=ib.DFC, kernel=ib.HAT)]
+    members = [box(4500, ny, bodies, FAR, ib.CMMRT, u_bc=0.05), box(4500, ny, [], FAR, ib.BGK, u_bc=0.05)]
+    batch = ib.Batch(prec)
+    sims = [ib.Sim(m, precision=prec) for m in members]
+    for s in sims:
+        batch.attach(s)
+    batch.step(5)
+    batch.sync()
+    for s, m in zip(sims, members):
+        alone = ib.Sim(m, precision=prec)
+        alone.step(5)
+        assert all(np.array_equal(a, b) for a, b in zip(s.fields(), alone.fields()))
+        if m["bodies"]:
+            assert s.forces(0)["fx"] == alone.forces(0)["fx"]
+        alone.close()
+    batch.close()
+    for s in sims:
+        s.close()
