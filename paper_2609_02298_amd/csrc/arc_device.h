@@ -32,6 +32,12 @@
 
 namespace iblbm {
 
+// A body's description as the passes read it: no kernel writes it, so it goes
+// through the scalar data cache into scalar registers.  As ordinary memory it
+// had to be loaded again, lane by lane, after every store that might have
+// changed it: a round trip each on the pass's chain, or registers to keep it.
+using ConstBody = const __attribute__((address_space(4))) BodyDesc;
+
 // Kinematics of a body over one step.
 struct Kin {
   double xc, yc, vhx, vhy, omh;  // position and (half-step) velocity of the step
@@ -43,7 +49,8 @@ struct Kin {
 // Fixed, prescribed sine, the half-kick and drift of the Velocity-Verlet
 // update (Eq. 23 / A3) or the Euler-explicit update (Eq. A1), from the state
 // bs of the last completed step, for the step from time level `step`.
-__device__ __forceinline__ Kin body_kinematics(const CaseDesc &c, const BodyDesc &B,
+template <typename BODY>
+__device__ __forceinline__ Kin body_kinematics(const CaseDesc &c, BODY &B,
                                                const BodyState *bs, int64_t step) {
   Kin k;
   k.xc = bs->xc;
@@ -278,8 +285,8 @@ __device__ __forceinline__ bool count_wait(const int32_t *cnt, int n) {
 // counted themselves in hold_done; OPEN: the lattice's Zou-He wall nodes are
 // still open then; par: the launch's parity in a batch, or -1.
 enum { kArcDF = 0, kArcMDF = 1, kArcDFC = 2 };
-template <typename T, int NS, int KIND, int RPL, bool OPEN, int BU>
-__device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, int64_t step, int cur,
+template <typename T, int NS, int KIND, int RPL, bool OPEN, int BU, typename BODY>
+__device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t step, int cur,
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
   constexpr int LPM = NS / RPL;
@@ -948,23 +955,25 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, const BodyDesc &B, i
 // The pass of one arc (see arc_pass).  SET: the schemes the instance holds, 0
 // all, 1 DF and MDF, 2 DFC.
 template <typename T, int SET, bool OPEN>
-__device__ __forceinline__ void arc_body(const CaseDesc &c, const BodyDesc &B, int64_t step, int cur,
+__device__ __forceinline__ void arc_body(const CaseDesc &c, const BodyDesc *body_desc, int64_t step, int cur,
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
-#define IBL_PASS(NSV, KINDV, RPLV) \
-  arc_pass<T, NSV, KINDV, RPLV, OPEN, (SET == 1 ? 4 : 2)>(c, B, step, cur, arc, body, nslots, wait_for, par, dyn, sh)
-  if (SET == 2 || (SET == 0 && B.scheme == kDFC)) {
+#define IBL_PASS(BODY, NSV, KINDV, RPLV)                                                           \
+  arc_pass<T, NSV, KINDV, RPLV, OPEN, (SET == 1 ? 4 : 2)>(c, *(BODY *)body_desc, step, cur, arc, body, \
+                                                          nslots, wait_for, par, dyn, sh)
+  if (SET == 2 || (SET == 0 && body_desc->scheme == kDFC)) {
     if constexpr (SET != 1) {
-      if (B.ns == 2) IBL_PASS(2, kArcDFC, 1);
-      else IBL_PASS(4, kArcDFC, 1);
+      if (body_desc->ns == 2) IBL_PASS(const BodyDesc, 2, kArcDFC, 1);
+      else IBL_PASS(const BodyDesc, 4, kArcDFC, 1);
     }
   } else if constexpr (SET != 2) {
+    ConstBody &B = *(ConstBody *)body_desc;
     if (B.scheme == kMDF) {
-      if (B.ns == 2) IBL_PASS(2, kArcMDF, 1);
-      else IBL_PASS(4, kArcMDF, 1);
+      if (B.ns == 2) IBL_PASS(ConstBody, 2, kArcMDF, 1);
+      else IBL_PASS(ConstBody, 4, kArcMDF, 1);
     } else {
-      if (B.ns == 2) IBL_PASS(2, kArcDF, 1);
-      else IBL_PASS(4, kArcDF, 1);
+      if (B.ns == 2) IBL_PASS(ConstBody, 2, kArcDF, 1);
+      else IBL_PASS(ConstBody, 4, kArcDF, 1);
     }
   }
 #undef IBL_PASS

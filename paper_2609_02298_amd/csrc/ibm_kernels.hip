@@ -1527,7 +1527,7 @@ __global__ __launch_bounds__(MAXT) void ibm_arc_kernel(const CaseDesc *__restric
   const int64_t step = cs->step;
   const int cur = cs->cur;
   if (step >= cs->target || (cs->flags & kCaseHalted)) return;
-  arc_body<T, (MAXT > 512 ? 1 : 0), false>(c, c.bodies[sl.body], step, cur, sl.arc, sl.body,
+  arc_body<T, (MAXT > 512 ? 1 : 0), false>(c, c.bodies + sl.body, step, cur, sl.arc, sl.body,
                                            sl.slots_in_case, -1, -1, dyn, sh);
 }
 

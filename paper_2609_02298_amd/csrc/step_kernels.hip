@@ -272,7 +272,7 @@ __global__ __launch_bounds__(DFC ? 512 : 1024) void step_one_kernel(const StepOn
       }
       return;
     }
-    arc_body<T, (DFC ? 2 : 1), FACE == kFaceZou>(a.cd, a.cd.bodies[body], step, a.cur,
+    arc_body<T, (DFC ? 2 : 1), FACE == kFaceZou>(a.cd, a.cd.bodies + body, step, a.cur,
                                                  b - a.arc_first[body], body, a.cd.nbodies,
                                                  hold_target(s, body), -1, dyn, sh);
     return;
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(1024) void step_batch_kernel(const StepBatchArgs g)
     return;
   }
   if (sl.cas >= 0) {
-    arc_body<T, 0, false>(a.cd, a.cd.bodies[sl.body], cs->step, s.cur, sl.arc, sl.body, sl.slots_in_case,
+    arc_body<T, 0, false>(a.cd, a.cd.bodies + sl.body, cs->step, s.cur, sl.arc, sl.body, sl.slots_in_case,
                           hold_target(s, sl.body), g.par, dyn, sh);
     return;
   }
