@@ -205,6 +205,25 @@ def test_batch_steps_are_bitwise_the_steps_alone(graph, prec):
         ref.close()
 
 
+# FP64 Peskin rows are loaded by columns: a body on a seam of the lattice's
+# storage (64 columns), at each offset of a stencil from it
+@pytest.mark.parametrize("scheme", [ib.DF, ib.MDF])
+@pytest.mark.parametrize("xc", [63.1, 64.2, 65.3, 66.4])
+def test_columns_across_a_storage_seam_match_the_oracle(scheme, xc):
+    print(f"seam scheme={scheme} xc={xc}", flush=True)
+    case = box(140, 60, [dict(xc=xc, yc=30.3, diameter=9.0, scheme=scheme, kernel=ib.PESKIN4, mdf_iters=5)],
+               FAR, u_bc=0.05)
+    sim, ref = ib.Sim(case), oracle.OracleSim(case)
+    ref.add_body(case["bodies"][0])
+    sim.step(9)
+    ref.step(9)
+    a, b = sim.forces(0), ref.body_state(0)
+    assert abs(a["fx"] - b["fx"]) < F64_DRAG * abs(b["fx"])
+    assert rel(sim.populations(), ref.populations()) < F64_FIELD
+    sim.close()
+    ref.close()
+
+
 # a batch's steps take one launch up to 20 M nodes (FP32) or 40 M (FP64), several
 # beyond: on both sides of the line the members are bitwise the sims alone
 @pytest.mark.parametrize("prec,ny", [(ib.FP32_SHIFTED, 2220), (ib.FP32_SHIFTED, 2225),
