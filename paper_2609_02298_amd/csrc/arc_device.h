@@ -22,9 +22,9 @@
 // nodes per arc): the tables this form does without took most of a moving
 // body's pass (their build: row intervals, scans, node lists), one workgroup per
 // body the rest.  Whole steps, one workgroup with tables and now: fixed 2000 x
-// 800 MDF P4 fp32 27.7 and 24.4 us, oscillating 1200 x 600 MDF P4 41 and 21.4,
+// 800 MDF P4 fp32 27.7 and 23.0 us, oscillating 1200 x 600 MDF P4 41 and 20.5,
 // settling 400 x 2000 DFC P4 fp64 55.5 and 23.6, settling 1281 x 3841 DF P4 (a
-// workspace in device memory before) 254 and 68.
+// workspace in device memory before) 254 and 67.
 #pragma once
 #include "ib_lbm_internal.h"
 #include "ibm_device.h"

@@ -308,7 +308,7 @@ __global__ __launch_bounds__(DFC ? 512 : 1024) void step_one_kernel(const StepOn
 // (work entry, case, populations), which 16 waves per CU hide only in part.
 // 12 cases (3.6 M nodes, all schemes and collisions, fp32): 130 us per step as
 // one collide-stream and one face launch per collision model and two launches
-// of the passes, 68 us so.
+// of the passes, 64 to 69 us so.  Large batches: see batch_tables.
 template <typename T, int FACE>
 __global__ __launch_bounds__(1024) void step_batch_kernel(const StepBatchArgs g) {
   extern __shared__ double dyn[];
