@@ -831,8 +831,9 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
               const int j = j0 + u;
               gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(ix0 + j, y0 + r, nseg);
               const bool first = (mine[r] & (1u << j)) != 0;
-              if (first && c.wall_closed && is_zou_he_wall(c, ix0 + j, y0 + r))
-                c.wall_closed[wall_index(nx, ny, ix0 + j, y0 + r)] = 1;
+              if constexpr (OPEN)
+                if (first && is_zou_he_wall(c, ix0 + j, y0 + r))
+                  *wall_flag(c, cur ^ 1, wall_index(nx, ny, ix0 + j, y0 + r)) = 1;
               T q[9];
 #pragma unroll
               for (int i = 0; i < 9; i++) {

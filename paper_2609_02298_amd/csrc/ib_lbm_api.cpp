@@ -1017,7 +1017,6 @@ ib_lbm_status enqueue_one(ib_lbm_sim *s, int64_t nsteps, hipStream_t stream, int
     a.lean.src = s->cd.f[cur];
     a.lean.dst = s->cd.f[cur ^ 1];
     a.lean.halt = &s->cd.state->halt[cur];
-    a.zh_fold = i > 0;
     HIPCHK(s, launch_step_one(s->cd.precision, s->one_face, !s->bodies.empty() && s->bodies[0].dev.scheme == kDFC,
                               a, s->one_threads, s->one_lds, stream));
   }
@@ -1071,7 +1070,7 @@ size_t ib_lbm_footprint(const ib_lbm_config *cfg, int32_t n_bodies, const int32_
   for (int f = 0; f < 4; f++) has_zou |= cfg->bc[f] == IB_LBM_ZOU_HE;
   const size_t lat = cfg->nx > 0 && cfg->ny > 0 ? (size_t)pop_values(cfg->nx, cfg->ny) : 0;
   size_t bytes = 2 * lat * elem + 2 * n * elem + sizeof(CaseState) + sizeof(CaseDesc) + 256 +
-                 (has_zou ? (size_t)wall_nodes(cfg->nx, cfg->ny) : 0);
+                 (has_zou ? 2 * (size_t)wall_nodes(cfg->nx, cfg->ny) : 0);
   const int hist = cfg->history_capacity > 0 ? cfg->history_capacity : 4096;
   for (int b = 0; b < n_bodies; b++) {
     const int nb = n_markers ? n_markers[b] : 256;
@@ -1167,9 +1166,10 @@ ib_lbm_status ib_lbm_create(const ib_lbm_config *cfg, ib_lbm_sim **out) {
   if ((st = dev_alloc(s, &s->force, 2 * (size_t)c.plane * elem))) return fail(st, s->err.c_str());
   if ((st = dev_alloc(s, &s->state, sizeof(CaseState)))) return fail(st, s->err.c_str());
   if (has_zou_he(c)) {
-    const size_t nw = (size_t)wall_nodes(c.nx, c.ny);
+    // (what a caller sets is used as it is, so it counts as closed)
+    const size_t nw = 2 * (size_t)wall_nodes(c.nx, c.ny);
     if ((st = dev_alloc(s, &s->wall_closed, nw))) return fail(st, s->err.c_str());
-    if (hipMemset(s->wall_closed.p, 0, nw) != hipSuccess) return fail(IB_LBM_E_DEVICE, "wall flags");
+    if (hipMemset(s->wall_closed.p, 1, nw) != hipSuccess) return fail(IB_LBM_E_DEVICE, "wall flags");
     c.wall_closed = (uint8_t *)s->wall_closed.p;
   }
   c.f[0] = s->f0.p;

@@ -198,8 +198,11 @@ struct CaseDesc {
   void *force;          // IB force density, 2 planes
   CaseState *state;
   BodyDesc *bodies;     // device array of nbodies
-  // Zou-He walls, one-launch steps: per perimeter node (wall_index), 1 while
-  // it holds closed populations that DFC has corrected since
+  // Zou-He walls: per lattice and perimeter node (wall_flag), 1 where its
+  // populations are closed.  A one-launch step leaves the wall nodes of the
+  // lattice it writes open, except those that DFC closes and corrects, and
+  // closes what it reads; it only reads the flags of its input lattice, which
+  // stays the current one if the step fails.
   uint8_t *wall_closed;
 };
 
@@ -427,7 +430,6 @@ struct StepOneArgs {
   CaseDesc cd;
   const CaseDesc *c;  // the same in device memory
   int32_t cur, nface, bx, by, tx_shift, ty_shift;  // shifts: log2 of a tile's nodes along x and y
-  int32_t zh_fold;  // Zou-He walls: the input lattice's wall nodes are still open
   int32_t narcs, nhold;
   int32_t arc_first[kMaxBodiesPerCase + 1], hold_first[kMaxBodiesPerCase + 1];  // prefix sums over bodies
 };

@@ -475,6 +475,11 @@ __device__ __forceinline__ bool is_zou_he_wall(const CaseDesc &c, int x, int y) 
          (y == 0 && c.bc[kFaceS] == kZouHe) || (y == c.ny - 1 && c.bc[kFaceN] == kZouHe);
 }
 
+// Whether wall node m (wall_index) of lattice lat is closed (CaseDesc::wall_closed).
+__device__ __forceinline__ uint8_t *wall_flag(const CaseDesc &c, int lat, int m) {
+  return c.wall_closed + (lat ? wall_nodes(c.nx, c.ny) : 0) + m;
+}
+
 template <typename T>
 __device__ __forceinline__ void zou_he_close(const CaseDesc &c, const T *f, int x, int y, T (&v)[9]) {
   #pragma clang fp contract(off)

@@ -109,8 +109,8 @@ __global__ __launch_bounds__(kFaceBlock) void collide_stream_face_kernel(const C
 
 // The Zou-He wall nodes of a case (zou_he_close), one thread per perimeter
 // node.  cur_arg >= 0: of the lattice a step with that input lattice writes;
-// -1: the same from the case state; -2 (after one-launch steps): of the
-// current lattice, but not the nodes the pass has closed and corrected.
+// -1: the same from the case state; -2 (after one-launch steps): those of the
+// current lattice that are still open.  They are marked closed.
 template <typename T>
 __global__ __launch_bounds__(256) void zou_he_kernel(const CaseDesc *__restrict__ cp, int cur_arg) {
   const CaseDesc &c = *cp;
@@ -128,11 +128,10 @@ __global__ __launch_bounds__(256) void zou_he_kernel(const CaseDesc *__restrict_
     y = 1 + q % (ny - 2);
   }
   if (!is_zou_he_wall(c, x, y)) return;
-  if (cur_arg != -2 && c.wall_closed) c.wall_closed[m] = 0;
   int out;
   if (cur_arg == -2) {
-    if (c.wall_closed[m]) return;
     out = cs->cur;
+    if (*wall_flag(c, out, m)) return;
   } else if (cur_arg < 0) {
     if (cs->step >= cs->target || (cs->flags & kCaseHalted)) return;
     out = cs->cur ^ 1;
@@ -140,6 +139,7 @@ __global__ __launch_bounds__(256) void zou_he_kernel(const CaseDesc *__restrict_
     if (__hip_atomic_load(&cs->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kCaseHalted) return;
     out = cur_arg ^ 1;
   }
+  *wall_flag(c, out, m) = 1;
   T *__restrict__ f = (T *)c.f[out] + pop_node(x, y, c.nseg);
   T v[9];
 #pragma unroll

@@ -213,9 +213,9 @@ __device__ __forceinline__ void step_face_node(const StepCase &s, int m) {
   for (int i = 0; i < 9; i++) f[i] = src[pn + i * kSeg];
   if constexpr (FACE == kFaceZou) {
     if (is_zou_he_wall(c, x, y)) {
-      uint8_t *const w = c.wall_closed + wall_index(nx, ny, x, y);
-      if (*w) *w = 0;
-      else if (s.a.zh_fold) zou_he_close<T>(c, src, x, y, f);
+      const int w = wall_index(nx, ny, x, y);
+      if (!*wall_flag(c, s.cur, w)) zou_he_close<T>(c, src, x, y, f);
+      *wall_flag(c, s.cur ^ 1, w) = 0;
     }
   }
   T Fx = T(c.fluid_fx), Fy = T(c.fluid_fy);

@@ -8,6 +8,7 @@ import pytest
 import ib_cases
 import oracle
 import paper_2609_02298_amd as ib
+from paper_2609_02298_amd import ib_lbm
 
 pytestmark = pytest.mark.gpu
 
@@ -155,6 +156,62 @@ def test_one_launch_steps_are_bitwise_the_plain_steps(name, prec):
             assert np.array_equal(p0, p1)
             assert np.array_equal(f0[0], f1[0]) and np.array_equal(f0[1], f1[1])
             assert s0 == s1
+
+
+def plain_and_one_launch(case, prec, calls):
+    """What plain steps, one-launch steps and replayed one-launch steps leave
+    after each call."""
+    pops = ib_cases.random_populations(case["nx"], case["ny"], 5, amp=0.004, u=(0.01, 0.005))
+    runs = []
+    for over, graph in ((False, 0), (True, 0), (True, 6)):
+        sim = ib.Sim(case, precision=prec)
+        sim.set_overlap(over)
+        sim.set_populations(pops)
+        sim.set_graph(graph)
+        seen = []
+        for k in calls:
+            sim.step(k)
+            st = [sim.forces(b, check=False) for b in range(len(case["bodies"]))]
+            seen.append((sim.steps_done, sim.populations(), sim.force(), st))
+        runs.append(seen)
+        sim.close()
+    return runs
+
+
+def assert_same(runs):
+    for seen in runs[1:]:
+        for (n0, p0, f0, s0), (n1, p1, f1, s1) in zip(runs[0], seen):
+            assert n0 == n1 and np.isfinite(p0).all()
+            assert np.array_equal(p0, p1)
+            assert np.array_equal(f0[0], f1[0]) and np.array_equal(f0[1], f1[1])
+            assert s0 == s1
+
+
+# DFC bodies that correct nodes of a Zou-He wall until the case halts: the
+# support leaves the lattice, or the body becomes too fast ("slide").  The step
+# that fails is not completed, and the lattice it started from is read back.
+# One arc and several; on a wall and in a corner
+HALTS = {
+    "fall-P4": (14.0, ib.PESKIN4, (30.2, 8.4), (0.0, -8e-3), "E_RANGE"),
+    "fall-hat": (14.0, ib.HAT, (30.2, 7.5), (0.0, -8e-3), "E_RANGE"),
+    "fall-P4-arcs": (26.0, ib.PESKIN4, (30.2, 14.4), (0.0, -8e-3), "E_RANGE"),
+    "corner-P4-arcs": (26.0, ib.PESKIN4, (44.6, 14.4), (6e-3, -6e-3), "E_RANGE"),
+    "slide-P4": (14.0, ib.PESKIN4, (22.2, 8.4), (0.3, 0.0), "E_DIVERGED"),
+    "slide-hat-arcs": (42.0, ib.HAT, (24.2, 21.5), (0.3, 0.0), "E_DIVERGED"),
+}
+
+
+@pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
+@pytest.mark.parametrize("name", list(HALTS))
+def test_a_case_halted_at_a_wall_is_left_as_plain_steps_leave_it(name, prec):
+    D, kernel, (x, y), g, status = HALTS[name]
+    print(f"halt at a wall {name} prec={prec}", flush=True)
+    case = box(60, 60, [free(x, y, D, ib.DFC, kernel)], ZOU, ib.CMMRT, gravity=g)
+    runs = plain_and_one_launch(case, prec, (1, 120, 7))
+    assert_same(runs)
+    done, _, _, (body,) = runs[0][-1]
+    print(name, done, body["status"], flush=True)
+    assert 1 < done < 121 and ib_lbm.STATUS[body["status"]] == status
 
 
 def test_one_launch_steps_after_atomic_spreading():
