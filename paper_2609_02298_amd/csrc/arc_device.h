@@ -253,6 +253,7 @@ struct ArcShared {
   Kin kin, next;  // this step's, and of a driven body the next step's
   int flags;
   int box[4], hold[4];  // force box; hold rectangle of the next step (not of a free body)
+  int corner;           // the force box reaches a corner node's diagonal neighbour
   int64_t hist;         // offset of the step's history row
 };
 
@@ -388,6 +389,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       const bool driven = motion == kPrescribedSin;
       arc_hold(xc, yc, driven ? sh.next.xc : xc, driven ? sh.next.yc : yc, r, s1, nx, ny, sh.hold);
     }
+    if (OPEN)
+      sh.corner = (sh.box[0] <= 1 || sh.box[2] >= nx - 2) && (sh.box[1] <= 1 || sh.box[3] >= ny - 2);
     sh.hist = (step % B.hist_cap) * kHistCols;
   }
   // The geometry of the step, all of it before the wait of a one-launch step:
@@ -799,6 +802,35 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         }
         __syncthreads();
         met = !(sh.flags & kFlagExchange);
+      }
+      if constexpr (OPEN) {
+        // A corner of two walls is closed from the node diagonally inside it
+        // as streaming left that node: whoever is about to correct the node
+        // closes the corner, unless the body's support holds it (and closed it
+        // as it was read).  Only a body near a corner looks for such nodes.
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(sh.corner), 0) && owned && met)
+#pragma unroll 1
+          for (int r = 0; r < RPL; r++)
+            for (int j = 0; j < NS; j++)
+              if (mine[r] & (1u << j)) {
+                const int x = ix0 + j, y = y0 + r;
+                int cx, cy;
+                if (!inside_corner(c, x, y, cx, cy)) continue;
+                bool held = false;
+                for_cover(cov[r], y, [&](int i, const double *, double) {
+                  const int p = lpos[m + i];
+                  held |= (unsigned)(cx - (p & 0xffff)) < (unsigned)NS && (unsigned)(cy - (p >> 16)) < (unsigned)NS;
+                });
+                if (held) continue;
+                gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(cx, cy, nseg);
+                T q[9];
+#pragma unroll
+                for (int i = 0; i < 9; i++) q[i] = fw[i * kSeg];
+                zou_he_close<T>(c, fpop, cx, cy, q);
+#pragma unroll
+                for (int i = 1; i < 9; i++) fw[i * kSeg] = q[i];
+                *wall_flag(c, cur ^ 1, wall_index(nx, ny, cx, cy)) = 1;
+              }
       }
       if (owned && met) {
         // Eq. (19) on every node of the lane's rows; the first marker's lane

@@ -475,6 +475,14 @@ __device__ __forceinline__ bool is_zou_he_wall(const CaseDesc &c, int x, int y) 
          (y == 0 && c.bc[kFaceS] == kZouHe) || (y == c.ny - 1 && c.bc[kFaceN] == kZouHe);
 }
 
+// Whether node (x, y) lies diagonally inside a corner (cx, cy) of two such walls.
+__device__ __forceinline__ bool inside_corner(const CaseDesc &c, int x, int y, int &cx, int &cy) {
+  if ((x != 1 && x != c.nx - 2) || (y != 1 && y != c.ny - 2)) return false;
+  cx = x == 1 ? 0 : c.nx - 1;
+  cy = y == 1 ? 0 : c.ny - 1;
+  return c.bc[x == 1 ? kFaceW : kFaceE] == kZouHe && c.bc[y == 1 ? kFaceS : kFaceN] == kZouHe;
+}
+
 // Whether wall node m (wall_index) of lattice lat is closed (CaseDesc::wall_closed).
 __device__ __forceinline__ uint8_t *wall_flag(const CaseDesc &c, int lat, int m) {
   return c.wall_closed + (lat ? wall_nodes(c.nx, c.ny) : 0) + m;

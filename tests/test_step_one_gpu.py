@@ -214,6 +214,22 @@ def test_a_case_halted_at_a_wall_is_left_as_plain_steps_leave_it(name, prec):
     assert 1 < done < 121 and ib_lbm.STATUS[body["status"]] == status
 
 
+# a small disk in a corner of two Zou-He walls: its support holds the node
+# diagonally inside the corner, which closes the corner, but not the corner
+@pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
+@pytest.mark.parametrize("kernel", [ib.HAT, ib.PESKIN4])
+@pytest.mark.parametrize("east", [False, True])
+@pytest.mark.parametrize("north", [False, True])
+def test_a_corner_is_closed_before_its_inner_node_is_corrected(north, east, kernel, prec):
+    print(f"corner north={north} east={east} kernel={kernel} prec={prec}", flush=True)
+    nx, ny, R = 44, 40, 4.0
+    low, high = (1.05, 2.05) if kernel == ib.PESKIN4 else (0.05, 1.05)
+    x = nx - high - R if east else low + R
+    y = ny - high - R if north else low + R
+    body = dict(xc=x, yc=y, diameter=2 * R, scheme=ib.DFC, kernel=kernel)
+    assert_same(plain_and_one_launch(box(nx, ny, [body], ZOU, ib.TRT), prec, (1, 2, 13, 24)))
+
+
 def test_one_launch_steps_after_atomic_spreading():
     """A sim that changes to the atomic scatter and back: the hold rectangles
     of the steps in between are not kept, so the first step after is plain."""
