@@ -2018,6 +2018,9 @@ ib_lbm_status ib_lbm_batch_set_target(ib_lbm_batch *b, ib_lbm_sim *s, int64_t ta
 
 static ib_lbm_status batch_tables(ib_lbm_batch *b) {
   if (!b->dirty) return IB_LBM_OK;
+  // steps still queued read the tables (and replay the graph) rewritten here:
+  // uploads are not ordered after the work of a non-blocking stream
+  BHIPCHK(b, hipStreamSynchronize(b->stream));
   if (b->graph_exec) {
     (void)hipGraphExecDestroy(b->graph_exec);
     b->graph_exec = nullptr;

@@ -278,6 +278,44 @@ def test_batch_steps_are_bitwise_the_steps_alone(graph, prec):
         ref.close()
 
 
+@pytest.mark.parametrize("graph", [0, 8])
+def test_a_batch_changes_behind_queued_steps(graph):
+    """Members that join, and a change of the spreading variant, while earlier
+    steps are still queued on a stream that the uploads do not wait for."""
+    import torch
+    print(f"batch changes behind queued steps graph={graph}", flush=True)
+    names = ["fast-MDF", "seam-DF", "empty-open", "driven-DFC"]
+    stream = torch.cuda.Stream().cuda_stream
+    batch = ib.Batch(ib.FP64, stream=stream)
+    sims = [ib.Sim(CASES[n], precision=ib.FP64, stream=stream) for n in names]
+    batch.set_graph(graph)
+    done = [0] * len(sims)
+    for i, s in enumerate(sims):
+        batch.attach(s)
+        batch.step(97)
+        for j in range(i + 1):
+            done[j] += 97
+    batch.set_spread(ib.SPREAD_ATOMIC)
+    batch.step(3)
+    batch.set_spread(ib.SPREAD_GATHER)
+    batch.step(41)
+    batch.sync()
+    for n, s, k in zip(names, sims, done):
+        ref = ib.Sim(CASES[n], precision=ib.FP64)
+        ref.step(k)
+        ref.set_spread(ib.SPREAD_ATOMIC)
+        ref.step(3)
+        ref.set_spread(ib.SPREAD_GATHER)
+        ref.step(41)
+        assert s.steps_done == ref.steps_done == k + 44, n
+        # (the order of the atomic sums is open)
+        assert rel(s.populations(), ref.populations()) < F64_FIELD, n
+        ref.close()
+    batch.close()
+    for s in sims:
+        s.close()
+
+
 # FP64 Peskin rows are loaded by columns: a body on a seam of the lattice's
 # storage (64 columns), at each offset of a stencil from it
 @pytest.mark.parametrize("scheme", [ib.DF, ib.MDF])
