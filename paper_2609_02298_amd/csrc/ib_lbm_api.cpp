@@ -620,6 +620,8 @@ hipError_t launch_ibm_slots(int precision, const CaseDesc *cases, const IbmSlot 
 
 ib_lbm_status build_sim_tables(ib_lbm_sim *s) {
   if (!s->tables_dirty) return IB_LBM_OK;
+  // steps still queued read the tables (and replay the graphs) rewritten here
+  HIPCHK(s, hipStreamSynchronize(s->stream));
   ib_lbm_status st0;
   std::vector<BodyDesc> bd;
   for (auto &hb : s->bodies) bd.push_back(hb.dev);

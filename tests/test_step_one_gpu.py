@@ -316,6 +316,24 @@ def test_a_batch_changes_behind_queued_steps(graph):
         s.close()
 
 
+def test_a_sim_changes_behind_queued_steps():
+    import torch
+    print("sim changes behind queued steps", flush=True)
+    out = []
+    for queued in (False, True):
+        sim = ib.Sim(CASES["fast-MDF"], stream=torch.cuda.Stream().cuda_stream)
+        for shape, spread in ((64, 0), (256, 1), (128, 0), (512, 1), (64, 0)):
+            sim.step(60)
+            if not queued:
+                sim.sync()
+            sim.set_launch(block_x=shape, block_y=1)
+            sim.set_spread(spread)
+            sim.step(5)
+        out.append(sim.populations())
+        sim.close()
+    assert rel(out[1], out[0]) < F64_FIELD
+
+
 # FP64 Peskin rows are loaded by columns: a body on a seam of the lattice's
 # storage (64 columns), at each offset of a stencil from it
 @pytest.mark.parametrize("scheme", [ib.DF, ib.MDF])
