@@ -75,6 +75,10 @@ enum { IB_LBM_VERLET = 0, IB_LBM_EULER_A1 = 1 };
 /* desired marker velocity of a body (ib_lbm_body_desc.udes) */
 enum { IB_LBM_UD_RIGID = 0, IB_LBM_UD_TAYLOR_GREEN = 1 };
 enum { IB_LBM_SPREAD_GATHER = 0, IB_LBM_SPREAD_ATOMIC = 1 };
+/* How steps are launched (ib_lbm_get_step_form): several launches on one
+ * stream; pipelined on two; one launch with the IB pass in workgroup 0; one
+ * launch with the IB pass in arcs, or without bodies. */
+enum { IB_LBM_STEP_PLAIN = 0, IB_LBM_STEP_PIPELINED = 1, IB_LBM_STEP_FUSED = 2, IB_LBM_STEP_ONE = 3 };
 
 /* Body flags reported in ib_lbm_body_state.flags */
 enum { IB_LBM_FLAG_NONFINITE = 1, IB_LBM_FLAG_RANGE = 2, IB_LBM_FLAG_OVERLAP = 4,
@@ -372,9 +376,12 @@ ib_lbm_status ib_lbm_get_overlap(const ib_lbm_sim *s, int32_t *in_use, int64_t *
  * (ib_lbm_timing_enable) runs pipelined steps.  set_fused(0/1) forbids or
  * allows it; get_fused reports (after the first step) whether a pipelined
  * sim with a fixed DF or MDF body, BGK or TRT and no Zou-He wall uses it, 0
- * for every other sim. */
+ * for every other sim, also those that step in one launch.  get_step_form
+ * reports for any sim how the last step enqueued was launched
+ * (IB_LBM_STEP_*; -1: none yet). */
 ib_lbm_status ib_lbm_set_fused(ib_lbm_sim *s, int32_t on);
 ib_lbm_status ib_lbm_get_fused(const ib_lbm_sim *s, int32_t *in_use);
+ib_lbm_status ib_lbm_get_step_form(const ib_lbm_sim *s, int32_t *form);
 
 /* Kernel timing with HIP events (direct launches only).  which: 0
  * collide-stream, 1 immersed boundary.  With pipelined steps a collide-stream
@@ -421,6 +428,9 @@ ib_lbm_status ib_lbm_batch_set_graph(ib_lbm_batch *b, int32_t steps_per_graph);
  * one-launch steps have a tile shape of their own). */
 ib_lbm_status ib_lbm_batch_set_launch(ib_lbm_batch *b, const ib_lbm_launch *l);
 ib_lbm_status ib_lbm_batch_set_spread(ib_lbm_batch *b, int32_t mode);
+/* How the batch's last step was launched: IB_LBM_STEP_PLAIN or
+ * IB_LBM_STEP_ONE (-1: none yet). */
+ib_lbm_status ib_lbm_batch_get_step_form(const ib_lbm_batch *b, int32_t *form);
 ib_lbm_status ib_lbm_batch_sync(ib_lbm_batch *b);
 ib_lbm_status ib_lbm_batch_destroy(ib_lbm_batch *b);
 const char *ib_lbm_batch_last_error(const ib_lbm_batch *b);

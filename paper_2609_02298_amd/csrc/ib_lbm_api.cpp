@@ -117,6 +117,9 @@ struct ib_lbm_sim {
   bool one = false;
   bool hold_ready = false;
   bool halted = false;  // the case was halted when its state was last read
+  // how the last step enqueued was launched (IB_LBM_STEP_*), and the steps of
+  // the captured graphs
+  int form = -1, graph_form = -1;
   StepOneArgs one_args;
   int one_threads = 0, one_lds = 0, one_face = 0;
   uint32_t fused_seq = 0;  // sequence number of the last fused launch (CaseState::gate)
@@ -143,6 +146,7 @@ struct ib_lbm_batch {
   bool one = false;
   DevBuf d_one, d_one_prefix, d_work;
   StepBatchArgs one_args{};
+  int form = -1;  // how the last step was launched (IB_LBM_STEP_*)
   int one_threads = 0, one_lds = 0, one_face = 0;
   int graph_steps = 0;
   hipGraphExec_t graph_exec = nullptr;
@@ -1031,11 +1035,17 @@ ib_lbm_status enqueue_one(ib_lbm_sim *s, int64_t nsteps, hipStream_t stream, int
 // pipelined when the sim allows it and `pipelined` is set.
 ib_lbm_status enqueue_steps(ib_lbm_sim *s, int64_t nsteps, bool timed, hipStream_t stream, int cur0,
                             bool pipelined) {
-  if (s->one && s->hold_ready && !timed) return enqueue_one(s, nsteps, stream, cur0);
+  const bool one = s->one && s->hold_ready && !timed;
+  const bool fused = s->fused && !s->one && s->bodies[0].src_ready && !timed;
+  if (nsteps > 0)
+    s->form = one ? IB_LBM_STEP_ONE
+                  : (fused ? IB_LBM_STEP_FUSED
+                           : (s->split && pipelined ? IB_LBM_STEP_PIPELINED : IB_LBM_STEP_PLAIN));
+  if (one) return enqueue_one(s, nsteps, stream, cur0);
   bool arcs = true;
   for (auto &hb : s->bodies) arcs &= body_arcs(hb, s->spread_mode);
   s->hold_ready = nsteps > 0 ? arcs : s->hold_ready;
-  if (s->fused && !s->one && s->bodies[0].src_ready && !timed) return enqueue_fused(s, nsteps, stream, cur0);
+  if (fused) return enqueue_fused(s, nsteps, stream, cur0);
   if (s->split && pipelined) return enqueue_pipelined(s, nsteps, timed, stream, cur0);
   for (int64_t i = 0; i < nsteps; i++) {
     ib_lbm_status st = enqueue_sim_step(s, timed, stream, cur0 ^ (int)(i & 1));
@@ -1455,6 +1465,7 @@ ib_lbm_status ib_lbm_step(ib_lbm_sim *s, int64_t nsteps) {
       for (int p = 0; p < 2; p++)
         if (!s->graph_exec[p] && (st = build_pipelined_graph(s, s->graph_len, p, &s->graph_exec[p])))
           return st;
+      s->graph_form = IB_LBM_STEP_PIPELINED;
     }
     if (!s->cap_stream) HIPCHK(s, hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking));
     while (left >= s->graph_len) {
@@ -1475,8 +1486,10 @@ ib_lbm_status ib_lbm_step(ib_lbm_sim *s, int64_t nsteps) {
         HIPCHK(s, hipStreamEndCapture(s->cap_stream, &g));
         HIPCHK(s, hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
         (void)hipGraphDestroy(g);
+        s->graph_form = s->form;
       }
       HIPCHK(s, hipGraphLaunch(ge, s->stream));
+      s->form = s->graph_form;
       left -= s->graph_len;
       s->host_cur ^= s->graph_len & 1;
     }
@@ -1857,6 +1870,12 @@ ib_lbm_status ib_lbm_get_fused(const ib_lbm_sim *s, int32_t *in_use) {
   return IB_LBM_OK;
 }
 
+ib_lbm_status ib_lbm_get_step_form(const ib_lbm_sim *s, int32_t *form) {
+  if (!s || !form) return IB_LBM_E_INVALID;
+  *form = s->form;
+  return IB_LBM_OK;
+}
+
 ib_lbm_status ib_lbm_set_graph(ib_lbm_sim *s, int32_t steps_per_graph) {
   ib_lbm_status st = usable(s);
   if (st) return st;
@@ -2185,6 +2204,7 @@ ib_lbm_status ib_lbm_batch_step(ib_lbm_batch *b, int64_t nsteps) {
   ib_lbm_status st = batch_tables(b);
   if (st) return st;
   if (b->sims.empty()) return IB_LBM_OK;
+  if (nsteps > 0) b->form = b->one ? IB_LBM_STEP_ONE : IB_LBM_STEP_PLAIN;
   int64_t left = nsteps;
   if (b->graph_steps > 0 && left >= b->graph_steps) {
     if (!b->graph_exec || b->graph_len != b->graph_steps) {
@@ -2209,6 +2229,12 @@ ib_lbm_status ib_lbm_batch_step(ib_lbm_batch *b, int64_t nsteps) {
     }
   }
   return batch_enqueue(b, left, b->stream);
+}
+
+ib_lbm_status ib_lbm_batch_get_step_form(const ib_lbm_batch *b, int32_t *form) {
+  if (!b || !form) return IB_LBM_E_INVALID;
+  *form = b->form;
+  return IB_LBM_OK;
 }
 
 ib_lbm_status ib_lbm_batch_set_graph(ib_lbm_batch *b, int32_t steps_per_graph) {

@@ -28,6 +28,7 @@ IM_NONE, IM_FENG = 0, 1
 VERLET, EULER_A1 = 0, 1
 UD_RIGID, UD_TAYLOR_GREEN = 0, 1
 SPREAD_GATHER, SPREAD_ATOMIC = 0, 1
+STEP_PLAIN, STEP_PIPELINED, STEP_FUSED, STEP_ONE = range(4)
 FLAG_NONFINITE, FLAG_RANGE, FLAG_OVERLAP = 1, 2, 4
 
 PENDING = 1
@@ -46,6 +47,7 @@ EXPORTS = [
     "ib_lbm_destroy", "ib_lbm_last_error", "ib_lbm_footprint", "ib_lbm_set_launch",
     "ib_lbm_get_launch", "ib_lbm_set_spread", "ib_lbm_set_graph", "ib_lbm_timing_enable",
     "ib_lbm_set_overlap", "ib_lbm_get_overlap", "ib_lbm_set_fused", "ib_lbm_get_fused",
+    "ib_lbm_get_step_form", "ib_lbm_batch_get_step_form",
     "ib_lbm_time_collide_stream", "ib_lbm_stream_copy",
     "ib_lbm_timing_read", "ib_lbm_batch_create", "ib_lbm_batch_attach", "ib_lbm_batch_detach",
     "ib_lbm_batch_set_target", "ib_lbm_batch_step", "ib_lbm_batch_set_graph",
@@ -187,6 +189,8 @@ def load_library(path: str = LIB_PATH):
     L.ib_lbm_stream_copy.argtypes = [vp, vp, C.c_size_t, C.c_int32, vp]
     L.ib_lbm_set_fused.argtypes = [vp, C.c_int32]
     L.ib_lbm_get_fused.argtypes = [vp, C.POINTER(C.c_int32)]
+    L.ib_lbm_get_step_form.argtypes = [vp, C.POINTER(C.c_int32)]
+    L.ib_lbm_batch_get_step_form.argtypes = [vp, C.POINTER(C.c_int32)]
     L.ib_lbm_time_collide_stream.argtypes = [vp, C.c_int32, dp, C.POINTER(C.c_int64)]
     L.ib_lbm_get_overlap.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int64)]
     L.ib_lbm_timing_enable.argtypes = [vp, C.c_int32]
@@ -491,6 +495,13 @@ class Sim:
         self._check(self.L.ib_lbm_get_fused(self.h, C.byref(v)), self.h)
         return bool(v.value)
 
+    def step_form(self) -> int:
+        """How the last step was launched (STEP_PLAIN, STEP_PIPELINED,
+        STEP_FUSED, STEP_ONE; -1 before the first)."""
+        v = C.c_int32()
+        self._check(self.L.ib_lbm_get_step_form(self.h, C.byref(v)), self.h)
+        return v.value
+
     def timing(self, on: bool):
         self._check(self.L.ib_lbm_timing_enable(self.h, 1 if on else 0), self.h)
 
@@ -552,6 +563,13 @@ class Batch:
 
     def set_spread(self, mode: int):
         self._check(self.L.ib_lbm_batch_set_spread(self.h, int(mode)))
+
+    def step_form(self) -> int:
+        """How the last step was launched (STEP_PLAIN or STEP_ONE; -1 before
+        the first)."""
+        v = C.c_int32()
+        self._check(self.L.ib_lbm_batch_get_step_form(self.h, C.byref(v)))
+        return v.value
 
     def sync(self):
         self._check(self.L.ib_lbm_batch_sync(self.h))

@@ -59,6 +59,7 @@ def test_arcs_match_the_oracle(scheme, kernel, nb):
         for k in (1, 7):
             sim.step(k)
             ref.step(k)
+            assert sim.step_form() == (ib.STEP_ONE if over and k > 1 else ib.STEP_PLAIN)
             a, b = sim.forces(0), ref.body_state(0)
             assert abs(a["fx"] - b["fx"]) < F64_DRAG * abs(b["fx"])
             assert abs(a["torque"] - b["torque"]) < F64_DRAG * abs(b["fx"]) * D
@@ -124,38 +125,30 @@ CASES = {
     "driven-DFC": box(200, 90, [dict(xc=90.0, yc=45.3, diameter=14.0, scheme=ib.DFC, kernel=ib.HAT,
                                    motion=ib.PRESCRIBED_SIN, amp=(20.0, 0.0), freq=0.002, phase=0.4)],
                     FAR, ib.CMMRT, u_bc=0.02),
+    # moving bodies of several arcs (more than 64 markers of 256 threads at the
+    # Peskin kernel): in the open, on a wall and in a corner that the arcs close
+    # themselves, and driven
+    "arcs-DFC": box(120, 110, [free(60.3, 50.6, 30.0, ib.DFC, ib.PESKIN4)], PER, ib.CMMRT,
+                    gravity=(1e-5, 2e-5)),
+    "wall-arcs-DFC": box(120, 90, [free(60.3, 16.4, 30.0, ib.DFC, ib.PESKIN4)], ZOU, ib.CMMRT,
+                         gravity=(2e-5, 1e-6)),
+    "corner-arcs-DFC": box(120, 90, [free(102.6, 72.6, 30.0, ib.DFC, ib.PESKIN4)], ZOU, ib.TRT,
+                           gravity=(-1e-6, -2e-6)),
+    "corner-arcs-DF": box(120, 90, [free(16.4, 72.6, 30.0, ib.DF, ib.PESKIN4)], ZOU, ib.TRT,
+                          gravity=(1e-6, -2e-6)),
+    "pair-arcs-DFC": box(130, 150, [free(60.3, 40.6, 30.0, ib.DFC, ib.PESKIN4),
+                                    free(66.1, 104.2, 36.0, ib.DFC, ib.PESKIN4)], (ib.BOUNCE_BACK,) * 4, ib.BGK,
+                         gravity=(0.0, -2e-5)),
+    "driven-arcs-DF": box(260, 160, [dict(xc=100.0, yc=80.3, diameter=80.0, scheme=ib.DF, kernel=ib.PESKIN4,
+                                          motion=ib.PRESCRIBED_SIN, amp=(0.0, 12.0), freq=0.002, phase=0.4)],
+                          FAR, ib.CMMRT, u_bc=0.03),
+    "driven-arcs-MDF": box(300, 190, [dict(xc=120.0, yc=95.3, diameter=100.0, scheme=ib.MDF, kernel=ib.PESKIN4,
+                                           mdf_iters=3, motion=ib.PRESCRIBED_SIN, amp=(15.0, 5.0), freq=0.002,
+                                           phase=0.4)], FAR, u_bc=0.03),
     # no body: tiles and faces alone
     "empty-open": box(131, 47, [], (ib.ZERO_GRADIENT,) * 4, ib.CMMRT),
     "empty-box": box(64, 33, [], ZOU, ib.BGK, fluid_force=(1e-6, -2e-6)),
 }
-
-
-@pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
-@pytest.mark.parametrize("name", list(CASES))
-def test_one_launch_steps_are_bitwise_the_plain_steps(name, prec):
-    case = CASES[name]
-    print(f"one-launch {name} prec={prec}", flush=True)
-    pops = ib_cases.random_populations(case["nx"], case["ny"], 5, amp=0.004, u=(0.01, 0.005))
-    runs = []
-    for over, graph in ((False, 0), (True, 0), (True, 6)):
-        sim = ib.Sim(case, precision=prec)
-        sim.set_overlap(over)
-        sim.set_populations(pops)
-        if graph:
-            sim.set_graph(graph)
-        seen = []
-        for k in (1, 2, 13, 24):
-            sim.step(k)
-            st = [sim.forces(b, check=False) for b in range(len(case["bodies"]))]
-            seen.append((sim.steps_done, sim.populations(), sim.force(), st))
-        runs.append(seen)
-        sim.close()
-    for seen in runs[1:]:
-        for (n0, p0, f0, s0), (n1, p1, f1, s1) in zip(runs[0], seen):
-            assert n0 == n1 and np.isfinite(p0).all()
-            assert np.array_equal(p0, p1)
-            assert np.array_equal(f0[0], f1[0]) and np.array_equal(f0[1], f1[1])
-            assert s0 == s1
 
 
 def plain_and_one_launch(case, prec, calls):
@@ -171,6 +164,7 @@ def plain_and_one_launch(case, prec, calls):
         seen = []
         for k in calls:
             sim.step(k)
+            assert sim.step_form() == (ib.STEP_ONE if over and (k > 1 or seen) else ib.STEP_PLAIN)
             st = [sim.forces(b, check=False) for b in range(len(case["bodies"]))]
             seen.append((sim.steps_done, sim.populations(), sim.force(), st))
         runs.append(seen)
@@ -185,6 +179,13 @@ def assert_same(runs):
             assert np.array_equal(p0, p1)
             assert np.array_equal(f0[0], f1[0]) and np.array_equal(f0[1], f1[1])
             assert s0 == s1
+
+
+@pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
+@pytest.mark.parametrize("name", list(CASES))
+def test_one_launch_steps_are_bitwise_the_plain_steps(name, prec):
+    print(f"one-launch {name} prec={prec}", flush=True)
+    assert_same(plain_and_one_launch(CASES[name], prec, (1, 2, 13, 24)))
 
 
 # DFC bodies that correct nodes of a Zou-He wall until the case halts: the
@@ -255,8 +256,9 @@ def test_batch_steps_are_bitwise_the_steps_alone(graph, prec):
     """Cases that move, halt, have no body or wait at a target that is raised
     later, stepped by shared launches in calls of odd and even lengths."""
     import torch
-    names = ["seam-DF", "open-MDF", "meet-DF", "driven-DFC", "empty-open", "fast-MDF"]
-    targets = [9, 40, 40, 23, 17, 31]
+    names = ["seam-DF", "open-MDF", "meet-DF", "driven-DFC", "empty-open", "fast-MDF", "arcs-DFC",
+             "pair-arcs-DFC", "driven-arcs-DF", "driven-arcs-MDF"]
+    targets = [9, 40, 40, 23, 17, 31, 36, 40, 21, 29]
     print(f"batch of one-launch steps graph={graph} prec={prec}", flush=True)
     stream = torch.cuda.current_stream().cuda_stream
     batch = ib.Batch(prec, stream=stream)
@@ -269,10 +271,12 @@ def test_batch_steps_are_bitwise_the_steps_alone(graph, prec):
     batch.set_target(sims[0], 14)
     batch.step(5)
     batch.sync()
+    assert batch.step_form() == ib.STEP_ONE
     targets[0] = 14
     for n, s, t in zip(names, sims, targets):
         ref = ib.Sim(CASES[n], precision=prec)
         ref.step(t)
+        assert ref.step_form() == ib.STEP_ONE
         assert s.steps_done == ref.steps_done, n
         assert np.array_equal(s.populations(), ref.populations()), n
         ref.close()
@@ -367,6 +371,7 @@ def test_batch_steps_on_both_sides_of_the_size_line(prec, ny):
         batch.attach(s)
     batch.step(5)
     batch.sync()
+    assert batch.step_form() == (ib.STEP_ONE if ny in (2220, 4440) else ib.STEP_PLAIN)
     for s, m in zip(sims, members):
         alone = ib.Sim(m, precision=prec)
         alone.step(5)
