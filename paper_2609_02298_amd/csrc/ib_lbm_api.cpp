@@ -418,9 +418,8 @@ static bool general_zero_gradient(const CaseDesc &c);
 int arc_lds_bytes(const BodyDesc &B);
 
 // One-launch steps (step_one_kernel, step_batch_kernel): sims without bodies,
-// or whose bodies are all cut into arcs.  The arcs wait for the tiles they
-// depend on while they are resident, so a launch has at most half as many arcs
-// as workgroups fit the device (step_max_waiting): the rest always runs tiles.
+// or whose bodies are all cut into arcs, at most step_max_waiting of them:
+// the arcs wait for the tiles they depend on while they are resident.
 // All workgroups have the size the arcs need (256 threads without bodies).
 // Tiles are 128 nodes wide on lattices of at least 1024 columns (186 against
 // 192 us per step on 7175 x 2014, 23.8 against 24.5 us on 1200 x 600) and 64
@@ -1531,7 +1530,9 @@ ib_lbm_status ib_lbm_forces(ib_lbm_sim *s, int32_t body_id, ib_lbm_body_state *o
     return IB_LBM_E_DIVERGED;
   }
   if (b.flags & kFlagExchange) {
-    set_err(&s->err, "body %d: the coupled MDF workgroups of the case did not meet (flags %d)",
+    set_err(&s->err, s->bodies[body_id].dev.mdf_coupled
+                         ? "body %d: the coupled MDF workgroups of the case did not meet (flags %d)"
+                         : "body %d: the pass waited too long for other workgroups of its step (flags %d)",
             body_id, b.flags);
     return IB_LBM_E_STATE;
   }

@@ -338,6 +338,69 @@ def test_a_sim_changes_behind_queued_steps():
     assert rel(out[1], out[0]) < F64_FIELD
 
 
+def disks(n, D, scheme, **kw):
+    """n fixed disks in two rows."""
+    p = int(D) + 24
+    return box((n + 1) // 2 * p + 40, 2 * p + 10,
+               [dict(xc=p * (i // 2 + 0.5) + 20.3, yc=p * (i % 2 + 0.5) + 5.2, diameter=D, scheme=scheme,
+                     kernel=ib.PESKIN4, **kw) for i in range(n)], FAR, u_bc=0.04)
+
+
+# 54 markers of its own an arc (DF, Peskin kernel): 7 or 8 arcs a disk, 56 or 64
+# in the launch, on both sides of the number that may wait in one
+@pytest.mark.parametrize("D,form", [(110.0, ib.STEP_ONE), (130.0, ib.STEP_PLAIN)])
+def test_sims_on_both_sides_of_the_arcs_that_may_wait(D, form):
+    print(f"eight disks of D={D}", flush=True)
+    case = disks(8, D, ib.DF)
+    out = []
+    for over in (False, True):
+        sim = ib.Sim(case, precision=ib.FP32_SHIFTED)
+        sim.set_overlap(over)
+        sim.step(6)
+        assert sim.step_form() == (form if over else ib.STEP_PLAIN)
+        out.append((sim.populations(), [sim.forces(b) for b in range(8)]))
+        sim.close()
+    assert np.array_equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
+
+
+@pytest.mark.parametrize("n,form", [(7, ib.STEP_ONE), (8, ib.STEP_PLAIN)])
+def test_batches_on_both_sides_of_the_arcs_that_may_wait(n, form):
+    print(f"batch of {n} disks", flush=True)
+    cases = [disks(1, 130.0, ib.DF) for _ in range(n)]
+    batch = ib.Batch(ib.FP32_SHIFTED)
+    sims = [ib.Sim(c, precision=ib.FP32_SHIFTED) for c in cases]
+    for s in sims:
+        batch.attach(s)
+    batch.step(6)
+    batch.sync()
+    assert batch.step_form() == form
+    alone = ib.Sim(cases[0], precision=ib.FP32_SHIFTED)
+    alone.step(6)
+    for s in sims:
+        assert np.array_equal(s.populations(), alone.populations())
+    batch.close()
+
+
+def test_sims_on_four_streams_at_the_arcs_that_may_wait():
+    """The most arcs a launch may have, on as many streams as have a hardware
+    queue, in workgroups of 256 and 1024 threads."""
+    import torch
+    print("four streams", flush=True)
+    cases = [disks(8, 110.0, ib.DF), disks(8, 36.0, ib.MDF, mdf_iters=5),
+             disks(8, 110.0, ib.DF), disks(8, 60.0, ib.DFC)]
+    sims = [ib.Sim(c, precision=ib.FP32_SHIFTED, stream=torch.cuda.Stream().cuda_stream) for c in cases]
+    for _ in range(20):
+        for s in sims:
+            s.step(25)
+    for s, c in zip(sims, cases):
+        assert s.step_form() == ib.STEP_ONE
+        alone = ib.Sim(c, precision=ib.FP32_SHIFTED)
+        alone.step(500)
+        assert [s.forces(b) for b in range(8)] == [alone.forces(b) for b in range(8)]
+        assert np.array_equal(s.populations(), alone.populations())
+        alone.close()
+
+
 # FP64 Peskin rows are loaded by columns: a body on a seam of the lattice's
 # storage (64 columns), at each offset of a stencil from it
 @pytest.mark.parametrize("scheme", [ib.DF, ib.MDF])
