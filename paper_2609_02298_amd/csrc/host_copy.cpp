@@ -65,6 +65,17 @@ hipError_t plain(const HostCopy *p, int n) {
   return hipSuccess;
 }
 
+// Whether p is ordinary (pageable) host memory.  A copy engine writes any other
+// kind itself, so the staging would only add a pass: 115 MB of populations into
+// a pinned array take 2.1 ms directly, 2.9 ms through the blocks (a pageable one
+// 6.3 and 2.9).
+bool pageable(const void *p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
+  (void)hipGetLastError();
+  return true;
+}
+
 // One lane: takes blocks until there are none left (or one has failed).
 void run_lane(Lane &l, int dev, const std::vector<HostCopy> &blocks, std::atomic<size_t> &next,
               std::atomic<int> &err) {
@@ -87,6 +98,8 @@ hipError_t host_copy(const HostCopy *pieces, int n) {
   size_t total = 0;
   for (int i = 0; i < n; i++) total += pieces[i].bytes;
   if (total < kSmall) return plain(pieces, n);
+  for (int i = 0; i < n; i++)
+    if (!pageable(pieces[i].host)) return plain(pieces, n);
   std::unique_lock<std::mutex> lk(mu, std::try_to_lock);
   int dev = 0;
   if (!lk.owns_lock() || hipGetDevice(&dev) != hipSuccess || !make_lanes(dev))

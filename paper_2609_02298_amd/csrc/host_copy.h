@@ -21,7 +21,8 @@ struct HostCopy {
 // 800).  Here a few threads each move blocks through a pinned buffer of their
 // own, so that one's copy and faults overlap the others' transfers (9.3 and 1.5
 // ms).  The other way a plain copy reaches 28 GB/s and stays.  Copies below 4
-// MB, and copies while another thread has the buffers, are plain ones.
+// MB, into memory that is not pageable, and while another thread has the buffers
+// are plain ones.
 hipError_t host_copy(const HostCopy *pieces, int n);
 
 // Sims and servers share the pinned buffers (12 MB, made at the first large

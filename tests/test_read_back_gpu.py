@@ -52,3 +52,17 @@ def test_read_back_from_several_threads():
         assert all(ex.map(read, range(3)))
     for s in sims:
         s.close()
+
+
+def test_populations_come_back_into_pinned_memory():
+    import ctypes as C
+    import torch
+    print("read-back into pinned memory", flush=True)
+    pops = ib_cases.random_populations(700, 500, 8)
+    sim = ib.Sim(dict(nx=700, ny=500, tau=0.8, bc=(ib.PERIODIC,) * 4, bodies=[]))
+    sim.set_populations(pops)
+    for pinned in (True, False, True):
+        out = torch.zeros(pops.shape, dtype=torch.float64, pin_memory=pinned)
+        assert sim.L.ib_lbm_get_populations(sim.h, C.cast(out.data_ptr(), C.POINTER(C.c_double))) == 0
+        assert np.array_equal(out.numpy(), pops)
+    sim.close()
