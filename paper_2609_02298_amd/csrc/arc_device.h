@@ -297,18 +297,16 @@ __device__ __forceinline__ bool count_wait(const int32_t *cnt, int n) {
 }
 
 // One arc of one body.  T: stored population; NS: stencil width; KIND: the
-// scheme; RPL: stencil rows per lane (a marker has NS / RPL lanes).  body: its
-// index in the case, of nslots bodies.  The workgroup has at least nl NS / RPL
-// threads (a multiple of 64).  BU: band entries built at a time (MDF).
+// scheme.  body: its index in the case, of nslots bodies.  The workgroup has at
+// least nl NS threads (a multiple of 64).  BU: band entries built at a time (MDF).
 // wait_for >= 0 (one-launch steps): the pass runs beside the tiles of its step and first waits until that many workgroups have
 // counted themselves in hold_done; OPEN: the lattice's Zou-He wall nodes are
 // still open then; par: the launch's parity in a batch, or -1.
 enum { kArcDF = 0, kArcMDF = 1, kArcDFC = 2 };
-template <typename T, int NS, int KIND, int RPL, bool OPEN, int BU, typename BODY>
+template <typename T, int NS, int KIND, bool OPEN, int BU, typename BODY>
 __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t step, int cur,
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
-  constexpr int LPM = NS / RPL;
   constexpr int QMAX = NS == 4 ? kArcBandRegsP4 : kArcBandRegsHat;
   const int tid = threadIdx.x;
   const double rho0 = c.rho0;
@@ -325,8 +323,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     sh.flags = bs->flags;
   }
   if (tid == 64 && B.motion == kPrescribedSin) sh.next = body_kinematics(c, B, bs, step + 1);
-  // the lane's marker and its first row
-  const int mm = tid / LPM, h = tid % LPM;
+  // the lane's marker and its row
+  const int mm = tid / NS, h = tid % NS;
   const bool live = mm < nl;
   const int m = live ? mm : 0;
   int k = whole ? m : k0 - halo + m;
@@ -374,7 +372,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   const double udx = sh.kin.udx - sh.kin.udo * (Y - yc), udy = sh.kin.udy + sh.kin.udo * (X - xc);
   const double ds = B.ds;
   const int ix0 = (int)floor(X) - s1, iy0 = (int)floor(Y) - s1;
-  const int y0 = iy0 + h * RPL;  // the lane's rows: y0 .. y0 + RPL - 1
+  const int y0 = iy0 + h;  // the lane's row
   double a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0, a6 = 0;  // fx fy torque slip | residual slip_max
   int iters = KIND == kArcDFC ? 0 : 1;
   const int motion = B.motion;
@@ -394,9 +392,9 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     sh.hist = (step % B.hist_cap) * kHistCols;
   }
   // The geometry of the step, all of it before the wait of a one-launch step:
-  // weights, the markers covering the lane's rows, its nodes' first markers,
+  // weights, the markers covering the lane's row, its nodes' first markers,
   // and DFC's correction scale.
-  double wx[NS], wyv[NS], wy[RPL];
+  double wx[NS], wyv[NS], wy;
   row_weights<NS>(X, wx);
   row_weights<NS>(Y, wyv);
   double wsum;  // (sum w_x) (sum w_y)
@@ -406,21 +404,20 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     for (int j = 0; j < NS; j++) { wsx += wx[j]; wsy += wyv[j]; }
     wsum = wsx * wsy;
   }
+  {
+    double wxh = wx[0];
+    wy = wyv[0];
 #pragma unroll
-  for (int r = 0; r < RPL; r++) {
-    double wxh = wx[r];
-    wy[r] = wyv[r];
-#pragma unroll
-    for (int q = 1; q < LPM; q++) {
-      wy[r] = h == q ? wyv[q * RPL + r] : wy[r];
-      wxh = h == q ? wx[q * RPL + r] : wxh;
+    for (int q = 1; q < NS; q++) {
+      wy = h == q ? wyv[q] : wy;
+      wxh = h == q ? wx[q] : wxh;
     }
     if (live) {
-      lwx[e0 * SW + NS + h * RPL + r] = wxh;
-      lwy[e0 * SY + 1 + h * RPL + r] = wy[r];
+      lwx[e0 * SW + NS + h] = wxh;
+      lwy[e0 * SY + 1 + h] = wy;
       if (e1 != e0) {
-        lwx[e1 * SW + NS + h * RPL + r] = wxh;
-        lwy[e1 * SY + 1 + h * RPL + r] = wy[r];
+        lwx[e1 * SW + NS + h] = wxh;
+        lwy[e1 * SY + 1 + h] = wy;
       }
     }
   }
@@ -439,15 +436,10 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     dx = (p & 0xffff) - ix0;
     ly = y - (p >> 16);
   };
-  // cov: the markers covering each row, one bit per entry m .. m + 2 bw
+  // cov: the markers covering the row, one bit per entry m .. m + 2 bw
   // (origins loaded four at a time: one LDS round trip each); mine: the nodes
   // of the row, one bit each, that no earlier marker covers.
-  uint32_t cov[RPL], mine[RPL];
-#pragma unroll
-  for (int r = 0; r < RPL; r++) {
-    cov[r] = 0;
-    mine[r] = (1u << NS) - 1;
-  }
+  uint32_t cov = 0, mine = (1u << NS) - 1;
   for (int i0 = 0; i0 <= 2 * bw; i0 += 4) {
     int p[4];
 #pragma unroll
@@ -458,12 +450,10 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       offsets(p[u], y0, dx, ly);
       const bool in = dx > -NS && dx < NS && i0 + u <= 2 * bw;
       const uint32_t cols = i0 + u < bw ? ((((1u << NS) - 1) << NS) >> (NS - dx)) : 0u;
-#pragma unroll
-      for (int r = 0; r < RPL; r++)
-        if (in && (unsigned)(ly + r) < (unsigned)NS) {
-          cov[r] |= 1u << (i0 + u);
-          mine[r] &= ~cols;
-        }
+      if (in && (unsigned)ly < (unsigned)NS) {
+        cov |= 1u << (i0 + u);
+        mine &= ~cols;
+      }
     }
   }
   // Calls f(i, w, wy) for the markers of a set covering row y in order along
@@ -485,15 +475,13 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     } else {
       // W_total interpolated to the marker (Eq. 17): sum_l sum_x D_k D_l
       double ws = 0.0;
+      for_cover(cov, y0, [&](int, const double *w, double wyl) {
+        double q = 0.0;
 #pragma unroll
-      for (int r = 0; r < RPL; r++)
-        for_cover(cov[r], y0 + r, [&](int, const double *w, double wyl) {
-          double q = 0.0;
-#pragma unroll
-          for (int j = 0; j < NS; j++) q += wx[j] * w[j];
-          ws += q * (wy[r] * wyl);
-        });
-      lam = 1.0 / (2.0 * rho0 * ds * group_sum<LPM>(ws));
+        for (int j = 0; j < NS; j++) q += wx[j] * w[j];
+        ws += q * (wy * wyl);
+      });
+      lam = 1.0 / (2.0 * rho0 * ds * group_sum<NS>(ws));
       if (motion == kFixed && owned && h == 0 && !fail) B.lambda_cache[k] = lam;
     }
   }
@@ -531,76 +519,72 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     };
     double Ux, Uy, Ftx = 0.0, Fty = 0.0;
     if constexpr (KIND != kArcDFC) {
-      // moments of the rows' nodes, interpolated to the marker (rin, ux, uy:
+      // moments of the row's nodes, interpolated to the marker (rin, ux, uy:
       // 1/rho and the velocity, kept for DF)
-      constexpr int KR = KIND == kArcDF ? RPL : 1;
-      double rin[KR][NS], ux[KR][NS], uy[KR][NS], t[RPL][NS];
+      double rin[NS], ux[NS], uy[NS], t[NS];
       double ra = 0, rb = 0, rc = 0;
+      double sm[NS], jx[NS], jy[NS];
+      if constexpr (sizeof(T) == 8 && NS == 4) {
+        // By columns: the marker's lanes read neighbouring nodes of one row,
+        // so a load touches a line per marker, not one per lane, and no row
+        // is split by a segment of the lattice's storage; the moments then
+        // change places within the lanes.
+        // (FP64 fixed body, Peskin kernel, by rows and so: DF D = 9 12.8 and
+        // 10.2 us per step, D = 30 15.1 and 12.8; MDF D = 30 21.5 and 17.2.
+        // In FP32 a row is one 16-byte load, which by columns would be four.)
+        T v[NS][9];
+        const T *p = fpop + pop_node(ix0 + h, iy0, nseg);
 #pragma unroll
-      for (int r = 0; r < RPL; r++) {
-        double sm[NS], jx[NS], jy[NS];
-        if constexpr (sizeof(T) == 8 && NS == 4 && RPL == 1) {
-          // By columns: the marker's lanes read neighbouring nodes of one row,
-          // so a load touches a line per marker, not one per lane, and no row
-          // is split by a segment of the lattice's storage; the moments then
-          // change places within the lanes.
-          // (FP64 fixed body, Peskin kernel, by rows and so: DF D = 9 12.8 and
-          // 10.2 us per step, D = 30 15.1 and 12.8; MDF D = 30 21.5 and 17.2.
-          // In FP32 a row is one 16-byte load, which by columns would be four.)
-          T v[NS][9];
-          const T *p = fpop + pop_node(ix0 + h, iy0, nseg);
+        for (int j = 0; j < NS; j++)
 #pragma unroll
-          for (int j = 0; j < NS; j++)
-#pragma unroll
-            for (int i = 0; i < 9; i++) v[j][i] = p[j * nseg * kSegBlock + i * kSeg];
-#pragma unroll
-          for (int j = 0; j < NS; j++) {
-            T q[9];
-#pragma unroll
-            for (int i = 0; i < 9; i++) q[i] = v[j][i];
-            if constexpr (OPEN)
-              if (is_zou_he_wall(c, ix0 + h, iy0 + j)) zou_he_close<T>(c, fpop, ix0 + h, iy0 + j, q);
-            node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
-          }
-          quad_transpose(sm, h);
-          quad_transpose(jx, h);
-          quad_transpose(jy, h);
-        } else {
-          T v[9][NS];
-          load_row(y0 + r, v);
-#pragma unroll
-          for (int j = 0; j < NS; j++) {
-            T q[9];
-#pragma unroll
-            for (int i = 0; i < 9; i++) q[i] = v[i][j];
-            node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
-          }
-        }
-        double qa = 0, qb = 0, qc = 0;
+          for (int i = 0; i < 9; i++) v[j][i] = p[j * nseg * kSegBlock + i * kSeg];
 #pragma unroll
         for (int j = 0; j < NS; j++) {
-          const double inv = 1.0 / sm[j];
-          jx[j] *= inv;
-          jy[j] *= inv;
-          qa += sm[j] * wx[j];
-          qb += jx[j] * wx[j];
-          qc += jy[j] * wx[j];
-          if constexpr (KIND == kArcDF) {
-            rin[r][j] = inv;
-            ux[r][j] = jx[j];
-            uy[r][j] = jy[j];
-          } else {
-            t[r][j] = wx[j] * wy[r] * (0.5 * ds * inv);
-          }
+          T q[9];
+#pragma unroll
+          for (int i = 0; i < 9; i++) q[i] = v[j][i];
+          if constexpr (OPEN)
+            if (is_zou_he_wall(c, ix0 + h, iy0 + j)) zou_he_close<T>(c, fpop, ix0 + h, iy0 + j, q);
+          node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
         }
-        ra += qa * wy[r];
-        rb += qb * wy[r];
-        rc += qc * wy[r];
-        if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);  // one row of populations at a time
+        quad_transpose(sm, h);
+        quad_transpose(jx, h);
+        quad_transpose(jy, h);
+      } else {
+        T v[9][NS];
+        load_row(y0, v);
+#pragma unroll
+        for (int j = 0; j < NS; j++) {
+          T q[9];
+#pragma unroll
+          for (int i = 0; i < 9; i++) q[i] = v[i][j];
+          node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
+        }
       }
-      const double rX = group_sum<LPM>(ra);
-      Ux = group_sum<LPM>(rb);
-      Uy = group_sum<LPM>(rc);
+      double qa = 0, qb = 0, qc = 0;
+#pragma unroll
+      for (int j = 0; j < NS; j++) {
+        const double inv = 1.0 / sm[j];
+        jx[j] *= inv;
+        jy[j] *= inv;
+        qa += sm[j] * wx[j];
+        qb += jx[j] * wx[j];
+        qc += jy[j] * wx[j];
+        if constexpr (KIND == kArcDF) {
+          rin[j] = inv;
+          ux[j] = jx[j];
+          uy[j] = jy[j];
+        } else {
+          t[j] = wx[j] * wy * (0.5 * ds * inv);
+        }
+      }
+      ra += qa * wy;
+      rb += qb * wy;
+      rc += qc * wy;
+      if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);  // the populations end here
+      const double rX = group_sum<NS>(ra);
+      Ux = group_sum<NS>(rb);
+      Uy = group_sum<NS>(rc);
       if constexpr (KIND == kArcDF) {
         // Eq. (11)
         Ftx = 2.0 * rX * (udx - Ux);
@@ -611,7 +595,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         // MDF, Eq. (12)-(14), in marker space: interpolating the updated
         // node velocities of Eq. (14) gives U^(n+1) = U^(n) + omega B F^(n),
         // B_kl = sum_x D_h(x - X_k) D_h(x - X_l) ds / (2 rho(x)).  The lane
-        // keeps its rows' terms of B's row k and, for the passes, its share of
+        // keeps its row's terms of B's row k and, for the passes, its share of
         // the band in registers: a pass is one LDS round trip and one barrier.
         // BU entries at a time overlap their LDS round trips: 25.0 us per step
         // of 2000 x 800 fp32 with four, 25.8 with two.  A batch stays at two:
@@ -628,34 +612,31 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
 #pragma unroll
             for (int j = 0; j < NS; j++) wj[j] = w[j];
             b[u] = 0.0;
+            double q = 0.0;
 #pragma unroll
-            for (int r = 0; r < RPL; r++) {
-              double q = 0.0;
-#pragma unroll
-              for (int j = 0; j < NS; j++) q += t[r][j] * wj[j];
-              b[u] += q * lwy[e * SY + 1 + max(-1, min(NS, ly + r))];
-            }
+            for (int j = 0; j < NS; j++) q += t[j] * wj[j];
+            b[u] += q * lwy[e * SY + 1 + max(-1, min(NS, ly))];
           }
 #pragma unroll
           for (int u = 0; u < BU; u++) {
-            b[u] = group_sum<LPM>(b[u]);
+            b[u] = group_sum<NS>(b[u]);
             const int d = d0 + u;
-            if (live && d <= bw && h == (d & (LPM - 1))) {
+            if (live && d <= bw && h == (d & (NS - 1))) {
               lB[e0 * nB + d] = b[u];
               if (e1 != e0) lB[e1 * nB + d] = b[u];
             }
           }
         }
         __syncthreads();
-        // the lane's entries of row k: i = h, h + LPM, ... of 0 .. 2 bw; the
+        // the lane's entries of row k: i = h, h + NS, ... of 0 .. 2 bw; the
         // ones behind the diagonal are read from the earlier marker's row
         double bq[QMAX];
 #pragma unroll
         for (int q = 0; q < QMAX; q++) {
-          const int i = q * LPM + h;
+          const int i = q * NS + h;
           bq[q] = i > 2 * bw ? 0.0 : (i >= bw ? lB[e0 * nB + i - bw] : lB[(m + i) * nB + bw - i]);
         }
-        const int nq = (2 * bw + LPM) / LPM;  // entries of a lane, ceil((2 bw + 1) / LPM)
+        const int nq = (2 * bw + NS) / NS;  // entries of a lane, ceil((2 bw + 1) / NS)
         const int N = B.mdf_iters;
         const double om = B.omega_mdf, tol = B.mdf_tol;
         const bool adapt = tol > 0.0;
@@ -671,7 +652,6 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
             // keeps the order)
             double r = live ? ex * ex + ey * ey : 0.0;
             r = r == r ? r : 0.0;
-            if (LPM == 1) r = fmax(r, dpp_f64<0xB1>(r));
             r = fmax(r, dpp_f64<0x4E>(r));
             r = fmax(r, dpp_f64<0x141>(r));
             r = fmax(r, dpp_f64<0x140>(r));
@@ -695,12 +675,12 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
 #pragma unroll
           for (int q = 0; q < QMAX; q++)
             if (q < nq) {
-              const double2 F = fb[m + h + q * LPM];
+              const double2 F = fb[m + h + q * NS];
               sx += bq[q] * F.x;
               sy += bq[q] * F.y;
             }
-          Ux += group_sum<LPM>(sx);
-          Uy += group_sum<LPM>(sy);
+          Ux += group_sum<NS>(sx);
+          Uy += group_sum<NS>(sy);
         }
         a5 = res;
         // every lane has read the last pass's forces
@@ -710,46 +690,46 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       }
       // Eulerian force f(x) = sum_k F_total D_h ds (Eq. 8) on the nodes whose
       // first marker is this lane's; DF also adds f/(2 rho) to the velocity
-      // for the slip, so there every lane sums every node of its rows
+      // for the slip, so there every lane sums every node of its row
+      auto spread = [&](double &sa, double &sb) {
+        double fx[NS], fy[NS];
+#pragma unroll
+        for (int j = 0; j < NS; j++) fx[j] = fy[j] = 0.0;
+        const uint32_t set = KIND == kArcDF ? cov : (mine ? cov & (~0u << bw) : 0u);
+        for_cover(set, y0, [&](int i, const double *w, double wyl) {
+          const double2 F = lF[m + i];
+          const double Fx = F.x * wyl, Fy = F.y * wyl;
+#pragma unroll
+          for (int j = 0; j < NS; j++) {
+            fx[j] += Fx * w[j];
+            fy[j] += Fy * w[j];
+          }
+        });
+        gmem<T> *const frc = to_global((T *)c.force) + ((uint32_t)y0 * nx + ix0);
+#pragma unroll
+        for (int j = 0; j < NS; j++)
+          if (mine & (1u << j)) {
+            frc[j] = (T)(fx[j] * ds);
+            frc[plane + j] = (T)(fy[j] * ds);
+          }
+        if constexpr (KIND == kArcDF) {
+          double qa = 0, qb = 0;
+#pragma unroll
+          for (int j = 0; j < NS; j++) {
+            const double g = 0.5 * ds * rin[j];
+            qa += (ux[j] + fx[j] * g) * wx[j];
+            qb += (uy[j] + fy[j] * g) * wx[j];
+          }
+          sa += qa * wy;
+          sb += qb * wy;
+        }
+      };
       if (owned) {
         double sa = 0, sb = 0;
-#pragma unroll
-        for (int r = 0; r < RPL; r++) {
-          double fx[NS], fy[NS];
-#pragma unroll
-          for (int j = 0; j < NS; j++) fx[j] = fy[j] = 0.0;
-          const uint32_t set = KIND == kArcDF ? cov[r] : (mine[r] ? cov[r] & (~0u << bw) : 0u);
-          for_cover(set, y0 + r, [&](int i, const double *w, double wyl) {
-            const double2 F = lF[m + i];
-            const double Fx = F.x * wyl, Fy = F.y * wyl;
-#pragma unroll
-            for (int j = 0; j < NS; j++) {
-              fx[j] += Fx * w[j];
-              fy[j] += Fy * w[j];
-            }
-          });
-          gmem<T> *const frc = to_global((T *)c.force) + ((uint32_t)(y0 + r) * nx + ix0);
-#pragma unroll
-          for (int j = 0; j < NS; j++)
-            if (mine[r] & (1u << j)) {
-              frc[j] = (T)(fx[j] * ds);
-              frc[plane + j] = (T)(fy[j] * ds);
-            }
-          if constexpr (KIND == kArcDF) {
-            double qa = 0, qb = 0;
-#pragma unroll
-            for (int j = 0; j < NS; j++) {
-              const double g = 0.5 * ds * rin[r][j];
-              qa += (ux[r][j] + fx[j] * g) * wx[j];
-              qb += (uy[r][j] + fy[j] * g) * wx[j];
-            }
-            sa += qa * wy[r];
-            sb += qb * wy[r];
-          }
-        }
+        spread(sa, sb);
         if constexpr (KIND == kArcDF) {
-          Ux = group_sum<LPM>(sa);
-          Uy = group_sum<LPM>(sb);
+          Ux = group_sum<NS>(sa);
+          Uy = group_sum<NS>(sb);
         }
         if (h == 0) {
           // force on the body (Newton's third law) and torque (Sec. 2.7)
@@ -761,21 +741,17 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       }
     } else {
       // DFC, Eq. (15)-(20)
-      T v[RPL][9][NS];
-#pragma unroll
-      for (int r = 0; r < RPL; r++) load_row(y0 + r, v[r]);
+      T v[9][NS];
+      load_row(y0, v);
       double gi[9];
 #pragma unroll
       for (int i = 0; i < 9; i++) {
         double s = 0.0;
+        double q = 0.0;
 #pragma unroll
-        for (int r = 0; r < RPL; r++) {
-          double q = 0.0;
-#pragma unroll
-          for (int j = 0; j < NS; j++) q += (double)v[r][i][j] * wx[j];
-          s += q * wy[r];
-        }
-        gi[i] = group_sum<LPM>(s);
+        for (int j = 0; j < NS; j++) q += (double)v[i][j] * wx[j];
+        s += q * wy;
+        gi[i] = group_sum<NS>(s);
       }
       double fsx = 0, fsy = 0;
 #pragma unroll
@@ -784,7 +760,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         const double dl = lam * (gi[opp_of(i)] - gi[i] + 6.0 * c_w[i] * rho0 * eud);
         fsx += c_exi[i] * dl;
         fsy += c_eyi[i] * dl;
-        if (live && h == (i & (LPM - 1))) {
+        if (live && h == (i & (NS - 1))) {
           lB[e0 * 9 + i] = dl;
           if (e1 != e0) lB[e1 * 9 + i] = dl;
         }
@@ -809,81 +785,76 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         // closes the corner, unless the body's support holds it (and closed it
         // as it was read).  Only a body near a corner looks for such nodes.
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(sh.corner), 0) && owned && met)
-#pragma unroll 1
-          for (int r = 0; r < RPL; r++)
-            for (int j = 0; j < NS; j++)
-              if (mine[r] & (1u << j)) {
-                const int x = ix0 + j, y = y0 + r;
-                int cx, cy;
-                if (!inside_corner(c, x, y, cx, cy)) continue;
-                bool held = false;
-                for_cover(cov[r], y, [&](int i, const double *, double) {
-                  const int p = lpos[m + i];
-                  held |= (unsigned)(cx - (p & 0xffff)) < (unsigned)NS && (unsigned)(cy - (p >> 16)) < (unsigned)NS;
-                });
-                if (held) continue;
-                gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(cx, cy, nseg);
-                T q[9];
+          for (int j = 0; j < NS; j++)
+            if (mine & (1u << j)) {
+              const int x = ix0 + j, y = y0;
+              int cx, cy;
+              if (!inside_corner(c, x, y, cx, cy)) continue;
+              bool held = false;
+              for_cover(cov, y, [&](int i, const double *, double) {
+                const int p = lpos[m + i];
+                held |= (unsigned)(cx - (p & 0xffff)) < (unsigned)NS && (unsigned)(cy - (p >> 16)) < (unsigned)NS;
+              });
+              if (held) continue;
+              gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(cx, cy, nseg);
+              T q[9];
 #pragma unroll
-                for (int i = 0; i < 9; i++) q[i] = fw[i * kSeg];
-                zou_he_close<T>(c, fpop, cx, cy, q);
+              for (int i = 0; i < 9; i++) q[i] = fw[i * kSeg];
+              zou_he_close<T>(c, fpop, cx, cy, q);
 #pragma unroll
-                for (int i = 1; i < 9; i++) fw[i * kSeg] = q[i];
-                *wall_flag(c, cur ^ 1, wall_index(nx, ny, cx, cy)) = 1;
-              }
+              for (int i = 1; i < 9; i++) fw[i * kSeg] = q[i];
+              *wall_flag(c, cur ^ 1, wall_index(nx, ny, cx, cy)) = 1;
+            }
       }
       if (owned && met) {
-        // Eq. (19) on every node of the lane's rows; the first marker's lane
+        // Eq. (19) on every node of the lane's row; the first marker's lane
         // writes it, and every lane takes the corrected velocity for the slip
         // (two columns at a time: the sums of four would take 72 registers)
         double sa = 0, sb = 0;
+        double qa = 0, qb = 0;
 #pragma unroll
-        for (int r = 0; r < RPL; r++) {
-          double qa = 0, qb = 0;
+        for (int j0 = 0; j0 < NS; j0 += 2) {
+          double corr[2][9];
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int j0 = 0; j0 < NS; j0 += 2) {
-            double corr[2][9];
-            __builtin_amdgcn_sched_barrier(0);
+          for (int u = 0; u < 2; u++)
 #pragma unroll
-            for (int u = 0; u < 2; u++)
+            for (int i = 0; i < 9; i++) corr[u][i] = 0.0;
+          for_cover(cov, y0, [&](int i, const double *w, double wyl) {
+            const double *q = lB + (m + i) * 9;
+            const double w0 = w[j0] * wyl, w1 = w[j0 + 1] * wyl;
 #pragma unroll
-              for (int i = 0; i < 9; i++) corr[u][i] = 0.0;
-            for_cover(cov[r], y0 + r, [&](int i, const double *w, double wyl) {
-              const double *q = lB + (m + i) * 9;
-              const double w0 = w[j0] * wyl, w1 = w[j0 + 1] * wyl;
-#pragma unroll
-              for (int n = 0; n < 9; n++) {
-                const double dq = q[n];
-                corr[0][n] += dq * w0;
-                corr[1][n] += dq * w1;
-              }
-            });
-#pragma unroll
-            for (int u = 0; u < 2; u++) {
-              const int j = j0 + u;
-              gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(ix0 + j, y0 + r, nseg);
-              const bool first = (mine[r] & (1u << j)) != 0;
-              if constexpr (OPEN)
-                if (first && is_zou_he_wall(c, ix0 + j, y0 + r))
-                  *wall_flag(c, cur ^ 1, wall_index(nx, ny, ix0 + j, y0 + r)) = 1;
-              T q[9];
-#pragma unroll
-              for (int i = 0; i < 9; i++) {
-                q[i] = (T)((double)v[r][i][j] + corr[u][i] * ds);
-                if (first) fw[i * kSeg] = q[i];
-              }
-              double sm, jx, jy;
-              node_sums<T>(q, rho0, sm, jx, jy);
-              const double inv = 1.0 / sm;
-              qa += jx * inv * wx[j];
-              qb += jy * inv * wx[j];
+            for (int n = 0; n < 9; n++) {
+              const double dq = q[n];
+              corr[0][n] += dq * w0;
+              corr[1][n] += dq * w1;
             }
+          });
+#pragma unroll
+          for (int u = 0; u < 2; u++) {
+            const int j = j0 + u;
+            gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(ix0 + j, y0, nseg);
+            const bool first = (mine & (1u << j)) != 0;
+            if constexpr (OPEN)
+              if (first && is_zou_he_wall(c, ix0 + j, y0))
+                *wall_flag(c, cur ^ 1, wall_index(nx, ny, ix0 + j, y0)) = 1;
+            T q[9];
+#pragma unroll
+            for (int i = 0; i < 9; i++) {
+              q[i] = (T)((double)v[i][j] + corr[u][i] * ds);
+              if (first) fw[i * kSeg] = q[i];
+            }
+            double sm, jx, jy;
+            node_sums<T>(q, rho0, sm, jx, jy);
+            const double inv = 1.0 / sm;
+            qa += jx * inv * wx[j];
+            qb += jy * inv * wx[j];
           }
-          sa += qa * wy[r];
-          sb += qb * wy[r];
         }
-        Ux = group_sum<LPM>(sa);
-        Uy = group_sum<LPM>(sb);
+        sa += qa * wy;
+        sb += qb * wy;
+        Ux = group_sum<NS>(sa);
+        Uy = group_sum<NS>(sb);
         if (h == 0) {
           a1 = Ftx;
           a2 = Fty;
@@ -898,7 +869,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         a6 = a4;
         mo[0] = lX[3 * m]; mo[1] = lX[3 * m + 1]; mo[2] = udx; mo[3] = udy;
       }
-      if (h == LPM - 1) {
+      if (h == NS - 1) {
         mo[4] = Ftx; mo[5] = Fty; mo[6] = lam; mo[7] = ds;
       }
     }
@@ -1040,22 +1011,22 @@ template <typename T, int SET, bool OPEN>
 __device__ __forceinline__ void arc_body(const CaseDesc &c, const BodyDesc *body_desc, int64_t step, int cur,
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
-#define IBL_PASS(BODY, NSV, KINDV, RPLV)                                                           \
-  arc_pass<T, NSV, KINDV, RPLV, OPEN, (SET == 1 ? 4 : 2)>(c, *(BODY *)body_desc, step, cur, arc, body, \
-                                                          nslots, wait_for, par, dyn, sh)
+#define IBL_PASS(BODY, NSV, KINDV)                                                               \
+  arc_pass<T, NSV, KINDV, OPEN, (SET == 1 ? 4 : 2)>(c, *(BODY *)body_desc, step, cur, arc, body, \
+                                                    nslots, wait_for, par, dyn, sh)
   if (SET == 2 || (SET == 0 && body_desc->scheme == kDFC)) {
     if constexpr (SET != 1) {
-      if (body_desc->ns == 2) IBL_PASS(const BodyDesc, 2, kArcDFC, 1);
-      else IBL_PASS(const BodyDesc, 4, kArcDFC, 1);
+      if (body_desc->ns == 2) IBL_PASS(const BodyDesc, 2, kArcDFC);
+      else IBL_PASS(const BodyDesc, 4, kArcDFC);
     }
   } else if constexpr (SET != 2) {
     ConstBody &B = *(ConstBody *)body_desc;
     if (B.scheme == kMDF) {
-      if (B.ns == 2) IBL_PASS(ConstBody, 2, kArcMDF, 1);
-      else IBL_PASS(ConstBody, 4, kArcMDF, 1);
+      if (B.ns == 2) IBL_PASS(ConstBody, 2, kArcMDF);
+      else IBL_PASS(ConstBody, 4, kArcMDF);
     } else {
-      if (B.ns == 2) IBL_PASS(ConstBody, 2, kArcDF, 1);
-      else IBL_PASS(ConstBody, 4, kArcDF, 1);
+      if (B.ns == 2) IBL_PASS(ConstBody, 2, kArcDF);
+      else IBL_PASS(ConstBody, 4, kArcDF);
     }
   }
 #undef IBL_PASS

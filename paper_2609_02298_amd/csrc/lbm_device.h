@@ -397,7 +397,7 @@ __device__ __forceinline__ bool lean_tile_index(const LeanArgs &a, int t, int &t
   return !(MODE == 2 && tx >= a.htx0 && tx < a.htx0 + a.hntx && ty >= a.hty0 && ty < a.hty0 + a.hnty);
 }
 
-template <typename T, int COL, int MODE, bool AGENT = false>
+template <typename T, int COL, int MODE>
 __device__ __forceinline__ void lean_tile(const LeanArgs &a, int tx, int ty, int lx, int ly, int bx,
                                           int by) {
   #pragma clang fp contract(off)
@@ -447,14 +447,14 @@ __device__ __forceinline__ void lean_tile(const LeanArgs &a, int tx, int ty, int
       if (fa != T(0) || fb != T(0)) {
         Fx += fa;
         Fy += fb;
-        put<AGENT>(frc + p, T(0));
-        put<AGENT>(frc + plane + p, T(0));
+        frc[p] = T(0);
+        frc[plane + p] = T(0);
       }
     } else if (MODE == 0) {
       node_force<T>(frc, plane, p, x, y, a.force_on && fv != 0, f0, f1, f2, f3, Fx, Fy);
     }
     collide<T, sizeof(T) == 4, COL>(f, Fx, Fy, a);
-    push_inner<T, AGENT>(dst + b0, dxp, dxm, rs, f);
+    push_inner<T>(dst + b0, dxp, dxm, rs, f);
   }
 }
 
