@@ -1,7 +1,8 @@
 // The immersed-boundary pass of a body cut into arcs: one workgroup per arc
 // of consecutive markers, no support tables.
 //
-// A marker's NS stencil rows lie on NS adjacent lanes (lane h of local marker
+// A marker's NS stencil rows (columns for DFC with the Peskin kernel, see COLS)
+// lie on NS adjacent lanes (lane h of local marker
 // m is thread m NS + h), each lane holding one row of NS nodes in registers:
 // it loads their populations, forms their moments and its row's part of the
 // interpolation, and DPP adds join the rows.  Markers whose stencils share a
@@ -23,7 +24,7 @@
 // body's pass (their build: row intervals, scans, node lists), one workgroup per
 // body the rest.  Whole steps, one workgroup with tables and now: fixed 2000 x
 // 800 MDF P4 fp32 27.7 and 23.0 us, oscillating 1200 x 600 MDF P4 41 and 20.5,
-// settling 400 x 2000 DFC P4 fp64 55.5 and 23.6, settling 1281 x 3841 DF P4 (a
+// settling 400 x 2000 DFC P4 fp64 55.5 and 22.3, settling 1281 x 3841 DF P4 (a
 // workspace in device memory before) 254 and 67.
 #pragma once
 #include "ib_lbm_internal.h"
@@ -307,6 +308,13 @@ template <typename T, int NS, int KIND, bool OPEN, int BU, typename BODY>
 __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t step, int cur,
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
+  // A lane's strip of its marker's stencil: NS nodes along x in a row, or
+  // (COLS) along y in a column, so that the marker's lanes load and correct
+  // neighbouring nodes of a row together, one line per marker and access instead
+  // of one per lane.  DFC moves all nine populations both ways and gains most:
+  // fixed disk, D = 9, plain steps, rows and columns: fp64 25.5 and 22.6 us, fp32
+  // 22.5 and 21.7.  (DF and MDF only load; fp64 transposes their moments below.)
+  constexpr bool COLS = KIND == kArcDFC && NS == 4;
   constexpr int QMAX = NS == 4 ? kArcBandRegsP4 : kArcBandRegsHat;
   const int tid = threadIdx.x;
   const double rho0 = c.rho0;
@@ -323,7 +331,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     sh.flags = bs->flags;
   }
   if (tid == 64 && B.motion == kPrescribedSin) sh.next = body_kinematics(c, B, bs, step + 1);
-  // the lane's marker and its row
+  // the lane's marker and its strip
   const int mm = tid / NS, h = tid % NS;
   const bool live = mm < nl;
   const int m = live ? mm : 0;
@@ -372,7 +380,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   const double udx = sh.kin.udx - sh.kin.udo * (Y - yc), udy = sh.kin.udy + sh.kin.udo * (X - xc);
   const double ds = B.ds;
   const int ix0 = (int)floor(X) - s1, iy0 = (int)floor(Y) - s1;
-  const int y0 = iy0 + h;  // the lane's row
+  const int s0 = COLS ? iy0 : ix0;       // where the strip starts
+  const int y0 = (COLS ? ix0 : iy0) + h;  // the row (column) it lies in
   double a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0, a6 = 0;  // fx fy torque slip | residual slip_max
   int iters = KIND == kArcDFC ? 0 : 1;
   const int motion = B.motion;
@@ -395,8 +404,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   // weights, the markers covering the lane's row, its nodes' first markers,
   // and DFC's correction scale.
   double wx[NS], wyv[NS], wy;
-  row_weights<NS>(X, wx);
-  row_weights<NS>(Y, wyv);
+  row_weights<NS>(COLS ? Y : X, wx);
+  row_weights<NS>(COLS ? X : Y, wyv);
   double wsum;  // (sum w_x) (sum w_y)
   {
     double wsx = 0, wsy = 0;
@@ -433,8 +442,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   // The marker at stencil origin p against row y: dx, its first column
   // relative to this marker's, and ly, the row in its stencil.
   auto offsets = [&](int p, int y, int &dx, int &ly) {
-    dx = (p & 0xffff) - ix0;
-    ly = y - (p >> 16);
+    dx = (COLS ? p >> 16 : p & 0xffff) - s0;
+    ly = y - (COLS ? p & 0xffff : p >> 16);
   };
   // cov: the markers covering the row, one bit per entry m .. m + 2 bw
   // (origins loaded four at a time: one LDS round trip each); mine: the nodes
@@ -742,7 +751,30 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     } else {
       // DFC, Eq. (15)-(20)
       T v[9][NS];
-      load_row(y0, v);
+      if constexpr (COLS) {
+        const T *p = fpop + pop_node(y0, iy0, nseg);
+#pragma unroll
+        for (int j = 0; j < NS; j++) {
+#pragma unroll
+          for (int i = 0; i < 9; i++) v[i][j] = p[j * nseg * kSegBlock + i * kSeg];
+        }
+        if constexpr (OPEN) {
+          if (y0 == 0 || y0 == nx - 1 || iy0 == 0 || iy0 + NS == ny) {
+#pragma unroll
+            for (int j = 0; j < NS; j++) {
+              if (!is_zou_he_wall(c, y0, iy0 + j)) continue;
+              T w[9];
+#pragma unroll
+              for (int i = 0; i < 9; i++) w[i] = v[i][j];
+              zou_he_close<T>(c, fpop, y0, iy0 + j, w);
+#pragma unroll
+              for (int i = 0; i < 9; i++) v[i][j] = w[i];
+            }
+          }
+        }
+      } else {
+        load_row(y0, v);
+      }
       double gi[9];
 #pragma unroll
       for (int i = 0; i < 9; i++) {
@@ -787,11 +819,11 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(sh.corner), 0) && owned && met)
           for (int j = 0; j < NS; j++)
             if (mine & (1u << j)) {
-              const int x = ix0 + j, y = y0;
+              const int x = COLS ? y0 : ix0 + j, y = COLS ? iy0 + j : y0;
               int cx, cy;
               if (!inside_corner(c, x, y, cx, cy)) continue;
               bool held = false;
-              for_cover(cov, y, [&](int i, const double *, double) {
+              for_cover(cov, y0, [&](int i, const double *, double) {
                 const int p = lpos[m + i];
                 held |= (unsigned)(cx - (p & 0xffff)) < (unsigned)NS && (unsigned)(cy - (p >> 16)) < (unsigned)NS;
               });
@@ -807,49 +839,49 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
             }
       }
       if (owned && met) {
-        // Eq. (19) on every node of the lane's row; the first marker's lane
-        // writes it, and every lane takes the corrected velocity for the slip
-        // (two columns at a time: the sums of four would take 72 registers)
+        // Eq. (19) on every node of the lane's strip; the first marker's lane
+        // writes it, and every lane takes the corrected velocity for the slip.
+        // One walk over the covering markers for the whole strip: in two walks of
+        // two nodes (176 VGPRs instead of 222, two waves per SIMD either way) the
+        // D = 9 steps above take 22.6 and 21.7 us instead of 21.4 and 20.5.
         double sa = 0, sb = 0;
         double qa = 0, qb = 0;
+        double corr[NS][9];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j0 = 0; j0 < NS; j0 += 2) {
-          double corr[2][9];
-          __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < NS; j++)
 #pragma unroll
-          for (int u = 0; u < 2; u++)
+          for (int i = 0; i < 9; i++) corr[j][i] = 0.0;
+        for_cover(cov, y0, [&](int i, const double *w, double wyl) {
+          const double *q = lB + (m + i) * 9;
+          double ww[NS];
 #pragma unroll
-            for (int i = 0; i < 9; i++) corr[u][i] = 0.0;
-          for_cover(cov, y0, [&](int i, const double *w, double wyl) {
-            const double *q = lB + (m + i) * 9;
-            const double w0 = w[j0] * wyl, w1 = w[j0 + 1] * wyl;
+          for (int j = 0; j < NS; j++) ww[j] = w[j] * wyl;
 #pragma unroll
-            for (int n = 0; n < 9; n++) {
-              const double dq = q[n];
-              corr[0][n] += dq * w0;
-              corr[1][n] += dq * w1;
-            }
-          });
+          for (int n = 0; n < 9; n++) {
+            const double dq = q[n];
 #pragma unroll
-          for (int u = 0; u < 2; u++) {
-            const int j = j0 + u;
-            gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(ix0 + j, y0, nseg);
-            const bool first = (mine & (1u << j)) != 0;
-            if constexpr (OPEN)
-              if (first && is_zou_he_wall(c, ix0 + j, y0))
-                *wall_flag(c, cur ^ 1, wall_index(nx, ny, ix0 + j, y0)) = 1;
-            T q[9];
-#pragma unroll
-            for (int i = 0; i < 9; i++) {
-              q[i] = (T)((double)v[i][j] + corr[u][i] * ds);
-              if (first) fw[i * kSeg] = q[i];
-            }
-            double sm, jx, jy;
-            node_sums<T>(q, rho0, sm, jx, jy);
-            const double inv = 1.0 / sm;
-            qa += jx * inv * wx[j];
-            qb += jy * inv * wx[j];
+            for (int j = 0; j < NS; j++) corr[j][n] += dq * ww[j];
           }
+        });
+#pragma unroll
+        for (int j = 0; j < NS; j++) {
+          const int x = COLS ? y0 : ix0 + j, y = COLS ? iy0 + j : y0;
+          gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(x, y, nseg);
+          const bool first = (mine & (1u << j)) != 0;
+          if constexpr (OPEN)
+            if (first && is_zou_he_wall(c, x, y)) *wall_flag(c, cur ^ 1, wall_index(nx, ny, x, y)) = 1;
+          T q[9];
+#pragma unroll
+          for (int i = 0; i < 9; i++) {
+            q[i] = (T)((double)v[i][j] + corr[j][i] * ds);
+            if (first) fw[i * kSeg] = q[i];
+          }
+          double sm, jx, jy;
+          node_sums<T>(q, rho0, sm, jx, jy);
+          const double inv = 1.0 / sm;
+          qa += jx * inv * wx[j];
+          qb += jy * inv * wx[j];
         }
         sa += qa * wy;
         sb += qb * wy;

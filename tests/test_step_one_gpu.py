@@ -36,12 +36,13 @@ def box(nx, ny, bodies, bc, col=ib.TRT, **kw):
 FAR = (ib.VEL_UNIFORM, ib.ZERO_GRADIENT, ib.VEL_UNIFORM, ib.VEL_UNIFORM)
 
 
-# markers per workgroup: 64 (P4) or 128 (hat) at 256 threads, MDF of five passes
-# up to 1024 threads; below, at and above each bound, and many arcs
+# markers per workgroup: 64 (P4) or 128 (hat) at 256 threads, DFC in one arc up to
+# 512 threads (P4), MDF of five passes up to 1024; below, at and above each bound, and many arcs
 @pytest.mark.parametrize("scheme,kernel,nb", [
     (ib.DF, ib.PESKIN4, 64), (ib.DF, ib.PESKIN4, 65), (ib.DF, ib.PESKIN4, 301),
     (ib.DF, ib.HAT, 128), (ib.DF, ib.HAT, 129), (ib.DF, ib.HAT, 301),
-    (ib.DFC, ib.PESKIN4, 64), (ib.DFC, ib.PESKIN4, 65), (ib.DFC, ib.PESKIN4, 200),
+    (ib.DFC, ib.PESKIN4, 64), (ib.DFC, ib.PESKIN4, 65), (ib.DFC, ib.PESKIN4, 128),
+    (ib.DFC, ib.PESKIN4, 129), (ib.DFC, ib.PESKIN4, 200),
     (ib.DFC, ib.HAT, 128), (ib.DFC, ib.HAT, 129), (ib.DFC, ib.HAT, 301),
     (ib.MDF, ib.PESKIN4, 64), (ib.MDF, ib.PESKIN4, 65), (ib.MDF, ib.PESKIN4, 128),
     (ib.MDF, ib.PESKIN4, 129), (ib.MDF, ib.PESKIN4, 301),
@@ -125,19 +126,19 @@ CASES = {
     "driven-DFC": box(200, 90, [dict(xc=90.0, yc=45.3, diameter=14.0, scheme=ib.DFC, kernel=ib.HAT,
                                    motion=ib.PRESCRIBED_SIN, amp=(20.0, 0.0), freq=0.002, phase=0.4)],
                     FAR, ib.CMMRT, u_bc=0.02),
-    # moving bodies of several arcs (more than 64 markers of 256 threads at the
-    # Peskin kernel): in the open, on a wall and in a corner that the arcs close
+    # moving bodies of several arcs (more than 64 markers at the Peskin kernel,
+    # 128 for DFC): in the open, on a wall and in a corner that the arcs close
     # themselves, and driven
-    "arcs-DFC": box(120, 110, [free(60.3, 50.6, 30.0, ib.DFC, ib.PESKIN4)], PER, ib.CMMRT,
+    "arcs-DFC": box(120, 110, [free(60.3, 50.6, 46.0, ib.DFC, ib.PESKIN4)], PER, ib.CMMRT,
                     gravity=(1e-5, 2e-5)),
-    "wall-arcs-DFC": box(120, 90, [free(60.3, 16.4, 30.0, ib.DFC, ib.PESKIN4)], ZOU, ib.CMMRT,
+    "wall-arcs-DFC": box(120, 90, [free(60.3, 24.4, 46.0, ib.DFC, ib.PESKIN4)], ZOU, ib.CMMRT,
                          gravity=(2e-5, 1e-6)),
-    "corner-arcs-DFC": box(120, 90, [free(102.6, 72.6, 30.0, ib.DFC, ib.PESKIN4)], ZOU, ib.TRT,
+    "corner-arcs-DFC": box(120, 90, [free(94.6, 64.6, 46.0, ib.DFC, ib.PESKIN4)], ZOU, ib.TRT,
                            gravity=(-1e-6, -2e-6)),
     "corner-arcs-DF": box(120, 90, [free(16.4, 72.6, 30.0, ib.DF, ib.PESKIN4)], ZOU, ib.TRT,
                           gravity=(1e-6, -2e-6)),
-    "pair-arcs-DFC": box(130, 150, [free(60.3, 40.6, 30.0, ib.DFC, ib.PESKIN4),
-                                    free(66.1, 104.2, 36.0, ib.DFC, ib.PESKIN4)], (ib.BOUNCE_BACK,) * 4, ib.BGK,
+    "pair-arcs-DFC": box(130, 170, [free(60.3, 40.6, 46.0, ib.DFC, ib.PESKIN4),
+                                    free(66.1, 114.2, 56.0, ib.DFC, ib.PESKIN4)], (ib.BOUNCE_BACK,) * 4, ib.BGK,
                          gravity=(0.0, -2e-5)),
     "driven-arcs-DF": box(260, 160, [dict(xc=100.0, yc=80.3, diameter=80.0, scheme=ib.DF, kernel=ib.PESKIN4,
                                           motion=ib.PRESCRIBED_SIN, amp=(0.0, 12.0), freq=0.002, phase=0.4)],
@@ -195,8 +196,8 @@ def test_one_launch_steps_are_bitwise_the_plain_steps(name, prec):
 HALTS = {
     "fall-P4": (14.0, ib.PESKIN4, (30.2, 8.4), (0.0, -8e-3), "E_RANGE"),
     "fall-hat": (14.0, ib.HAT, (30.2, 7.5), (0.0, -8e-3), "E_RANGE"),
-    "fall-P4-arcs": (26.0, ib.PESKIN4, (30.2, 14.4), (0.0, -8e-3), "E_RANGE"),
-    "corner-P4-arcs": (26.0, ib.PESKIN4, (44.6, 14.4), (6e-3, -6e-3), "E_RANGE"),
+    "fall-P4-arcs": (46.0, ib.PESKIN4, (30.2, 24.4), (0.0, -8e-3), "E_RANGE"),
+    "corner-P4-arcs": (46.0, ib.PESKIN4, (34.6, 24.4), (6e-3, -6e-3), "E_RANGE"),
     "slide-P4": (14.0, ib.PESKIN4, (22.2, 8.4), (0.3, 0.0), "E_DIVERGED"),
     "slide-hat-arcs": (42.0, ib.HAT, (24.2, 21.5), (0.3, 0.0), "E_DIVERGED"),
 }
@@ -401,9 +402,9 @@ def test_sims_on_four_streams_at_the_arcs_that_may_wait():
         alone.close()
 
 
-# FP64 Peskin rows are loaded by columns: a body on a seam of the lattice's
-# storage (64 columns), at each offset of a stencil from it
-@pytest.mark.parametrize("scheme", [ib.DF, ib.MDF])
+# FP64 Peskin rows (and all of DFC) are loaded by columns: a body on a seam of the
+# lattice's storage (64 columns), at each offset of a stencil from it
+@pytest.mark.parametrize("scheme", [ib.DF, ib.MDF, ib.DFC])
 @pytest.mark.parametrize("xc", [63.1, 64.2, 65.3, 66.4])
 def test_columns_across_a_storage_seam_match_the_oracle(scheme, xc):
     print(f"seam scheme={scheme} xc={xc}", flush=True)
