@@ -1,11 +1,11 @@
 // The immersed-boundary pass of a body cut into arcs: one workgroup per arc
 // of consecutive markers, no support tables.
 //
-// A marker's NS stencil rows (columns for DFC with the Peskin kernel, see COLS)
-// lie on NS adjacent lanes (lane h of local marker
-// m is thread m NS + h), each lane holding one row of NS nodes in registers:
-// it loads their populations, forms their moments and its row's part of the
-// interpolation, and DPP adds join the rows.  Markers whose stencils share a
+// A marker's stencil lies on NS adjacent lanes (lane h of local marker m is
+// thread m NS + h), each lane holding a strip of NS nodes in registers, a column
+// of the Peskin kernel's stencil or a row of the hat's: it loads their
+// populations, forms their moments and its strip's part of the interpolation, and
+// DPP adds join the strips.  Markers whose stencils share a
 // node are at most `bw` apart along the circle (plan_arcs), so an arc works on
 // its own markers plus a margin on either side ("local" markers): bw for DF,
 // 2 bw for DFC, N bw for N marker-space MDF passes, whose results are exact on
@@ -14,7 +14,7 @@
 // corrects the populations in place, once between its reads and its writes
 // (arc_sync).  A body of few markers is one arc that wraps around.
 //
-// Spreading stays a gather in marker order: a lane sums, for each of its row's
+// Spreading stays a gather in marker order: a lane sums, for each of its strip's
 // nodes, the local markers covering it from the first along the circle to
 // the last, and the lane of the first marker writes the node.  Each support
 // node has exactly one such lane over all arcs.
@@ -23,7 +23,7 @@
 // nodes per arc): the tables this form does without took most of a moving
 // body's pass (their build: row intervals, scans, node lists), one workgroup per
 // body the rest.  Whole steps, one workgroup with tables and now: fixed 2000 x
-// 800 MDF P4 fp32 27.7 and 23.0 us, oscillating 1200 x 600 MDF P4 41 and 20.5,
+// 800 MDF P4 fp32 27.7 and 22.0 us, oscillating 1200 x 600 MDF P4 41 and 19.6,
 // settling 400 x 2000 DFC P4 fp64 55.5 and 22.3, settling 1281 x 3841 DF P4 (a
 // workspace in device memory before) 254 and 67.
 #pragma once
@@ -142,24 +142,6 @@ __device__ __forceinline__ void load_pop_row(const T *__restrict__ f, int x0, in
   }
 }
 
-// The 4 x 4 transpose within each group of four lanes: v[j] of lane h becomes
-// v[h] of lane j.
-__device__ __forceinline__ void quad_transpose(double (&v)[4], int h) {
-  const bool odd = h & 1, high = h & 2;
-#pragma unroll
-  for (int i = 0; i < 4; i += 2) {
-    const double o = dpp_f64<0xB1>(odd ? v[i] : v[i + 1]);
-    v[i] = odd ? o : v[i];
-    v[i + 1] = odd ? v[i + 1] : o;
-  }
-#pragma unroll
-  for (int i = 0; i < 2; i++) {
-    const double o = dpp_f64<0x4E>(high ? v[i] : v[i + 2]);
-    v[i] = high ? o : v[i];
-    v[i + 2] = high ? v[i + 2] : o;
-  }
-}
-
 // Waits until this wave's earlier stores (device-scope ones have then
 // reached the level that all compute dies share) and loads have completed.
 __device__ __forceinline__ void vmem_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -258,7 +240,7 @@ struct ArcShared {
   int64_t hist;         // offset of the step's history row
 };
 
-// A stencil origin that covers no row.
+// A stencil origin that covers no node.
 constexpr int kArcNowhere = 0x7fffffff;
 
 // What the next step's pass waits for: the nodes whose pushes (two nodes
@@ -308,13 +290,16 @@ template <typename T, int NS, int KIND, bool OPEN, int BU, typename BODY>
 __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t step, int cur,
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
-  // A lane's strip of its marker's stencil: NS nodes along x in a row, or
-  // (COLS) along y in a column, so that the marker's lanes load and correct
-  // neighbouring nodes of a row together, one line per marker and access instead
-  // of one per lane.  DFC moves all nine populations both ways and gains most:
-  // fixed disk, D = 9, plain steps, rows and columns: fp64 25.5 and 22.6 us, fp32
-  // 22.5 and 21.7.  (DF and MDF only load; fp64 transposes their moments below.)
-  constexpr bool COLS = KIND == kArcDFC && NS == 4;
+  // A lane's strip of its marker's stencil: NS nodes along y in a column (COLS),
+  // or along x in a row.  By columns the marker's lanes access neighbouring nodes
+  // together, one line per marker and access instead of one per lane, and a strip
+  // never crosses a segment of the lattice's storage; FP32 then loads each
+  // population by itself where a row is one 16-byte load, and still gains.  Fixed
+  // disk, D = 9, plain steps, rows and columns: DFC fp64 25.5 and 22.6 us, fp32
+  // 22.5 and 21.7; DF and MDF fp32 19.6 and 18.4, 23.6 and 22.2 (fp64 19.3 and
+  // 19.1, 23.2 and 22.7 against columns transposed into rows).  One launch,
+  // oscillating 1200 x 600 MDF fp32 21.0 and 20.1.
+  constexpr bool COLS = NS == 4;
   constexpr int QMAX = NS == 4 ? kArcBandRegsP4 : kArcBandRegsHat;
   const int tid = threadIdx.x;
   const double rho0 = c.rho0;
@@ -343,8 +328,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   // the neighbour d markers further along is always entry m + bw + d, with no
   // test.  Around an arc bw entries on either side cover nothing and hold
   // zeros; a body in one arc keeps copies of its last and first markers there.
-  // w_x has NS zeros on either side and w_y one, so that a shifted row of
-  // weights (its shift clamped) needs no test either.
+  // w_x (the weights along a strip) has NS zeros on either side and w_y (across)
+  // one, so that a shifted row of weights (its shift clamped) needs no test either.
   constexpr int SW = 3 * NS, SY = NS + 2;
   const int E = arc_entries(NS, bw, nl);
   double2 *const lF = (double2 *)dyn;              // [2][E] forces
@@ -380,8 +365,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   const double udx = sh.kin.udx - sh.kin.udo * (Y - yc), udy = sh.kin.udy + sh.kin.udo * (X - xc);
   const double ds = B.ds;
   const int ix0 = (int)floor(X) - s1, iy0 = (int)floor(Y) - s1;
-  const int s0 = COLS ? iy0 : ix0;       // where the strip starts
-  const int y0 = (COLS ? ix0 : iy0) + h;  // the row (column) it lies in
+  const int s0 = COLS ? iy0 : ix0;        // where the strip starts
+  const int ln = (COLS ? ix0 : iy0) + h;  // the column or row it lies in
   double a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0, a6 = 0;  // fx fy torque slip | residual slip_max
   int iters = KIND == kArcDFC ? 0 : 1;
   const int motion = B.motion;
@@ -401,7 +386,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     sh.hist = (step % B.hist_cap) * kHistCols;
   }
   // The geometry of the step, all of it before the wait of a one-launch step:
-  // weights, the markers covering the lane's row, its nodes' first markers,
+  // weights, the markers covering the lane's strip, its nodes' first markers,
   // and DFC's correction scale.
   double wx[NS], wyv[NS], wy;
   row_weights<NS>(COLS ? Y : X, wx);
@@ -439,15 +424,15 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     lpos[e1] = ix0 | (iy0 << 16);
   }
   __syncthreads();
-  // The marker at stencil origin p against row y: dx, its first column
-  // relative to this marker's, and ly, the row in its stencil.
-  auto offsets = [&](int p, int y, int &dx, int &ly) {
+  // The marker at stencil origin p against the lane's strip: dx, the start of its
+  // strips relative to this one's, and ly, the strip's line in its stencil.
+  auto offsets = [&](int p, int &dx, int &ly) {
     dx = (COLS ? p >> 16 : p & 0xffff) - s0;
-    ly = y - (COLS ? p & 0xffff : p >> 16);
+    ly = ln - (COLS ? p & 0xffff : p >> 16);
   };
-  // cov: the markers covering the row, one bit per entry m .. m + 2 bw
+  // cov: the markers covering nodes of the strip, one bit per entry m .. m + 2 bw
   // (origins loaded four at a time: one LDS round trip each); mine: the nodes
-  // of the row, one bit each, that no earlier marker covers.
+  // of the strip, one bit each, that no earlier marker covers.
   uint32_t cov = 0, mine = (1u << NS) - 1;
   for (int i0 = 0; i0 <= 2 * bw; i0 += 4) {
     int p[4];
@@ -456,7 +441,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
 #pragma unroll
     for (int u = 0; u < 4; u++) {
       int dx, ly;
-      offsets(p[u], y0, dx, ly);
+      offsets(p[u], dx, ly);
       const bool in = dx > -NS && dx < NS && i0 + u <= 2 * bw;
       const uint32_t cols = i0 + u < bw ? ((((1u << NS) - 1) << NS) >> (NS - dx)) : 0u;
       if (in && (unsigned)ly < (unsigned)NS) {
@@ -465,15 +450,15 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       }
     }
   }
-  // Calls f(i, w, wy) for the markers of a set covering row y in order along
-  // the circle: entry m + i, its weights at this lane's columns (w, zero where
-  // it does not reach) and at the row.
-  auto for_cover = [&](uint32_t set, int y, auto &&f) {
+  // Calls f(i, w, wy) for the markers of a set covering the strip in order along
+  // the circle: entry m + i, its weights at the strip's nodes (w, zero where it
+  // does not reach) and at the strip's line.
+  auto for_cover = [&](uint32_t set, auto &&f) {
     while (set) {
       const int i = __ffs(set) - 1;
       set &= set - 1;
       int dx, ly;
-      offsets(lpos[m + i], y, dx, ly);
+      offsets(lpos[m + i], dx, ly);
       f(i, lwx + (m + i) * SW + NS - dx, lwy[(m + i) * SY + 1 + ly]);
     }
   };
@@ -484,7 +469,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     } else {
       // W_total interpolated to the marker (Eq. 17): sum_l sum_x D_k D_l
       double ws = 0.0;
-      for_cover(cov, y0, [&](int, const double *w, double wyl) {
+      for_cover(cov, [&](int, const double *w, double wyl) {
         double q = 0.0;
 #pragma unroll
         for (int j = 0; j < NS; j++) q += wx[j] * w[j];
@@ -503,17 +488,26 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   }
   if (!fail) {
     const T *const fpop = (const T *)c.f[cur ^ 1];
-    auto load_row = [&](int y, T (&v)[9][NS]) {
-      load_pop_row<T, NS>(fpop, ix0, y, nseg, v);
+    auto load_strip = [&](T (&v)[9][NS]) {
+      if constexpr (COLS) {
+        const T *p = fpop + pop_node(ln, s0, nseg);
+#pragma unroll
+        for (int j = 0; j < NS; j++)
+#pragma unroll
+          for (int i = 0; i < 9; i++) v[i][j] = p[j * nseg * kSegBlock + i * kSeg];
+      } else {
+        load_pop_row<T, NS>(fpop, s0, ln, nseg, v);
+      }
       if constexpr (OPEN) {
-        if (y == 0 || y == ny - 1 || ix0 == 0 || ix0 + NS == nx) {
+        if (ln == 0 || ln == (COLS ? nx : ny) - 1 || s0 == 0 || s0 + NS == (COLS ? ny : nx)) {
 #pragma unroll
           for (int j = 0; j < NS; j++) {
-            if (!is_zou_he_wall(c, ix0 + j, y)) continue;
+            const int x = COLS ? ln : s0 + j, y = COLS ? s0 + j : ln;
+            if (!is_zou_he_wall(c, x, y)) continue;
             T w[9];
 #pragma unroll
             for (int i = 0; i < 9; i++) w[i] = v[i][j];
-            zou_he_close<T>(c, fpop, ix0 + j, y, w);
+            zou_he_close<T>(c, fpop, x, y, w);
 #pragma unroll
             for (int i = 0; i < 9; i++) v[i][j] = w[i];
           }
@@ -528,47 +522,22 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     };
     double Ux, Uy, Ftx = 0.0, Fty = 0.0;
     if constexpr (KIND != kArcDFC) {
-      // moments of the row's nodes, interpolated to the marker (rin, ux, uy:
+      // moments of the strip's nodes, interpolated to the marker (rin, ux, uy:
       // 1/rho and the velocity, kept for DF)
       double rin[NS], ux[NS], uy[NS], t[NS];
       double ra = 0, rb = 0, rc = 0;
       double sm[NS], jx[NS], jy[NS];
-      if constexpr (sizeof(T) == 8 && NS == 4) {
-        // By columns: the marker's lanes read neighbouring nodes of one row,
-        // so a load touches a line per marker, not one per lane, and no row
-        // is split by a segment of the lattice's storage; the moments then
-        // change places within the lanes.
-        // (FP64 fixed body, Peskin kernel, by rows and so: DF D = 9 12.8 and
-        // 10.2 us per step, D = 30 15.1 and 12.8; MDF D = 30 21.5 and 17.2.
-        // In FP32 a row is one 16-byte load, which by columns would be four.)
-        T v[NS][9];
-        const T *p = fpop + pop_node(ix0 + h, iy0, nseg);
+      T v[9][NS];
+      load_strip(v);
+      // FP32: every load is issued before the first sum waits (2000 x 800 MDF 22.7
+      // us per step, 23.2 without; plain FP64 passes are 1 % slower with it)
+      if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < NS; j++)
+      for (int j = 0; j < NS; j++) {
+        T q[9];
 #pragma unroll
-          for (int i = 0; i < 9; i++) v[j][i] = p[j * nseg * kSegBlock + i * kSeg];
-#pragma unroll
-        for (int j = 0; j < NS; j++) {
-          T q[9];
-#pragma unroll
-          for (int i = 0; i < 9; i++) q[i] = v[j][i];
-          if constexpr (OPEN)
-            if (is_zou_he_wall(c, ix0 + h, iy0 + j)) zou_he_close<T>(c, fpop, ix0 + h, iy0 + j, q);
-          node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
-        }
-        quad_transpose(sm, h);
-        quad_transpose(jx, h);
-        quad_transpose(jy, h);
-      } else {
-        T v[9][NS];
-        load_row(y0, v);
-#pragma unroll
-        for (int j = 0; j < NS; j++) {
-          T q[9];
-#pragma unroll
-          for (int i = 0; i < 9; i++) q[i] = v[i][j];
-          node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
-        }
+        for (int i = 0; i < 9; i++) q[i] = v[i][j];
+        node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
       }
       double qa = 0, qb = 0, qc = 0;
 #pragma unroll
@@ -590,7 +559,6 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       ra += qa * wy;
       rb += qb * wy;
       rc += qc * wy;
-      if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);  // the populations end here
       const double rX = group_sum<NS>(ra);
       Ux = group_sum<NS>(rb);
       Uy = group_sum<NS>(rc);
@@ -604,18 +572,19 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         // MDF, Eq. (12)-(14), in marker space: interpolating the updated
         // node velocities of Eq. (14) gives U^(n+1) = U^(n) + omega B F^(n),
         // B_kl = sum_x D_h(x - X_k) D_h(x - X_l) ds / (2 rho(x)).  The lane
-        // keeps its row's terms of B's row k and, for the passes, its share of
+        // keeps its strip's terms of B's row k and, for the passes, its share of
         // the band in registers: a pass is one LDS round trip and one barrier.
-        // BU entries at a time overlap their LDS round trips: 25.0 us per step
-        // of 2000 x 800 fp32 with four, 25.8 with two.  A batch stays at two:
-        // with four a step of twelve members takes 67.4 us instead of 65.2.
+        // BU entries at a time overlap their LDS round trips: six (all of a band at
+        // markers a node apart, bw 5) 22.05 us per step of 2000 x 800 fp32, five
+        // 22.2, four 22.75.  A batch, whose passes have fewer registers, stays at
+        // two: with four a step of twelve members took 67.4 us instead of 65.2.
         for (int d0 = 0; d0 <= bw; d0 += BU) {
           double b[BU];
 #pragma unroll
           for (int u = 0; u < BU; u++) {
             const int e = e0 + min(d0 + u, bw);
             int dx, ly;
-            offsets(lpos[e], y0, dx, ly);
+            offsets(lpos[e], dx, ly);
             const double *w = lwx + e * SW + NS - max(-NS, min(NS, dx));
             double wj[NS];
 #pragma unroll
@@ -699,13 +668,13 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       }
       // Eulerian force f(x) = sum_k F_total D_h ds (Eq. 8) on the nodes whose
       // first marker is this lane's; DF also adds f/(2 rho) to the velocity
-      // for the slip, so there every lane sums every node of its row
+      // for the slip, so there every lane sums every node of its strip
       auto spread = [&](double &sa, double &sb) {
         double fx[NS], fy[NS];
 #pragma unroll
         for (int j = 0; j < NS; j++) fx[j] = fy[j] = 0.0;
         const uint32_t set = KIND == kArcDF ? cov : (mine ? cov & (~0u << bw) : 0u);
-        for_cover(set, y0, [&](int i, const double *w, double wyl) {
+        for_cover(set, [&](int i, const double *w, double wyl) {
           const double2 F = lF[m + i];
           const double Fx = F.x * wyl, Fy = F.y * wyl;
 #pragma unroll
@@ -714,12 +683,13 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
             fy[j] += Fy * w[j];
           }
         });
-        gmem<T> *const frc = to_global((T *)c.force) + ((uint32_t)y0 * nx + ix0);
+        const uint32_t sn = COLS ? nx : 1;  // to the strip's next node
+        gmem<T> *const frc = to_global((T *)c.force) + (COLS ? (uint32_t)s0 * nx + ln : (uint32_t)ln * nx + s0);
 #pragma unroll
         for (int j = 0; j < NS; j++)
           if (mine & (1u << j)) {
-            frc[j] = (T)(fx[j] * ds);
-            frc[plane + j] = (T)(fy[j] * ds);
+            frc[j * sn] = (T)(fx[j] * ds);
+            frc[plane + j * sn] = (T)(fy[j] * ds);
           }
         if constexpr (KIND == kArcDF) {
           double qa = 0, qb = 0;
@@ -751,30 +721,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     } else {
       // DFC, Eq. (15)-(20)
       T v[9][NS];
-      if constexpr (COLS) {
-        const T *p = fpop + pop_node(y0, iy0, nseg);
-#pragma unroll
-        for (int j = 0; j < NS; j++) {
-#pragma unroll
-          for (int i = 0; i < 9; i++) v[i][j] = p[j * nseg * kSegBlock + i * kSeg];
-        }
-        if constexpr (OPEN) {
-          if (y0 == 0 || y0 == nx - 1 || iy0 == 0 || iy0 + NS == ny) {
-#pragma unroll
-            for (int j = 0; j < NS; j++) {
-              if (!is_zou_he_wall(c, y0, iy0 + j)) continue;
-              T w[9];
-#pragma unroll
-              for (int i = 0; i < 9; i++) w[i] = v[i][j];
-              zou_he_close<T>(c, fpop, y0, iy0 + j, w);
-#pragma unroll
-              for (int i = 0; i < 9; i++) v[i][j] = w[i];
-            }
-          }
-        }
-      } else {
-        load_row(y0, v);
-      }
+      load_strip(v);
       double gi[9];
 #pragma unroll
       for (int i = 0; i < 9; i++) {
@@ -819,11 +766,11 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(sh.corner), 0) && owned && met)
           for (int j = 0; j < NS; j++)
             if (mine & (1u << j)) {
-              const int x = COLS ? y0 : ix0 + j, y = COLS ? iy0 + j : y0;
+              const int x = COLS ? ln : s0 + j, y = COLS ? s0 + j : ln;
               int cx, cy;
               if (!inside_corner(c, x, y, cx, cy)) continue;
               bool held = false;
-              for_cover(cov, y0, [&](int i, const double *, double) {
+              for_cover(cov, [&](int i, const double *, double) {
                 const int p = lpos[m + i];
                 held |= (unsigned)(cx - (p & 0xffff)) < (unsigned)NS && (unsigned)(cy - (p >> 16)) < (unsigned)NS;
               });
@@ -852,7 +799,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         for (int j = 0; j < NS; j++)
 #pragma unroll
           for (int i = 0; i < 9; i++) corr[j][i] = 0.0;
-        for_cover(cov, y0, [&](int i, const double *w, double wyl) {
+        for_cover(cov, [&](int i, const double *w, double wyl) {
           const double *q = lB + (m + i) * 9;
           double ww[NS];
 #pragma unroll
@@ -866,7 +813,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         });
 #pragma unroll
         for (int j = 0; j < NS; j++) {
-          const int x = COLS ? y0 : ix0 + j, y = COLS ? iy0 + j : y0;
+          const int x = COLS ? ln : s0 + j, y = COLS ? s0 + j : ln;
           gmem<T> *const fw = to_global((T *)c.f[cur ^ 1]) + pop_node(x, y, nseg);
           const bool first = (mine & (1u << j)) != 0;
           if constexpr (OPEN)
@@ -1044,7 +991,7 @@ __device__ __forceinline__ void arc_body(const CaseDesc &c, const BodyDesc *body
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
 #define IBL_PASS(BODY, NSV, KINDV)                                                               \
-  arc_pass<T, NSV, KINDV, OPEN, (SET == 1 ? 4 : 2)>(c, *(BODY *)body_desc, step, cur, arc, body, \
+  arc_pass<T, NSV, KINDV, OPEN, (SET == 1 ? 6 : 2)>(c, *(BODY *)body_desc, step, cur, arc, body, \
                                                     nslots, wait_for, par, dyn, sh)
   if (SET == 2 || (SET == 0 && body_desc->scheme == kDFC)) {
     if constexpr (SET != 1) {
