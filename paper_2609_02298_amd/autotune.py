@@ -9,12 +9,15 @@ fastest.  Results are cached in memory and in a JSON table keyed by
 paper_2609_02298_amd.autotune --write PATH``) is loaded first, so tuned
 workloads start without re-tuning.
 
-The IB pass runs one workgroup per body; its size (256, 512 or 1024
-threads) is tuned per body description and precision by timing the pass on
-the workload itself (``tune_ib``).  For a workload with bodies the tile
-shape is then chosen by the time of whole steps (``tune_step``): the tiles
-that wait for the IB pass in a pipelined step are whole tiles, so wide tiles
-can lengthen the step.  ``--ib`` tunes both for the benchmark's workloads.
+Steps that take one launch each (``Sim.step_form``: sims without bodies, or
+whose bodies all run their pass in arcs) have a tile shape and pass size of
+their own, so there is nothing to tune.  Other IB passes run one workgroup
+per body; its size (256, 512 or 1024 threads) is tuned per body description
+and precision by timing the pass on the workload itself (``tune_ib``), and
+the tile shape is then chosen by the time of whole steps (``tune_step``): the
+tiles that wait for the IB pass in a pipelined step are whole tiles, so wide
+tiles can lengthen the step.  ``--ib`` tunes both for those of the benchmark's
+workloads that use them.
 """
 from __future__ import annotations
 
@@ -134,9 +137,19 @@ def time_ib(case, precision, threads, steps=40, shape=None) -> float:
     return ms / max(n, 1) * 1e3
 
 
+def one_launch(case, precision) -> bool:
+    """Whether the case steps in one launch each, whatever the launch shape."""
+    s = ib.Sim(case, precision=precision)
+    try:
+        s.step(2)
+        return s.step_form() == ib.STEP_ONE
+    finally:
+        s.close()
+
+
 def tune_ib(case, precision, candidates=IB_CANDIDATES, steps=40) -> int:
     """Best IB workgroup size for the case's bodies (from the table, else
-    timed on this case)."""
+    timed on this case; 0, the library's choice, where steps ignore it)."""
     if not case.get("bodies"):
         return 0
     k = _ib_key(case, precision)
@@ -144,6 +157,8 @@ def tune_ib(case, precision, candidates=IB_CANDIDATES, steps=40) -> int:
         load_cache(TABLE)
     if k in _cache:
         return int(_cache[k]["ib_threads"])
+    if one_launch(case, precision):
+        return 0
     shape = tune(case["nx"], case["ny"], case["collision"], precision)
     best = None
     for t in candidates:
@@ -185,7 +200,8 @@ def tune_step(case, precision, steps=100) -> dict:
     """Launch shape and IB workgroup size for a workload with bodies, chosen
     by whole-step time: in a pipelined step the tiles that wait for the IB
     pass are whole tiles, so the shape that is fastest for the collide-stream
-    alone can lengthen the step."""
+    alone can lengthen the step.  One-launch steps ignore both: the
+    collide-stream's own shape, nothing timed."""
     base = dict(tune(case["nx"], case["ny"], case["collision"], precision))
     if not case.get("bodies"):
         return base
@@ -193,6 +209,8 @@ def tune_step(case, precision, steps=100) -> dict:
     k = "step-" + _key(case["nx"], case["ny"], case["collision"], precision) + "-" + _ib_key(case, precision)
     if k in _cache:
         return dict(_cache[k]["shape"], ib_threads=ibt)
+    if one_launch(case, precision):
+        return dict(base, ib_threads=ibt)
     cands = [base] + [c for c in STEP_CANDIDATES if c != base]
     best = None
     for sh in cands:
@@ -241,8 +259,11 @@ def _main(argv=None):
     if args.ib:
         for case in _bench_cases():
             for prec in (ib.FP32_SHIFTED, ib.FP64):
-                t = tune_ib(case, prec)
                 k = _ib_key(case, prec)
+                if one_launch(case, prec):
+                    print(f"{case['name']} {k}: one launch per step", flush=True)
+                    continue
+                t = tune_ib(case, prec)
                 print(f"{case['name']} IB {k}: {t} threads {_cache[k]['us']:.1f} us", flush=True)
                 sh = tune_step(case, prec)
                 ks = "step-" + _key(case["nx"], case["ny"], case["collision"], prec) + "-" + k

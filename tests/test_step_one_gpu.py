@@ -402,13 +402,31 @@ def test_sims_on_four_streams_at_the_arcs_that_may_wait():
         alone.close()
 
 
-# FP64 Peskin rows (and all of DFC) are loaded by columns: a body on a seam of the
+def test_the_tuner_times_nothing_that_one_launch_steps_ignore(monkeypatch):
+    from paper_2609_02298_amd import autotune
+    print("tuner and one-launch steps", flush=True)
+    shape = dict(block_x=64, block_y=2, rows_per_thread=1, xcd_remap=1)
+    monkeypatch.setattr(autotune, "_cache", {"other": {}})
+    monkeypatch.setattr(autotune, "tune", lambda *a, **k: dict(shape))
+    timed = []
+    monkeypatch.setattr(autotune, "time_step", lambda c, p, sh, n: timed.append("step") or 1.0)
+    monkeypatch.setattr(autotune, "time_ib", lambda c, p, t, n, sh: timed.append("ib") or 1.0)
+    case = disks(1, 20.0, ib.MDF, mdf_iters=5)
+    assert autotune.tune_step(case, ib.FP64) == dict(shape, ib_threads=0)
+    assert not timed and set(autotune._cache) == {"other"}
+    # a coupled body keeps the launches that the shape is for
+    autotune.tune_step(disks(1, 20.0, ib.MDF, mdf_iters=5, mdf_coupled=1), ib.FP64)
+    assert set(timed) == {"step", "ib"} and len(autotune._cache) == 3
+
+
+# Peskin stencils are loaded by columns, the hat's by rows: a body on a seam of the
 # lattice's storage (64 columns), at each offset of a stencil from it
 @pytest.mark.parametrize("scheme", [ib.DF, ib.MDF, ib.DFC])
 @pytest.mark.parametrize("xc", [63.1, 64.2, 65.3, 66.4])
-def test_columns_across_a_storage_seam_match_the_oracle(scheme, xc):
-    print(f"seam scheme={scheme} xc={xc}", flush=True)
-    case = box(140, 60, [dict(xc=xc, yc=30.3, diameter=9.0, scheme=scheme, kernel=ib.PESKIN4, mdf_iters=5)],
+@pytest.mark.parametrize("kernel", [ib.PESKIN4, ib.HAT])
+def test_columns_across_a_storage_seam_match_the_oracle(kernel, scheme, xc):
+    print(f"seam scheme={scheme} kernel={kernel} xc={xc}", flush=True)
+    case = box(140, 60, [dict(xc=xc, yc=30.3, diameter=9.0, scheme=scheme, kernel=kernel, mdf_iters=5)],
                FAR, u_bc=0.05)
     sim, ref = ib.Sim(case), oracle.OracleSim(case)
     ref.add_body(case["bodies"][0])
