@@ -574,10 +574,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         // B_kl = sum_x D_h(x - X_k) D_h(x - X_l) ds / (2 rho(x)).  The lane
         // keeps its strip's terms of B's row k and, for the passes, its share of
         // the band in registers: a pass is one LDS round trip and one barrier.
-        // BU entries at a time overlap their LDS round trips: six (all of a band at
-        // markers a node apart, bw 5) 22.05 us per step of 2000 x 800 fp32, five
-        // 22.2, four 22.75.  A batch, whose passes have fewer registers, stays at
-        // two: with four a step of twelve members took 67.4 us instead of 65.2.
+        // BU entries at a time (arc_build) overlap their LDS round trips.
         for (int d0 = 0; d0 <= bw; d0 += BU) {
           double b[BU];
 #pragma unroll
@@ -984,6 +981,17 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   case_body_done(c, c.state, step, cur, nslots, flags, box_valid, box, par);
 }
 
+// Band entries that an MDF pass builds at a time.  FP32 Peskin: six, the whole
+// band of markers a node apart (bw 5); 2000 x 800 takes 22.05 us per step, 22.2
+// with five, 22.75 with four.  FP64: four; with six a disk of D = 9 (bw 6) takes 13.7
+// us instead of 13.2, of D = 30 16.5 instead of 16.7.  Hat: three (bw 2); with four
+// FP64 disks are up to 1 % slower.  A batch, whose passes have fewer registers,
+// stays at two: with four a step of twelve members took 67.4 us instead of 65.2.
+template <typename T>
+__device__ constexpr int arc_build(int set, int ns) {
+  return set != 1 ? 2 : (ns == 2 ? 3 : (sizeof(T) == 4 ? 6 : 4));
+}
+
 // The pass of one arc (see arc_pass).  SET: the schemes the instance holds, 0
 // all, 1 DF and MDF, 2 DFC.
 template <typename T, int SET, bool OPEN>
@@ -991,7 +999,7 @@ __device__ __forceinline__ void arc_body(const CaseDesc &c, const BodyDesc *body
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
 #define IBL_PASS(BODY, NSV, KINDV)                                                               \
-  arc_pass<T, NSV, KINDV, OPEN, (SET == 1 ? 6 : 2)>(c, *(BODY *)body_desc, step, cur, arc, body, \
+  arc_pass<T, NSV, KINDV, OPEN, arc_build<T>(SET, NSV)>(c, *(BODY *)body_desc, step, cur, arc, body, \
                                                     nslots, wait_for, par, dyn, sh)
   if (SET == 2 || (SET == 0 && body_desc->scheme == kDFC)) {
     if constexpr (SET != 1) {

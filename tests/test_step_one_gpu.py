@@ -148,6 +148,8 @@ CASES = {
                                            phase=0.4)], FAR, u_bc=0.03),
     # no body: tiles and faces alone
     "empty-open": box(131, 47, [], (ib.ZERO_GRADIENT,) * 4, ib.CMMRT),
+    "empty-3x3": box(3, 3, [], PER),
+    "empty-5x4": box(5, 4, [], (ib.BOUNCE_BACK,) * 4, ib.BGK),
     "empty-box": box(64, 33, [], ZOU, ib.BGK, fluid_force=(1e-6, -2e-6)),
 }
 
@@ -230,6 +232,38 @@ def test_a_corner_is_closed_before_its_inner_node_is_corrected(north, east, kern
     y = ny - high - R if north else low + R
     body = dict(xc=x, yc=y, diameter=2 * R, scheme=ib.DFC, kernel=kernel)
     assert_same(plain_and_one_launch(box(nx, ny, [body], ZOU, ib.TRT), prec, (1, 2, 13, 24)))
+
+
+# a body in arcs beside one that is too small for them: their passes are two
+# launches, and the last to finish completes the case
+@pytest.mark.parametrize("scheme", [ib.DF, ib.MDF, ib.DFC])
+def test_a_body_in_arcs_beside_one_that_is_not(scheme):
+    print(f"mixed bodies scheme={scheme}", flush=True)
+    bodies = [dict(xc=x, yc=y, diameter=D, scheme=scheme, kernel=ib.PESKIN4, mdf_iters=3, motion=ib.FREE,
+                   density_ratio=1.6, internal_mass=ib.IM_FENG)
+              for x, y, D in ((30.3, 40.2, 26.0), (70.4, 38.1, 5.0), (96.2, 60.7, 20.0))]
+    case = box(130, 90, bodies, ZOU if scheme == ib.DFC else PER, gravity=(2e-5, 1e-5))
+    batch = ib.Batch(ib.FP64)
+    sims = [ib.Sim(case), ib.Sim(case)] if scheme != ib.DFC else [ib.Sim(case)]
+    ref = oracle.OracleSim(case)
+    for b in bodies:
+        ref.add_body(b)
+    if len(sims) > 1:
+        batch.attach(sims[1])
+        batch.step(12)
+        assert batch.step_form() == ib.STEP_PLAIN
+    sims[0].step(12)
+    ref.step(12)
+    for sim in sims:
+        for k in range(3):
+            a, b = sim.forces(k), ref.body_state(k)
+            assert abs(a["yc"] - b["yc"]) < 1e-12 * b["yc"] and abs(a["vx"] - b["vx"]) < 1e-10 * abs(b["vx"])
+        assert rel(sim.populations(), ref.populations()) < F64_FIELD
+    assert sims[0].step_form() == ib.STEP_PLAIN
+    batch.close()
+    for sim in sims:
+        sim.close()
+    ref.close()
 
 
 def test_one_launch_steps_after_atomic_spreading():
