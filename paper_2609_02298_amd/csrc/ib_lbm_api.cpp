@@ -10,8 +10,9 @@
 #include <cstdio>
 #include <cstring>
 #include <initializer_list>
-#include <map>
 #include <limits>
+#include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -417,9 +418,53 @@ ib_lbm_status plan_fused(ib_lbm_sim *s) {
 static bool general_zero_gradient(const CaseDesc &c);
 int arc_lds_bytes(const BodyDesc &B);
 
+// The arcs of the one-launch steps that may be running: per stream, whose launches
+// follow each other, those of the sim or batch with the most.
+class ArcBudget {
+ public:
+  // Whether `who` may have narcs waiting on a stream, with at most `most` in all;
+  // gives back what it had.
+  bool take(int dev, hipStream_t stream, const void *who, int narcs, int most) {
+    std::lock_guard<std::mutex> lk(mu_);
+    drop(who);
+    if (narcs == 0) return most > 0;
+    int others = 0, own = narcs;
+    for (auto &st : use_) {
+      int n = 0;
+      for (auto &o : st.second) n = std::max(n, o.second);
+      if (st.first == Key(dev, stream)) own = std::max(own, n);
+      else if (st.first.first == dev) others += n;
+    }
+    if (own + others > most) return false;
+    use_[Key(dev, stream)][who] = narcs;
+    return true;
+  }
+  void give_back(const void *who) {
+    std::lock_guard<std::mutex> lk(mu_);
+    drop(who);
+  }
+
+ private:
+  using Key = std::pair<int, hipStream_t>;
+  void drop(const void *who) {
+    for (auto it = use_.begin(); it != use_.end();) {
+      it->second.erase(who);
+      it = it->second.empty() ? use_.erase(it) : std::next(it);
+    }
+  }
+  std::mutex mu_;
+  std::map<Key, std::map<const void *, int>> use_;
+};
+// (never destroyed: sims may outlive the library's static objects)
+ArcBudget &arc_budget = *new ArcBudget;
+
 // One-launch steps (step_one_kernel, step_batch_kernel): sims without bodies,
-// or whose bodies are all cut into arcs, at most step_max_waiting of them:
-// the arcs wait for the tiles they depend on while they are resident.
+// or whose bodies are all cut into arcs.  The arcs wait for the tiles they
+// depend on while they are resident, so all launches that may run at once share
+// step_max_waiting of them (ArcBudget), and a sim on its own has at most kArcMax:
+// beyond, one launch is no gain (8 x DF D = 200, 96 arcs, fp32 936 x 458: 105 us
+// per step, 45 in several; 8 x DFC D = 130, 72 arcs, 2440 x 1210: 102 and 72; a
+// batch of 56 cases, 64 arcs, 5.4 M nodes: 119 and 169).
 // All workgroups have the size the arcs need (256 threads without bodies).
 // Tiles are 128 nodes wide on lattices of at least 1024 columns (186 against
 // 192 us per step on 7175 x 2014, 23.8 against 24.5 us on 1200 x 600) and 64
@@ -480,6 +525,7 @@ void fill_step_args(const ib_lbm_sim *s, int threads, int rows, StepOneArgs *out
 
 void plan_one(ib_lbm_sim *s) {
   s->one = false;
+  arc_budget.give_back(s);
   if (!s->overlap || !s->fused_allowed) return;
   OneShape sh;
   if (!sh.add(s->bodies, s->spread_mode)) return;
@@ -489,7 +535,9 @@ void plan_one(ib_lbm_sim *s) {
   s->one_threads = sh.threads;
   s->one_lds = sh.lds;
   s->one_face = has_zou_he(s->cd) ? 2 : (general_zero_gradient(s->cd) ? 1 : 0);
-  s->one = s->one_args.narcs <= step_max_waiting(s->cd.precision, s->one_face, dfc, false, sh.threads, sh.lds);
+  s->one = s->one_args.narcs <= kArcMax &&
+           arc_budget.take(s->dev, s->stream, s, s->one_args.narcs,
+                           step_max_waiting(s->cd.precision, s->one_face, dfc, false, sh.threads, sh.lds));
 }
 
 // A body runs on the 1024-thread IB kernel when it is DF/MDF, its workspace
@@ -1776,6 +1824,7 @@ ib_lbm_status ib_lbm_destroy(ib_lbm_sim *s) {
   if (!s) return IB_LBM_E_INVALID;
   if (s->batch) ib_lbm_batch_detach(s->batch, s);
   if (s->stream) (void)hipStreamSynchronize(s->stream);
+  arc_budget.give_back(s);
   drop_graphs(s);
   if (s->lq) (void)hipStreamSynchronize(s->lq);
   if (s->iq) (void)hipStreamSynchronize(s->iq);
@@ -2019,6 +2068,7 @@ ib_lbm_status ib_lbm_batch_detach(ib_lbm_batch *b, ib_lbm_sim *s) {
   if (it == b->sims.end()) return IB_LBM_E_INVALID;
   if (b->stream) (void)hipStreamSynchronize(b->stream);
   b->sims.erase(it);
+  if (b->sims.empty()) arc_budget.give_back(b);
   s->batch = nullptr;
   b->dirty = true;
   // stepped on its own again: no target, and the lattice index the batch
@@ -2109,6 +2159,7 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
     if ((st = upload(&b->d_slots, slots.data(), slots.size() * sizeof(IbmSlot)))) return st;
   }
   b->ib = lists.ib;
+  arc_budget.give_back(b);
   OneShape sh;
   // One launch per step saves a batch the launches per collision model and
   // their gaps; its tiles, compiled with the passes, have fewer waves per SIMD
@@ -2139,7 +2190,8 @@ static ib_lbm_status batch_tables(ib_lbm_batch *b) {
       g.nface += one[i].nface;
       g.ntile += one[i].lean.ntiles;
     }
-    b->one = g.narcs <= step_max_waiting(b->precision, b->one_face, false, true, sh.threads, sh.lds);
+    b->one = arc_budget.take(case_sims[0]->dev, b->stream, b, g.narcs,
+                             step_max_waiting(b->precision, b->one_face, false, true, sh.threads, sh.lds));
     if (b->one) {
       if ((st = upload(&b->d_one, one.data(), one.size() * sizeof(StepOneArgs)))) return st;
       std::vector<int32_t> all;
@@ -2282,6 +2334,7 @@ ib_lbm_status ib_lbm_batch_destroy(ib_lbm_batch *b) {
   if (!b) return IB_LBM_E_INVALID;
   if (b->stream) (void)hipStreamSynchronize(b->stream);
   for (auto *s : b->sims) s->batch = nullptr;
+  arc_budget.give_back(b);
   if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   if (b->d_cases.p) (void)hipFree(b->d_cases.p);

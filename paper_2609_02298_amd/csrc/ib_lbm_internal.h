@@ -255,7 +255,7 @@ __host__ __device__ inline int ws_coupled_doubles(int nb, int mn) { return 4 * n
 // of the 2 bw + 1 entries, ceil((2 bw + 1) / ns), in registers.
 constexpr int kArcBandRegsP4 = 5;   // bw <= 9
 constexpr int kArcBandRegsHat = 6;  // bw <= 5
-constexpr int kArcMax = 56;         // arcs per body (one wave sums them; see step_max_waiting)
+constexpr int kArcMax = 56;         // arcs per body (one wave sums them), and of a sim's launch
 // LDS entries of an arc of nl local markers (a margin of bw on both sides,
 // ns of slack behind the last lane's share of the band) and its shared memory
 // in doubles: position and weight sum, forces, weights, the band (MDF) or the corrections (DFC), and
@@ -456,15 +456,14 @@ hipError_t launch_step_batch(int precision, int face, const StepBatchArgs &a, in
                              hipStream_t stream);
 hipError_t launch_batch_control(const StepOneArgs *cases, int ncases, hipStream_t stream);
 hipError_t launch_batch_work(const StepBatchArgs &a, hipStream_t stream);
-// Arcs that a one-launch step may have: they wait, resident, for tiles of their
-// own launch, so the launches that run together must not fill the device with
-// them.  A waiting arc keeps work from one compute unit at most, and consecutive
-// workgroups go round the eight XCDs.  Four launches run at once (HIP's default
-// of hardware queues per process), and on each XCD of 32 units the arcs of all
-// four leave some free: 7 each, 56 in all.  Launches of other processes and
-// streams held to a few units by a mask are not counted; there, and where more
-// queues are asked for, only the bound of the wait ends it (kFlagExchange).
-// 0 if the kernel does not fit the device.
+// Arcs that one-launch steps may have waiting on the device at once.  They wait,
+// resident, for tiles of their own launch, so the launches that run together must
+// not fill the device with them.  A waiting arc keeps work from one compute unit at
+// most, and consecutive workgroups go round the XCDs, so up to three quarters of
+// the units, over all launches, leave some free on each.  Launches of other
+// processes and streams held to a few units by a mask are not counted; there only
+// the bound of the wait ends it (kFlagExchange).  0 if the kernel does not fit the
+// device.
 int step_max_waiting(int precision, int face, bool dfc, bool batch, int threads, int lds_bytes);
 int fused_grid(const FusedArgs &a);
 hipError_t launch_step_fused(int precision, int collision, const FusedArgs &a, int lds_bytes,

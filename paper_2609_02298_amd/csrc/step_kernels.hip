@@ -479,7 +479,7 @@ int step_max_waiting(int precision, int face, bool dfc, bool batch, int threads,
     (void)hipGetLastError();
     return 0;
   }
-  return per > 0 ? 8 * ((ncu / 8 - 1) / 4) : 0;
+  return per > 0 ? ncu * 3 / 4 : 0;
 }
 
 }  // namespace iblbm

@@ -382,9 +382,9 @@ def disks(n, D, scheme, **kw):
 
 
 # 54 markers of its own an arc (DF, Peskin kernel): 7 or 8 arcs a disk, 56 or 64
-# in the launch, on both sides of the number that may wait in one
+# in the launch, on both sides of the number that a sim has in one
 @pytest.mark.parametrize("D,form", [(110.0, ib.STEP_ONE), (130.0, ib.STEP_PLAIN)])
-def test_sims_on_both_sides_of_the_arcs_that_may_wait(D, form):
+def test_sims_on_both_sides_of_the_arcs_in_one_launch(D, form):
     print(f"eight disks of D={D}", flush=True)
     case = disks(8, D, ib.DF)
     out = []
@@ -398,27 +398,51 @@ def test_sims_on_both_sides_of_the_arcs_that_may_wait(D, form):
     assert np.array_equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
 
 
-@pytest.mark.parametrize("n,form", [(7, ib.STEP_ONE), (8, ib.STEP_PLAIN)])
+# 8 arcs a member: 192 or 200, on both sides of the arcs that may wait at once
+@pytest.mark.parametrize("n,form", [(24, ib.STEP_ONE), (25, ib.STEP_PLAIN)])
 def test_batches_on_both_sides_of_the_arcs_that_may_wait(n, form):
     print(f"batch of {n} disks", flush=True)
-    cases = [disks(1, 130.0, ib.DF) for _ in range(n)]
+    case = disks(1, 130.0, ib.DF)
     batch = ib.Batch(ib.FP32_SHIFTED)
-    sims = [ib.Sim(c, precision=ib.FP32_SHIFTED) for c in cases]
+    sims = [ib.Sim(case, precision=ib.FP32_SHIFTED) for _ in range(n)]
     for s in sims:
         batch.attach(s)
     batch.step(6)
     batch.sync()
     assert batch.step_form() == form
-    alone = ib.Sim(cases[0], precision=ib.FP32_SHIFTED)
+    alone = ib.Sim(case, precision=ib.FP32_SHIFTED)
     alone.step(6)
     for s in sims:
         assert np.array_equal(s.populations(), alone.populations())
     batch.close()
 
 
+def test_sims_on_several_streams_share_the_arcs_that_may_wait():
+    """Three sims of 56 arcs on streams of their own leave 24 of 192: the fourth
+    steps in several launches, until another gives its arcs back; one on the
+    stream of another needs none of its own."""
+    import torch
+    print("arcs shared by streams", flush=True)
+    case = disks(8, 110.0, ib.DF)
+    streams = [torch.cuda.Stream().cuda_stream for _ in range(4)]
+    sims = [ib.Sim(case, precision=ib.FP32_SHIFTED, stream=st) for st in streams + streams[:1]]
+    for s in sims:
+        s.step(6)
+    assert [s.step_form() for s in sims] == [ib.STEP_ONE] * 3 + [ib.STEP_PLAIN, ib.STEP_ONE]
+    sims[1].close()
+    for s in (sims[0], sims[2], sims[3], sims[4]):
+        s.set_launch()  # plans its steps anew
+        s.step(5)
+        assert s.step_form() == ib.STEP_ONE
+    pops = [s.populations() for s in (sims[0], sims[2], sims[3], sims[4])]
+    assert all(np.array_equal(p, pops[0]) for p in pops)
+    for s in sims:
+        s.close()
+
+
 def test_sims_on_four_streams_at_the_arcs_that_may_wait():
-    """The most arcs a launch may have, on as many streams as have a hardware
-    queue, in workgroups of 256 and 1024 threads."""
+    """160 arcs on as many streams as have a hardware queue, in workgroups of 256
+    and 512 threads."""
     import torch
     print("four streams", flush=True)
     cases = [disks(8, 110.0, ib.DF), disks(8, 36.0, ib.MDF, mdf_iters=5),
