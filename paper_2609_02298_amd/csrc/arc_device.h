@@ -2,9 +2,8 @@
 // of consecutive markers, no support tables.
 //
 // A marker's stencil lies on NS adjacent lanes (lane h of local marker m is
-// thread m NS + h), each lane holding a strip of NS nodes in registers, a column
-// of the Peskin kernel's stencil or a row of the hat's: it loads their
-// populations, forms their moments and its strip's part of the interpolation, and
+// thread m NS + h), each lane holding a strip of NS nodes in registers, a row of
+// the stencil or a column (see COLS): it loads their populations, forms their moments and its strip's part of the interpolation, and
 // DPP adds join the strips.  Markers whose stencils share a
 // node are at most `bw` apart along the circle (plan_arcs), so an arc works on
 // its own markers plus a margin on either side ("local" markers): bw for DF,
@@ -139,6 +138,24 @@ __device__ __forceinline__ void load_pop_row(const T *__restrict__ f, int x0, in
 #pragma unroll
       for (int i = 0; i < 9; i++) v[i][j] = p[i * kSeg];
     }
+  }
+}
+
+// The 4 x 4 transpose within each group of four lanes: v[j] of lane h becomes
+// v[h] of lane j.
+__device__ __forceinline__ void quad_transpose(double (&v)[4], int h) {
+  const bool odd = h & 1, high = h & 2;
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    const double o = dpp_f64<0xB1>(odd ? v[i] : v[i + 1]);
+    v[i] = odd ? o : v[i];
+    v[i + 1] = odd ? v[i + 1] : o;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const double o = dpp_f64<0x4E>(high ? v[i] : v[i + 2]);
+    v[i] = high ? o : v[i];
+    v[i + 2] = high ? v[i + 2] : o;
   }
 }
 
@@ -290,16 +307,19 @@ template <typename T, int NS, int KIND, bool OPEN, int BU, typename BODY>
 __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t step, int cur,
                                          int arc, int body, int nslots, int wait_for, int par, double *dyn,
                                          ArcShared &sh) {
-  // A lane's strip of its marker's stencil: NS nodes along y in a column (COLS),
-  // or along x in a row.  By columns the marker's lanes access neighbouring nodes
-  // together, one line per marker and access instead of one per lane, and a strip
-  // never crosses a segment of the lattice's storage; FP32 then loads each
-  // population by itself where a row is one 16-byte load, and still gains.  Fixed
-  // disk, D = 9, plain steps, rows and columns: DFC fp64 25.5 and 22.6 us, fp32
-  // 22.5 and 21.7; DF and MDF fp32 19.6 and 18.4, 23.6 and 22.2 (fp64 19.3 and
-  // 19.1, 23.2 and 22.7 against columns transposed into rows).  One launch,
-  // oscillating 1200 x 600 MDF fp32 21.0 and 20.1.
-  constexpr bool COLS = NS == 4;
+  // A lane's strip of its marker's stencil: NS nodes along x in a row, or (COLS,
+  // FP32 Peskin) along y in a column.  By columns the marker's lanes access
+  // neighbouring nodes together, one line per marker and access instead of one per
+  // lane, and a strip never crosses a segment of the lattice's storage; FP32 then
+  // loads each population by itself where a row is one 16-byte load, and still
+  // gains.  FP64 Peskin loads columns too and turns them into rows (TURN: the sums
+  // keep their order, and with it the last bits of FP64 results).  Fixed disk, D =
+  // 9, plain steps, row loads and now: DFC fp64 25.8 and 22.2 us, fp32 22.5 and
+  // 20.3; DF fp32 19.7 and 18.4, MDF fp32 23.4 and 22.2.  One launch, DF fp64 12.8
+  // and 10.2, MDF D = 30 fp64 21.5 and 17.2, oscillating 1200 x 600 MDF fp32 21.0
+  // and 20.1.
+  constexpr bool COLS = NS == 4 && sizeof(T) == 4;
+  constexpr bool TURN = NS == 4 && sizeof(T) == 8;
   constexpr int QMAX = NS == 4 ? kArcBandRegsP4 : kArcBandRegsHat;
   const int tid = threadIdx.x;
   const double rho0 = c.rho0;
@@ -488,21 +508,24 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   }
   if (!fail) {
     const T *const fpop = (const T *)c.f[cur ^ 1];
+    // The populations of the strip's nodes, or, to be turned, of the h-th column's.
     auto load_strip = [&](T (&v)[9][NS]) {
-      if constexpr (COLS) {
-        const T *p = fpop + pop_node(ln, s0, nseg);
+      constexpr bool cols = COLS || TURN;
+      const int l = TURN ? ix0 + h : ln, a0 = TURN ? iy0 : s0;
+      if constexpr (cols) {
+        const T *p = fpop + pop_node(l, a0, nseg);
 #pragma unroll
         for (int j = 0; j < NS; j++)
 #pragma unroll
           for (int i = 0; i < 9; i++) v[i][j] = p[j * nseg * kSegBlock + i * kSeg];
       } else {
-        load_pop_row<T, NS>(fpop, s0, ln, nseg, v);
+        load_pop_row<T, NS>(fpop, a0, l, nseg, v);
       }
       if constexpr (OPEN) {
-        if (ln == 0 || ln == (COLS ? nx : ny) - 1 || s0 == 0 || s0 + NS == (COLS ? ny : nx)) {
+        if (l == 0 || l == (cols ? nx : ny) - 1 || a0 == 0 || a0 + NS == (cols ? ny : nx)) {
 #pragma unroll
           for (int j = 0; j < NS; j++) {
-            const int x = COLS ? ln : s0 + j, y = COLS ? s0 + j : ln;
+            const int x = cols ? l : a0 + j, y = cols ? a0 + j : l;
             if (!is_zou_he_wall(c, x, y)) continue;
             T w[9];
 #pragma unroll
@@ -539,6 +562,11 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         for (int i = 0; i < 9; i++) q[i] = v[i][j];
         node_sums<T>(q, rho0, sm[j], jx[j], jy[j]);
       }
+      if constexpr (TURN) {
+        quad_transpose(sm, h);
+        quad_transpose(jx, h);
+        quad_transpose(jy, h);
+      }
       double qa = 0, qb = 0, qc = 0;
 #pragma unroll
       for (int j = 0; j < NS; j++) {
@@ -559,6 +587,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       ra += qa * wy;
       rb += qb * wy;
       rc += qc * wy;
+      if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);  // the populations end here
       const double rX = group_sum<NS>(ra);
       Ux = group_sum<NS>(rb);
       Uy = group_sum<NS>(rc);
@@ -719,6 +748,10 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
       // DFC, Eq. (15)-(20)
       T v[9][NS];
       load_strip(v);
+      if constexpr (TURN) {
+#pragma unroll
+        for (int i = 0; i < 9; i++) quad_transpose(v[i], h);
+      }
       double gi[9];
 #pragma unroll
       for (int i = 0; i < 9; i++) {
@@ -787,7 +820,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
         // writes it, and every lane takes the corrected velocity for the slip.
         // One walk over the covering markers for the whole strip: in two walks of
         // two nodes (176 VGPRs instead of 222, two waves per SIMD either way) the
-        // D = 9 steps above take 22.6 and 21.7 us instead of 21.4 and 20.5.
+        // D = 9 steps above take 21.7 us instead of 20.5 in fp32.
         double sa = 0, sb = 0;
         double qa = 0, qb = 0;
         double corr[NS][9];

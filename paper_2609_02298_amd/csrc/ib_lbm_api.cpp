@@ -572,11 +572,12 @@ bool body_arcs(const HostBody &hb, int spread_mode) { return spread_mode == 0 &&
 // bodies take many arcs of 256 threads, whose repeated margins hold up the
 // tiles: 2000 x 800 MDF P4 fp32 23.9 us per step instead of 24.4, but fp64 36.5
 // instead of 35.5 and a batch of twelve 68.9 instead of 66.9.
-// DFC with the Peskin kernel is one arc as long as 512 threads hold its markers:
-// the arcs' meeting between reads and writes costs more than the second wave per
-// SIMD (free disk, D = 30, fp64 19.0 us per step in three arcs, 17.7 in one; fixed,
-// plain steps, 26.9 and 26.1).  With the hat kernel a fixed disk is slower so (D =
-// 78 fp32 14.5 and 15.2), so it is cut as the others are.
+// FP32 DFC with the Peskin kernel is one arc as long as 512 threads hold its
+// markers: the arcs' meeting between reads and writes costs more than the second
+// wave per SIMD (free disk, D = 30, 17.8 us per step in three arcs, 16.6 in one;
+// fixed, plain steps, 25.8 and 25.2).  FP64 keeps its arcs, and with them the order
+// of its sums; with the hat kernel a fixed disk is slower in one (D = 78 fp32 14.5
+// and 15.2).
 void plan_arcs(BodyDesc *B) {
   B->arc_n = 0;
   if (B->mdf_coupled || B->udes != kUdRigid) return;
@@ -594,7 +595,7 @@ void plan_arcs(BodyDesc *B) {
     if (nb <= cap) {
       own = nb;
       n = 1;
-    } else if (!adapt && cap - 2 * halo >= cap / 4 && !(B->scheme == kDFC && ns == 4 && nb <= 512 / ns)) {
+    } else if (!adapt && cap - 2 * halo >= cap / 4 && !(B->scheme == kDFC && ns == 4 && B->pop_bytes == 4 && nb <= 512 / ns)) {
       n = (int)((nb + cap - 2 * halo - 1) / (cap - 2 * halo));
       own = (nb + n - 1) / n;
       n = (nb + own - 1) / own;

@@ -36,8 +36,8 @@ def box(nx, ny, bodies, bc, col=ib.TRT, **kw):
 FAR = (ib.VEL_UNIFORM, ib.ZERO_GRADIENT, ib.VEL_UNIFORM, ib.VEL_UNIFORM)
 
 
-# markers per workgroup: 64 (P4) or 128 (hat) at 256 threads, DFC in one arc up to
-# 512 threads (P4), MDF of five passes up to 1024; below, at and above each bound, and many arcs
+# markers per workgroup: 64 (P4) or 128 (hat) at 256 threads, FP32 DFC in one arc
+# up to 512 threads (P4), MDF of five passes up to 1024; below, at and above each bound, and many arcs
 @pytest.mark.parametrize("scheme,kernel,nb", [
     (ib.DF, ib.PESKIN4, 64), (ib.DF, ib.PESKIN4, 65), (ib.DF, ib.PESKIN4, 301),
     (ib.DF, ib.HAT, 128), (ib.DF, ib.HAT, 129), (ib.DF, ib.HAT, 301),
@@ -68,6 +68,33 @@ def test_arcs_match_the_oracle(scheme, kernel, nb):
         assert rel(sim.populations(), ref.populations()) < F64_FIELD
         sim.close()
         ref.close()
+
+
+# FP32: strips by columns (Peskin) and rows, DFC in one arc up to 128 markers.  A
+# population's rounding (2^-24 of at most its maximum) enters each of the eight
+# steps through its nine-term sums
+@pytest.mark.parametrize("scheme,kernel,nb", [
+    (ib.DFC, ib.PESKIN4, 64), (ib.DFC, ib.PESKIN4, 65), (ib.DFC, ib.PESKIN4, 128), (ib.DFC, ib.PESKIN4, 129),
+    (ib.DFC, ib.HAT, 129), (ib.DF, ib.PESKIN4, 65), (ib.DF, ib.HAT, 129), (ib.MDF, ib.PESKIN4, 129),
+    (ib.MDF, ib.HAT, 301)])
+def test_fp32_arcs_match_the_oracle(scheme, kernel, nb):
+    D = nb / np.pi
+    n = int(D) + 40
+    print(f"fp32 arcs scheme={scheme} kernel={kernel} markers={nb}", flush=True)
+    case = box(n + 30, n, [dict(xc=n / 2 + 0.37, yc=n / 2 - 0.21, diameter=D, n_markers=nb, scheme=scheme,
+                                kernel=kernel, mdf_iters=5)], FAR, u_bc=0.06)
+    sim, ref = ib.Sim(case, precision=ib.FP32_SHIFTED), oracle.OracleSim(case)
+    ref.add_body(case["bodies"][0])
+    sim.step(8)
+    ref.step(8)
+    assert sim.step_form() == ib.STEP_ONE
+    a, b = sim.forces(0), ref.body_state(0)
+    bound = 8 * 9 * 2.0 ** -24
+    assert rel(sim.populations(), ref.populations()) < bound
+    # a marker's force is a difference of populations of at least 1/20 of them
+    assert abs(a["fx"] - b["fx"]) < 20 * bound * abs(b["fx"])
+    sim.close()
+    ref.close()
 
 
 # marker spacings just below and above those at which one neighbour more shares
