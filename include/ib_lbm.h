@@ -362,10 +362,13 @@ ib_lbm_status ib_lbm_get_overlap(const ib_lbm_sim *s, int32_t *in_use, int64_t *
  * ib_lbm_set_overlap).  A sim without bodies, or whose bodies all run their
  * pass in arcs (several workgroups per body: every body but coupled MDF,
  * IB_LBM_UD_TAYLOR_GREEN, atomic spreading, very small circles or dense
- * markers, and MDF bodies of many markers), takes one launch per step on the
- * sim's stream, with no second stream and no events, whatever its faces,
- * collision and motion: the arcs wait for the tiles whose updates they read
- * and run beside the others.  Of the rest, a pipelined sim whose single body
+ * markers, and MDF bodies of many markers; up to 56 arcs in all), takes one
+ * launch per step on the sim's stream, with no second stream and no events,
+ * whatever its faces, collision and motion: the arcs wait for the tiles whose
+ * updates they read and run beside the others.  Arcs that wait hold compute
+ * units, so the sims and batches of all streams share a number of them; one
+ * that finds too little left steps in several launches until its steps are
+ * planned anew (after a set_* call).  Of the rest, a pipelined sim whose single body
  * is fixed, DF or MDF on the 1024-thread IB kernel, with BGK or TRT and no
  * Zou-He wall, also takes one launch: workgroup 0 runs the IB pass and
  * collides the nodes that push into the body's support itself.  Results are
@@ -413,7 +416,8 @@ ib_lbm_status ib_lbm_stream_copy(const void *src, void *dst, size_t bytes, int32
 /* ---- batching: many independent sims stepped by shared launches ----
  * All sims of a batch share one precision and one stream.  A batch step is
  * one launch for everything when every body runs its pass in arcs (see
- * ib_lbm_set_fused), else a collide-stream and a face launch per collision
+ * ib_lbm_set_fused; up to the number that may wait at once) and the cases have
+ * at most 20 M nodes (FP32) or 40 M (FP64) in all, else a collide-stream and a face launch per collision
  * model present and the IB launches of all bodies; results are bitwise the
  * same.  Each sim keeps its own step count and target and stops at its own
  * target (ib_lbm_batch_set_target). */
