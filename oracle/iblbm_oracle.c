@@ -235,10 +235,11 @@ static void place_markers(or_body *b) {
 }
 
 static int supports_inside(const or_sim *s, const or_body *b) {
-  int ns = support_n(b->d.kernel);
+  /* in doubles: a marker may be beyond every int (or NaN) */
+  const double h = support_n(b->d.kernel) / 2;
   for (int k = 0; k < b->nb; k++) {
-    int x0 = support_lo(b->d.kernel, b->X[k]), y0 = support_lo(b->d.kernel, b->Y[k]);
-    if (x0 < 0 || y0 < 0 || x0 + ns - 1 > s->c.nx - 1 || y0 + ns - 1 > s->c.ny - 1) return 0;
+    const double x = floor(b->X[k]), y = floor(b->Y[k]);
+    if (!(x >= h - 1 && y >= h - 1 && x <= s->c.nx - 1 - h && y <= s->c.ny - 1 - h)) return 0;
   }
   return 1;
 }

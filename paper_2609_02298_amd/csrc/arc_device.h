@@ -260,16 +260,28 @@ struct ArcShared {
 // A stencil origin that covers no node.
 constexpr int kArcNowhere = 0x7fffffff;
 
+// floor(x) for sums of node numbers: a body's next position may be any number (a
+// force that blows up moves it by more than 2^31 nodes in one step), and the
+// conversion saturates, so that a sum with it would wrap to the other side.
+__device__ __forceinline__ int node_floor(double x) { return (int)fmax(-1e9, fmin(floor(x), 1e9)); }
+
+// Whether the NS nodes around coordinate X (first node floor(X) - (NS / 2 - 1))
+// lie in 0 .. n - 1; false for NaN.  Compared as doubles, as above.
+__device__ __forceinline__ bool support_in(double X, int ns, int n) {
+  const double i = floor(X);
+  return i >= ns / 2 - 1 && i <= n - 1 - ns / 2;
+}
+
 // What the next step's pass waits for: the nodes whose pushes (two nodes
 // around its support, with the walls it may close) or reads of this step's
 // force reach its support, for a body at (x, y) now and (xn, yn) then; one
 // node wider than the circle's box for rounding.
 __device__ __forceinline__ void arc_hold(double x, double y, double xn, double yn, double r, int s1, int nx,
                                          int ny, int32_t *h) {
-  h[0] = max(0, (int)floor(fmin(xn, x) - r) - s1 - 3);
-  h[1] = max(0, (int)floor(fmin(yn, y) - r) - s1 - 3);
-  h[2] = min(nx - 1, (int)floor(fmax(xn, x) + r) + s1 + 4);
-  h[3] = min(ny - 1, (int)floor(fmax(yn, y) + r) + s1 + 4);
+  h[0] = max(0, node_floor(fmin(xn, x) - r) - s1 - 3);
+  h[1] = max(0, node_floor(fmin(yn, y) - r) - s1 - 3);
+  h[2] = min(nx - 1, node_floor(fmax(xn, x) + r) + s1 + 4);
+  h[3] = min(ny - 1, node_floor(fmax(yn, y) + r) + s1 + 4);
 }
 
 // Density and momentum of one node's populations (g = f - w rho0 in FP32).
@@ -375,8 +387,7 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
     const double R = B.radius;
     if (!(xc - R >= s1 + 1 && yc - R >= s1 + 1 && xc + R <= nx - NS && yc + R <= ny - NS)) {
       for (int q = tid; q < nb; q += blockDim.x) {
-        const int ix = (int)floor(xc + R * B.cos_t[q]) - s1, iy = (int)floor(yc + R * B.sin_t[q]) - s1;
-        if (ix < 0 || iy < 0 || ix + NS - 1 > nx - 1 || iy + NS - 1 > ny - 1) fail = 1;
+        if (!support_in(xc + R * B.cos_t[q], NS, nx) || !support_in(yc + R * B.sin_t[q], NS, ny)) fail = 1;
       }
       fail = __syncthreads_or(fail);
     }
@@ -384,7 +395,8 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   const double X = xc + B.radius * ct, Y = yc + B.radius * st;
   const double udx = sh.kin.udx - sh.kin.udo * (Y - yc), udy = sh.kin.udy + sh.kin.udo * (X - xc);
   const double ds = B.ds;
-  const int ix0 = (int)floor(X) - s1, iy0 = (int)floor(Y) - s1;
+  // (a body that does not fit keeps no origin: nothing is read or written for it)
+  const int ix0 = fail ? 0 : (int)floor(X) - s1, iy0 = fail ? 0 : (int)floor(Y) - s1;
   const int s0 = COLS ? iy0 : ix0;        // where the strip starts
   const int ln = (COLS ? ix0 : iy0) + h;  // the column or row it lies in
   double a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0, a6 = 0;  // fx fy torque slip | residual slip_max
@@ -393,10 +405,10 @@ __device__ __forceinline__ void arc_pass(const CaseDesc &c, BODY &B, int64_t ste
   if (tid == 64) {
     // what the end of the pass writes and the position alone decides
     const double r = B.radius;
-    sh.box[0] = max(0, (int)floor(xc - r) - NS);
-    sh.box[1] = max(0, (int)floor(yc - r) - NS);
-    sh.box[2] = min(nx - 1, (int)floor(xc + r) + NS + 1);
-    sh.box[3] = min(ny - 1, (int)floor(yc + r) + NS + 1);
+    sh.box[0] = max(0, node_floor(xc - r) - NS);
+    sh.box[1] = max(0, node_floor(yc - r) - NS);
+    sh.box[2] = min(nx - 1, node_floor(xc + r) + NS + 1);
+    sh.box[3] = min(ny - 1, node_floor(yc + r) + NS + 1);
     if (motion != kFree) {
       const bool driven = motion == kPrescribedSin;
       arc_hold(xc, yc, driven ? sh.next.xc : xc, driven ? sh.next.yc : yc, r, s1, nx, ny, sh.hold);

@@ -325,10 +325,13 @@ __device__ __forceinline__ int build_tables(const CaseDesc &c, const BodyDesc &B
     L.Y[k] = Y;
     L.Udx[k] = udx - udo * (Y - yc);
     L.Udy[k] = udy + udo * (X - xc);
+    if (!support_in(X, ns, nx) || !support_in(Y, ns, ny)) {
+      atomicOr(&ish[0], kFlagRange);
+      continue;
+    }
     const int ix0 = (int)floor(X) - (s - 1), iy0 = (int)floor(Y) - (s - 1);
     L.ix0[k] = ix0;
     L.iy0[k] = iy0;
-    if (ix0 < 0 || iy0 < 0 || ix0 + ns - 1 > nx - 1 || iy0 + ns - 1 > ny - 1) atomicOr(&ish[0], kFlagRange);
     for (int j = 0; j < ns; j++) {
       WX(L, k, j) = delta1(B.kernel, (double)(ix0 + j) - X);
       WY(L, k, j) = delta1(B.kernel, (double)(iy0 + j) - Y);
@@ -683,7 +686,7 @@ __device__ __forceinline__ void body_step(const CaseDesc &c, const BodyDesc &B, 
   constexpr bool in_lds = LDS;
   double *base = LDS ? dyn : B.ws;
   const WsLayout L = carve(base, B);
-  const int ylo = (int)floor(yc - B.radius) - ns;
+  const int ylo = node_floor(yc - B.radius) - ns;
   const bool fixed = B.motion == kFixed;
 
   // ---- 2-3. tables: cached for fixed bodies

@@ -1289,3 +1289,19 @@ def test_taylor_green_markers_carry_the_analytic_velocity():
     amp = u0 * math.exp(-2 * nu * k * k * 1)
     np.testing.assert_allclose(m[:, 4], -2 * amp * np.cos(k * m[:, 0]) * np.sin(k * m[:, 1]), atol=1e-15)
     np.testing.assert_allclose(m[:, 5], 2 * amp * np.sin(k * m[:, 0]) * np.cos(k * m[:, 1]), atol=1e-15)
+
+
+@pytest.mark.parametrize("u", [(0.01, 0.0), (-0.01, 0.0), (0.0, 0.01), (0.0, -0.01), (0.01, 0.01)])
+@pytest.mark.parametrize("kernel", [HAT, PESKIN4])
+def test_a_body_thrown_beyond_every_node_number_is_out_of_range(kernel, u):
+    """A light body that the first step's force throws further than 2^31 nodes
+    is outside the lattice, whichever way it went."""
+    import ib_cases
+    body = dict(xc=50.3, yc=44.6, diameter=14.0, scheme=DF, kernel=kernel, motion=oracle.FREE,
+                density_ratio=1e-13, integrator=oracle.EULER_A1)
+    s = oracle.OracleSim(dict(nx=100, ny=90, collision=oracle.TRT, tau=0.68, bc=(oracle.PERIODIC,) * 4, bodies=[body]))
+    s.add_body(body)
+    s.set_populations(ib_cases.random_populations(100, 90, 5, amp=0.0, u=u))
+    assert s.step(1) == 0 and s.step(1) != 0
+    st = s.body_state(0)
+    assert max(abs(st["xc"]), abs(st["yc"])) > 2.0 ** 31 and s.steps_done == 1

@@ -245,6 +245,51 @@ def test_a_case_halted_at_a_wall_is_left_as_plain_steps_leave_it(name, prec):
     assert 1 < done < 121 and ib_lbm.STATUS[body["status"]] == status
 
 
+# A light body under the explicit Euler update, which the first step's force
+# throws further than 2^31 nodes: the second step finds it outside, whichever
+# way it went, and reads nothing there.  (The int of a node so far out saturates.)
+# One arc and several, and the pass without arcs
+@pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
+@pytest.mark.parametrize("u", [(0.01, 0.0), (-0.01, 0.0), (0.0, 0.01), (0.01, 0.01), (-0.01, -0.01)])
+@pytest.mark.parametrize("arcs", [True, False])
+@pytest.mark.parametrize("scheme,kernel,D", [(ib.DF, ib.PESKIN4, 14.0), (ib.DF, ib.HAT, 60.0), (ib.DFC, ib.HAT, 14.0),
+                                             (ib.DFC, ib.PESKIN4, 60.0), (ib.MDF, ib.PESKIN4, 60.0)])
+def test_a_body_thrown_beyond_every_node_number_is_out_of_range(scheme, kernel, D, arcs, u, prec):
+    print(f"thrown {scheme} {kernel} D={D} arcs={arcs} u={u} prec={prec}", flush=True)
+    body = dict(xc=50.3, yc=44.6, diameter=D, scheme=scheme, kernel=kernel, mdf_iters=2, motion=ib.FREE,
+                density_ratio=1e-13, internal_mass=ib.IM_NONE, integrator=ib.EULER_A1)
+    case = box(100, 90, [body], PER)
+    pops = ib_cases.random_populations(100, 90, 5, amp=0.0, u=u)
+    o = oracle.OracleSim(case)
+    o.add_body(body)
+    o.set_populations(pops)
+    assert o.step(1) == 0 and o.step(1) != 0
+    ref = o.body_state()
+    o.close()
+    assert max(abs(ref["xc"]), abs(ref["yc"])) > 2.0 ** 31
+    left = []
+    for over in (False, True):
+        sim = ib.Sim(case, precision=prec)
+        sim.set_overlap(over)
+        if not arcs:
+            sim.set_spread(ib.SPREAD_ATOMIC)
+        sim.set_populations(pops)
+        sim.step(1)
+        first = sim.populations()
+        sim.step(3)
+        if arcs:
+            assert sim.step_form() == (ib.STEP_ONE if over else ib.STEP_PLAIN)
+        st = sim.forces(0, check=False)
+        left.append((sim.steps_done, sim.populations(), st))
+        sim.close()
+        assert left[-1][0] == 1 and ib_lbm.STATUS[st["status"]] == "E_RANGE"
+        assert np.array_equal(left[-1][1], first) and np.isfinite(first).all()
+        # the force of the first step, times 1 / mass: the schemes' tolerance against the oracle
+        d, r = np.array([st["xc"] - 50.3, st["yc"] - 44.6]), np.array([ref["xc"] - 50.3, ref["yc"] - 44.6])
+        assert np.abs(d - r).max() <= (1e-9 if prec == ib.FP64 else 1e-3) * np.abs(r).max()
+    assert np.array_equal(left[0][1], left[1][1]) and left[0][2] == left[1][2]
+
+
 # a small disk in a corner of two Zou-He walls: its support holds the node
 # diagonally inside the corner, which closes the corner, but not the corner
 @pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
