@@ -204,8 +204,8 @@ typedef struct {
  * ib_threads: workgroup size of an IB pass of one workgroup per body: 0 for
  * the library's choice (1024 for DF/MDF bodies whose workspace fits in LDS,
  * 512 otherwise), or 256, 512 or 1024 (the second kind takes at most 512).  A
- * pass in arcs has the size its markers need, and fused steps the tile shape
- * that goes with it. */
+ * pass in arcs has the size its markers need, and steps in one launch the
+ * tile shape that goes with it: there the launch shape changes nothing. */
 typedef struct {
   int32_t block_x, block_y, rows_per_thread;
   int32_t xcd_remap; /* 1: keep neighbouring tiles on one XCD */
@@ -417,10 +417,10 @@ ib_lbm_status ib_lbm_stream_copy(const void *src, void *dst, size_t bytes, int32
  * All sims of a batch share one precision and one stream.  A batch step is
  * one launch for everything when every body runs its pass in arcs (see
  * ib_lbm_set_fused; up to the number that may wait at once) and the cases have
- * at most 20 M nodes (FP32) or 40 M (FP64) in all, else a collide-stream and a face launch per collision
- * model present and the IB launches of all bodies; results are bitwise the
- * same.  Each sim keeps its own step count and target and stops at its own
- * target (ib_lbm_batch_set_target). */
+ * at most 20 M nodes (FP32) or 40 M (FP64) in all, else a collide-stream and a
+ * face launch per collision model present and the IB launches of all bodies;
+ * results are bitwise the same.  Each sim keeps its own step count and target
+ * and stops at its own target (ib_lbm_batch_set_target). */
 ib_lbm_status ib_lbm_batch_create(void *stream, int32_t precision, ib_lbm_batch **out);
 ib_lbm_status ib_lbm_batch_attach(ib_lbm_batch *b, ib_lbm_sim *s);
 ib_lbm_status ib_lbm_batch_detach(ib_lbm_batch *b, ib_lbm_sim *s);
