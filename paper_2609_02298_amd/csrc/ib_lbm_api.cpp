@@ -1339,13 +1339,13 @@ ib_lbm_status ib_lbm_add_body(ib_lbm_sim *s, const ib_lbm_body_desc *b, int32_t 
     ct[k] = std::cos(th);
     stb[k] = std::sin(th);
   }
-  // every support inside the lattice at the start position
+  // every support inside the lattice at the start position (compared as doubles: a
+  // position may be beyond every int, or NaN)
   const int sw = B.ns / 2;
   auto inside = [&](double xc, double yc) {
     for (int k = 0; k < nb; k++) {
-      const double X = xc + B.radius * ct[k], Y = yc + B.radius * stb[k];
-      const int ix0 = (int)std::floor(X) - (sw - 1), iy0 = (int)std::floor(Y) - (sw - 1);
-      if (ix0 < 0 || iy0 < 0 || ix0 + B.ns - 1 > s->cfg.nx - 1 || iy0 + B.ns - 1 > s->cfg.ny - 1) return false;
+      const double ix = std::floor(xc + B.radius * ct[k]), iy = std::floor(yc + B.radius * stb[k]);
+      if (!(ix >= sw - 1 && iy >= sw - 1 && ix <= s->cfg.nx - 1 - sw && iy <= s->cfg.ny - 1 - sw)) return false;
     }
     return true;
   };

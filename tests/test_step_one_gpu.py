@@ -290,6 +290,22 @@ def test_a_body_thrown_beyond_every_node_number_is_out_of_range(scheme, kernel, 
     assert np.array_equal(left[0][1], left[1][1]) and left[0][2] == left[1][2]
 
 
+@pytest.mark.parametrize("kernel", [ib.HAT, ib.PESKIN4])
+def test_a_body_placed_beyond_every_node_number_is_refused(kernel):
+    base = dict(xc=50.3, yc=44.6, diameter=14.0, scheme=ib.DF, kernel=kernel, n_markers=40)
+    bad = [dict(base, xc=x) for x in (3e9, -3e9, 1e300, float("inf"), float("nan"))]
+    bad += [dict(base, yc=y) for y in (3e9, -3e9)] + [dict(base, diameter=1e12)]
+    bad += [dict(base, motion=ib.PRESCRIBED_SIN, amp=a, freq=1e-3) for a in ((1e12, 0.0), (0.0, -1e12))]
+    sim = ib.Sim(box(100, 90, [], PER))
+    for b in bad:
+        print(f"refused {b}", flush=True)
+        with pytest.raises(ib.IbLbmError) as e:
+            sim.add_body(b)
+        assert e.value.status == -5
+    assert sim.add_body(base) == 0
+    sim.close()
+
+
 # a small disk in a corner of two Zou-He walls: its support holds the node
 # diagonally inside the corner, which closes the corner, but not the corner
 @pytest.mark.parametrize("prec", [ib.FP64, ib.FP32_SHIFTED])
